@@ -843,7 +843,7 @@ __device__ __forceinline__ void gram_sum_chunks(const double *__restrict__ Gpart
     }
 }
 
-// K <= 64: the whole solve on one wave (panel LDL^T with MFMA updates, ldl_blk64).
+// K <= 64: the whole solve on one wave (LDL^T on 16 x 16 tiles, ldl_blk64).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_chol_wave(
     const double *__restrict__ Gpart, int nch, int K, double lambda,
     const double *__restrict__ rI, const double *__restrict__ Pin, int nchP, int bmax,
@@ -851,8 +851,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     constexpr int NTH = 256;
     __shared__ double Gp[64 * 65 / 2];
     __shared__ double z[64];
-    __shared__ double colbuf[2 * 64];
-    __shared__ double Lc[64 * 65];
+    __shared__ double Lc[LB_LEN];
     // the stop flag is read by a vector load issued with the chunk loads (the
     // Gram buffer is valid either way), so the two latencies overlap
     const int stop = __hip_atomic_load(&ctrl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -886,7 +885,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     __syncthreads();
     // one wave from here on; the other waves leave and no block barrier follows
     if (threadIdx.x >= 64) return;
-    if (!ldl_blk64(Lc, z, K, colbuf)) {
+    if (!ldl_blk64(Lc, z, K)) {
         if (threadIdx.x == 0) {
             ctrl->status = RORBK_ERR_NOT_SPD;
             ctrl->done = 1;

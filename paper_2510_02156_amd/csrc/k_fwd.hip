@@ -750,7 +750,7 @@ struct FwdChainP {
 constexpr int CHN = 4;                       // most column chunks of G and C
 constexpr int FC_T = FWD_T - 64;             // threads of waves 1-7
 constexpr int FILL2 = (3 * FWD_B * FWD_B + FC_T - 1) / FC_T;   // H2, G32, H3 entries per thread
-constexpr int LA = 64 * 65 + 2 * 64;                          // LDS doubles: work matrix | colbuf
+constexpr int LA = LB_LEN;                                     // LDS doubles of region a
 
 template <typename T, typename V, bool AL, int RN>
 __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
@@ -763,8 +763,9 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
     V *__restrict__ x = (V *)p.x;
     const int tid = threadIdx.x;
     const int K = p.K, KP = K * (K + 1) / 2;
-    // LDS: region a holds the factorisation (the padded system, then L; column buffers),
-    // then z, y and the update's row sums; region b holds C, then H2, G32, H3
+    // LDS: region a holds the factorisation (the padded system, then its
+    // tiles), then z, y and the update's row sums; region b holds C, then H2,
+    // G32, H3
     __shared__ double lds_a[LA];
     __shared__ double lds_b[3 * FWD_B * LDM];
     __shared__ double s_yk[64], s_rs[3 * FWD_B];
@@ -772,7 +773,7 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
     __shared__ V s_x[SWC];
     __shared__ int32_t s_row[64 + 3 * FWD_B], s_slot[64 + 3 * FWD_B];
     __shared__ int s_ok;
-    double *Lc = lds_a, *colbuf = Lc + 64 * 65;
+    double *Lc = lds_a;
     double *s_z = lds_a, *s_y = lds_a + 256;
     V (*s_red)[SWC] = reinterpret_cast<V (*)[SWC]>(lds_a + 1024);
 
@@ -809,7 +810,7 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
     // wave index is made scalar so that both branches are real jumps) ...
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wv == 0) {
-        const bool ok = ldl_blk64(Lc, s_yk, K, colbuf);
+        const bool ok = ldl_blk64(Lc, s_yk, K);
         if (tid == 0) {
             s_ok = ok ? 1 : 0;
             if (!ok) {
