@@ -70,7 +70,8 @@ __global__ __launch_bounds__(64 * NW) void k_xgram(const T *__restrict__ A, int6
 // ------------------------------------------------- Grams of the chain form --
 // After the selection of iteration it, with the blocks S' drawn for iteration
 // it + 1 at tau[ti .. ti+2]: the greedy Gram A_I A_I^T (packed lower) and
-// C = A_{S'} A_I^T (C[(l * FWD_B + i) * 64 + j] = <row i of block l, row I_j>),
+// C = A_{S'} A_I^T (C[j * CHAIN_S + l * FWD_B + i] = <row i of block l, row
+// I_j>, so that the consumer's loads over a block's rows are contiguous),
 // as partial sums over nch column chunks (chunk ch at G + ch * K(K+1)/2 and
 // C + ch * CHAIN_C).  Since A_{S'} (x + A_I^T y) = A_{S'} x + C y, the next
 // iteration's z = b_{S'} - A_{S'} x_new = r_{S'} - C y follows from the
@@ -80,7 +81,8 @@ __global__ __launch_bounds__(64 * NW) void k_xgram(const T *__restrict__ A, int6
 // MFMA step) and are summed in wave order.  (The cross-Grams of S' do not
 // depend on I and are formed by spare workgroups of the selection.)
 constexpr int GC_W = 8;
-constexpr int CHAIN_C = 3 * FWD_B * 64;   // doubles of one chunk of C
+constexpr int CHAIN_S = 3 * FWD_B;        // slots of S' rows
+constexpr int CHAIN_C = CHAIN_S * 64;     // doubles of one chunk of C
 
 struct GramChainP {
     const void *A;
@@ -92,7 +94,7 @@ struct GramChainP {
     int64_t ti;
     int64_t wc;     // columns per chunk (a multiple of 32)
     double *G;      // [nch][K (K + 1) / 2], packed lower
-    double *C;      // [nch][3 * FWD_B][64]
+    double *C;      // [nch][64][3 * FWD_B]
     const Ctrl *ctrl;
 };
 
@@ -136,10 +138,13 @@ __global__ __launch_bounds__(64 * GC_W) void k_gram_chain(GramChainP p) {
     if (kind == 0) {
         ra = (ia < K) ? (int64_t)Ia : -1;
     } else {
+        // tile rows j (greedy rows), tile columns i (the block's rows): a
+        // wave's stores then run along the slots
         const int64_t t = p.tau[p.ti + l];
         ca = blk_rows(t, p.q, p.rem);
         if (bi * 16 >= ca) return;   // uniform: a tile past the block
-        ra = (ia < ca) ? blk_start(t, p.q, p.rem) + ia : -1;
+        ra = rb;
+        rb = (ia < ca) ? blk_start(t, p.q, p.rem) + ia : -1;
     }
     if (stop) return;
     const int64_t c0 = (int64_t)ch * p.wc;
@@ -160,11 +165,12 @@ __global__ __launch_bounds__(64 * GC_W) void k_gram_chain(GramChainP p) {
         double s = red[0][lane][r];
 #pragma unroll
         for (int v = 1; v < GC_W; ++v) s += red[v][lane][r];
-        const int ii = bi * 16 + (lane >> 4) + 4 * r, jj = bj * 16 + li;
         if (kind == 0) {
+            const int ii = bi * 16 + (lane >> 4) + 4 * r, jj = bj * 16 + li;
             if (ii < K && jj <= ii) p.G[(int64_t)ch * (K * (K + 1) / 2) + pk(ii, jj)] = s;
         } else {
-            if (ii < ca && jj < K) p.C[(int64_t)ch * CHAIN_C + (l * FWD_B + ii) * 64 + jj] = s;
+            const int jj = bj * 16 + (lane >> 4) + 4 * r, ii = bi * 16 + li;
+            if (ii < ca && jj < K) p.C[(int64_t)ch * CHAIN_C + jj * CHAIN_S + l * FWD_B + ii] = s;
         }
     }
 }
@@ -402,12 +408,12 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_greedy(FwdGreedyP p) {
 // x[cols] += A_S[:, cols]^T y over the rows of all three blocks.
 //
 // Memory round trips: the draws, then everything else at once.  Thread range
-// k = 0, 1, 2 (2 FWD_B threads each) reads H1, G21, G31 into registers
-// (thread u of a range takes row u / 2 and columns (u % 2) + 2 t); every
-// thread reads its share of H2, G32, H3, which go to LDS once the first two
-// stages are done; every thread also loads its entries of x and z, and its
-// rows of the update once the registers of the first half are free.  Each
-// stage of the chain is then register or LDS work, a shuffle and a barrier.
+// k = 0, 1, 2 (two waves each, a pair of threads per row; row 64 of the three
+// ranges on one more wave, see chain_rows) reads two of the six matrices into
+// registers: H1 and H2, G21 and G32, G31 and H3.  Every thread also loads its entries of x and z, and its rows of
+// the update once the first matrix's registers are free.  Each stage of the
+// chain is then 16-byte LDS reads of a vector, register FMAs, a pair sum by
+// DPP and a barrier.
 // Chain form (K > 0): the previous iteration's greedy rows I with their y
 // join the update, x += A_I^T y_I + sum_l A_l^T y_l, in the same pass (z then
 // already accounts for the greedy step, see k_gram_chain).
@@ -428,61 +434,117 @@ struct FwdSamp3P {
     const double *y;
 };
 
-constexpr int MC = (FWD_B + 1) / 2;          // matrix entries per thread and row pair
-constexpr int LDM = FWD_B;                   // row stride of the matrices kept in LDS
-constexpr int FILL = (3 * FWD_B * FWD_B + FWD_T - 1) / FWD_T;   // LDS entries per thread
+// A pair of threads (h = 0, 1) shares a matrix row of at most FWD_B entries:
+// thread h takes the entries hb h + t, t < hb, with hb = mv_half(columns), a
+// multiple of MG, so that the vector entries it needs are 16-byte LDS reads
+// and no group of MG entries needs a bound of its own.
+constexpr int MG = 4;
+constexpr int MC = ((FWD_B + 1) / 2 + MG - 1) / MG * MG;   // most entries per thread
+__device__ __forceinline__ int mv_half(int cols) { return ((cols + 1) / 2 + MG - 1) / MG * MG; }
+// LDS slots per block of the vectors mv_dot reads; the slots past the block
+// hold zeros, which meet whatever finite entries mv_load read past the matrix
+constexpr int ZS = 2 * MC;
 
-// Entry (i, j) of a matrix stored at M[i * si + j * sj] into m[t] for
-// j = h + 2 t, zero outside rows x cols; every load reads an in-bounds
-// address (entry (0, 0) stands in) so that none sits behind a branch.
-__device__ __forceinline__ void mv_load(const double *__restrict__ M, int64_t si, int64_t sj,
-                                        int i, int h, int rows, int cols, double (&m)[MC]) {
-    const bool okr = i < rows;
+// The other lane's value of a pair of lanes (2 u, 2 u + 1).
+__device__ __forceinline__ double pair_other(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0xb1, 0xf, 0xf, false);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0xb1, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Entry (i, hb h + t) of a rows x cols matrix stored at M[i + j * sj] into
+// m[t] (rows past it get some other row's entries, whose product is not used).
+// Up to nine columns past the matrix are read, finite numbers that meet
+// zeros: the stored inverses and the cross-Grams are allocated with
+// RORBK_FWD_PAD doubles behind them and cleared at setup where nothing else
+// writes.  So a load is an address addition and no select; clamping
+// every address cost 6 us for a thread's two matrices, and a select on the
+// loaded value made the compiler wait for every load by itself (12 us).
+__device__ __forceinline__ void mv_load(const double *__restrict__ M, uint32_t sj, int i, int h,
+                                        int rows, int hb, double (&m)[MC]) {
+    const double *pm = M + (uint32_t)(i < rows ? i : 0) + (h ? (uint32_t)hb * sj : 0u);
 #pragma unroll
-    for (int t = 0; t < MC; ++t) {
-        const int j = h + 2 * t;
-        const bool ok = okr && j < cols;
-        const double v = M[ok ? (int64_t)i * si + (int64_t)j * sj : 0];
-        m[t] = ok ? v : 0.0;
+    for (int t0 = 0; t0 < MC; t0 += MG)
+        if (t0 < hb) {   // uniform
+#pragma unroll
+            for (int t = t0; t < t0 + MG; ++t) {
+                m[t] = *pm;
+                pm += sj;
+            }
+        }
+}
+
+// sum_t m[t] vin[hb h + t] over the pair of threads: four accumulators in a
+// fixed order, then the pair's sum.
+__device__ __forceinline__ double mv_dot(const double (&m)[MC], const double *vin, int h, int hb) {
+    const double *v = vin + h * hb;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t0 = 0; t0 < MC; t0 += MG)
+        if (t0 < hb) {
+            const dvec2 w0 = *reinterpret_cast<const dvec2 *>(v + t0);
+            const dvec2 w1 = *reinterpret_cast<const dvec2 *>(v + t0 + 2);
+            a[0] = __builtin_fma(m[t0], w0[0], a[0]);
+            a[1] = __builtin_fma(m[t0 + 1], w0[1], a[1]);
+            a[2] = __builtin_fma(m[t0 + 2], w1[0], a[2]);
+            a[3] = __builtin_fma(m[t0 + 3], w1[1], a[3]);
+        }
+    const double s = (a[0] + a[1]) + (a[2] + a[3]);
+    return s + pair_other(s);
+}
+
+// Thread range rg (3: none), row i and half h of thread `lane` of wave w: the
+// same range over a whole wave for rows below 64, so that the matrices' bases
+// and strides are scalars there.
+__device__ __forceinline__ void chain_rows(int w, int lane, int *rg, int *i, int *h) {
+    *h = lane & 1;
+    if (w < 6) {
+        *rg = w >> 1;
+        *i = 32 * (w & 1) + (lane >> 1);
+    } else {
+        *rg = (w == 6 && lane < 6) ? lane >> 1 : 3;
+        *i = 64;
     }
 }
 
-// sum_j m[t] vin[h + 2 t] over the pair of threads: four accumulators in a
-// fixed order, then the pair's sum.  Entries past the matrix are zero in m,
-// and vin holds finite values at every index read (h + 2 t < FWD_B + 1 is
-// clamped).
-__device__ __forceinline__ double mv_dot(const double (&m)[MC], const double *vin, int h) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-#pragma unroll
-    for (int t = 0; t < MC; t += 4) {
-        a0 = __builtin_fma(m[t], vin[(h + 2 * t) < FWD_B ? h + 2 * t : 0], a0);
-        if (t + 1 < MC) a1 = __builtin_fma(m[t + 1], vin[h + 2 * t + 2], a1);
-        if (t + 2 < MC) a2 = __builtin_fma(m[t + 2], vin[h + 2 * t + 4], a2);
-        if (t + 3 < MC) a3 = __builtin_fma(m[t + 3], vin[h + 2 * t + 6], a3);
+// The two matrices of thread range rg (see above): m for the first two stages
+// of the chain, m2 for the last three; H1, H2, H3 are symmetric, the
+// cross-Grams column-major.
+__device__ __forceinline__ void chain_mats(const double *__restrict__ H,
+                                           const double *__restrict__ xg, int64_t hoff0,
+                                           int64_t hoff1, int64_t hoff2, int n0, int n1, int n2,
+                                           int bm, int rg, int i, int h, int hb, double (&m)[MC],
+                                           double (&m2)[MC]) {
+    const double *M = H, *M2 = H;
+    uint32_t sj = 1, sj2 = 1;
+    int rows = 0, rows2 = 0;
+    if (rg == 0) {
+        M = H + hoff0; sj = n0; rows = n0;                        // H1
+        M2 = H + hoff1; sj2 = n1; rows2 = n1;                     // H2
+    } else if (rg == 1) {
+        M = xg; sj = bm; rows = n1;                               // G21
+        M2 = xg + 2 * (int64_t)bm * bm; sj2 = bm; rows2 = n2;     // G32
+    } else if (rg == 2) {
+        M = xg + (int64_t)bm * bm; sj = bm; rows = n2;            // G31
+        M2 = H + hoff2; sj2 = n2; rows2 = n2;                     // H3
     }
-    const double s = (a0 + a1) + (a2 + a3);
-    const double o = __shfl_xor(s, 1, 2);
-    return h ? (o + s) : (s + o);
+    mv_load(M, sj, i, h, rows, hb, m);
+    mv_load(M2, sj2, i, h, rows2, hb, m2);
 }
 
-// The same product with the matrix row in LDS (L[i * LDM + j], zero outside
-// the matrix; a column index past the row, h + 2 t = FWD_B, contributes 0).
-__device__ __forceinline__ double mv_dot_lds(const double *L, int i, const double *vin, int h) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    const double *Lr = L + (i < FWD_B ? i : 0) * LDM;
-#pragma unroll
-    for (int t = 0; t < MC; t += 4) {
-        const int j0 = h + 2 * t;
-        const bool in = j0 < FWD_B;
-        const double lv = Lr[in ? j0 : 0];
-        a0 = __builtin_fma(in ? lv : 0.0, vin[in ? j0 : 0], a0);
-        if (t + 1 < MC) a1 = __builtin_fma(Lr[j0 + 2], vin[j0 + 2], a1);
-        if (t + 2 < MC) a2 = __builtin_fma(Lr[j0 + 4], vin[j0 + 4], a2);
-        if (t + 3 < MC) a3 = __builtin_fma(Lr[j0 + 6], vin[j0 + 6], a3);
-    }
-    const double s = (a0 + a1) + (a2 + a3);
-    const double o = __shfl_xor(s, 1, 2);
-    return h ? (o + s) : (s + o);
+// The same for wave w (scalar; see chain_rows): scalar bases where a wave
+// holds one range, and the seventh wave only where blocks have a row 64.
+__device__ __forceinline__ void chain_mats_wave(const double *__restrict__ H,
+                                                const double *__restrict__ xg, int64_t hoff0,
+                                                int64_t hoff1, int64_t hoff2, int n0, int n1,
+                                                int n2, int bm, int w, int rg, int i, int h, int hb,
+                                                double (&m)[MC], double (&m2)[MC]) {
+    if (w < 6)
+        chain_mats(H, xg, hoff0, hoff1, hoff2, n0, n1, n2, bm, w >> 1, i, h, hb, m, m2);
+    else if (w == 6 && bm > 64)
+        chain_mats(H, xg, hoff0, hoff1, hoff2, n0, n1, n2, bm, rg, i, h, hb, m, m2);
 }
 
 template <typename T, typename V, bool AL, int RN, bool MS>
@@ -509,8 +571,7 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
 
     __shared__ V s_x[1024];
     __shared__ V s_red[G][SWC];
-    __shared__ double s_z[3 * FWD_B], s_y[3 * FWD_B + 64];
-    __shared__ double s_m[3 * FWD_B * LDM];
+    __shared__ __align__(16) double s_z[3 * ZS], s_y[3 * ZS + 64];
     static_assert(64 + 3 * FWD_B <= FWD_T, "one row-table entry per thread");
     __shared__ int32_t s_row[64 + 3 * FWD_B], s_slot[64 + 3 * FWD_B];
     const int K = p.K;
@@ -523,7 +584,10 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
         const V t = x[c0 + (c < wcols ? c : 0)];
         xv[u] = (c < wcols) ? t : (V)0;
     }
-    const double zv = p.z3[tid < 3 * FWD_B ? tid : 0];
+    const int zl = tid / ZS, zi = tid - zl * ZS;   // slot of z (l, i), padded with zeros
+    const bool zok = zl < 3 && zi < FWD_B;
+    const double zt = p.z3[zok ? zl * FWD_B + zi : 0];
+    const double zv = zok ? zt : 0.0;
     // chain form: the greedy rows and their y (uniform branch)
     int32_t iv = 0;
     double ygv = 0.0;
@@ -531,33 +595,13 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
         iv = p.I[tid < K ? tid : 0];
         ygv = p.y[tid < K ? tid : 0];
     }
-    // the first three matrices of the chain, one per thread range
-    const int rg = tid / (2 * FWD_B), uu = tid - rg * 2 * FWD_B, ir = uu >> 1, h = uu & 1;
-    double m[MC];
-    {
-        const double *M = p.H;
-        int64_t sj = 1;
-        int rows = 0, cols = 0;
-        if (rg == 0) { M = p.H + hoff0; sj = n0; rows = n0; cols = n0; }   // H1 read transposed
-        else if (rg == 1) { M = p.xg; sj = bm; rows = n1; cols = n0; }     // G21, column-major
-        else if (rg == 2) { M = p.xg + (int64_t)bm * bm; sj = bm; rows = n2; cols = n0; }   // G31
-        mv_load(M, 1, sj, ir, h, rows, cols, m);
-    }
-    // this thread's share of H2, G32, H3 (for LDS), zero outside each matrix;
-    // consecutive threads take consecutive i, i.e. consecutive addresses
-    double fv[FILL];
-#pragma unroll
-    for (int u = 0; u < FILL; ++u) {
-        const int e = tid + u * FWD_T;
-        const int k = e / (FWD_B * FWD_B), rr = e - k * FWD_B * FWD_B;
-        const int j = rr / FWD_B, i = rr - j * FWD_B;    // LDS position (i, j)
-        const double *M = (k == 0) ? p.H + hoff1 : ((k == 1) ? p.xg + 2 * (int64_t)bm * bm : p.H + hoff2);
-        const int rows = (k == 0) ? n1 : n2, cols = (k == 1) ? n1 : (k == 0 ? n1 : n2);
-        const int64_t sj = (k == 1) ? bm : (k == 0 ? n1 : n2);
-        const bool ok = k < 3 && i < rows && j < cols;
-        const double t = M[ok ? i + (int64_t)j * sj : 0];
-        fv[u] = ok ? t : 0.0;
-    }
+    // two matrices per thread range (H symmetric, read along its rows)
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int rg, ir, h;
+    chain_rows(wv, tid & 63, &rg, &ir, &h);
+    const int hb = mv_half(bm);
+    double m[MC], m2[MC];
+    chain_mats_wave(p.H, p.xg, hoff0, hoff1, hoff2, n0, n1, n2, bm, wv, rg, ir, h, hb, m, m2);
     // row r of this thread's share of the update: its index in A (row 0
     // stands in past the last row) and its slot in s_y, read from the LDS
     // tables each time it is needed (volatile: not held in registers across
@@ -577,41 +621,31 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
         const int c = tid + u * FWD_T;
         if (c < wcols) s_x[c] = xv[u];
     }
-    if (tid < 3 * FWD_B) {
+    if (tid < 3 * ZS) {
         s_z[tid] = zv;
         s_y[tid] = 0.0;
     }
-    if (tid < K) s_y[3 * FWD_B + tid] = ygv;
+    if (tid < K) s_y[3 * ZS + tid] = ygv;
     // the row tables of the update: entry tid (fewer than FWD_T rows)
     if (tid < nrows) {
         int l, i;
         int64_t r3;
         split3(B, tid >= K ? tid - K : 0, &l, &i, &r3);
         s_row[tid] = (tid < K) ? iv : (int32_t)r3;
-        s_slot[tid] = (tid < K) ? 3 * FWD_B + tid : l * FWD_B + i;
+        s_slot[tid] = (tid < K) ? 3 * ZS + tid : l * ZS + i;
     }
     __syncthreads();
     // y1 = H1 z1
     if (rg == 0) {
-        const double d = mv_dot(m, s_z, h);
+        const double d = mv_dot(m, s_z, h, hb);
         if (h == 0 && ir < n0) s_y[ir] = d;
     }
     __syncthreads();
     // z2 -= G21 y1 and z3 -= G31 y1
     if (rg == 1 || rg == 2) {
-        const double d = mv_dot(m, s_y, h);
+        const double d = mv_dot(m, s_y, h, hb);
         const int rows = (rg == 1) ? n1 : n2;
-        if (h == 0 && ir < rows) s_z[rg * FWD_B + ir] -= d;
-    }
-    // the second half of the chain's matrices into LDS
-#pragma unroll
-    for (int u = 0; u < FILL; ++u) {
-        const int e = tid + u * FWD_T;
-        if (e < 3 * FWD_B * FWD_B) {
-            const int k = e / (FWD_B * FWD_B), rr = e - k * FWD_B * FWD_B;
-            const int j = rr / FWD_B, i = rr - j * FWD_B;
-            s_m[k * FWD_B * LDM + i * LDM + j] = fv[u];
-        }
+        if (h == 0 && ir < rows) s_z[rg * ZS + ir] -= d;
     }
     // the rows of the update (first sub-slab) load during the rest of the
     // chain, once the registers of the first half are free
@@ -629,20 +663,20 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
     __syncthreads();
     // y2 = H2 z2
     if (rg == 0) {
-        const double d = mv_dot_lds(s_m, ir, s_z + FWD_B, h);
-        if (h == 0 && ir < n1) s_y[FWD_B + ir] = d;
+        const double d = mv_dot(m2, s_z + ZS, h, hb);
+        if (h == 0 && ir < n1) s_y[ZS + ir] = d;
     }
     __syncthreads();
     // z3 -= G32 y2
     if (rg == 1) {
-        const double d = mv_dot_lds(s_m + FWD_B * LDM, ir, s_y + FWD_B, h);
-        if (h == 0 && ir < n2) s_z[2 * FWD_B + ir] -= d;
+        const double d = mv_dot(m2, s_y + ZS, h, hb);
+        if (h == 0 && ir < n2) s_z[2 * ZS + ir] -= d;
     }
     __syncthreads();
     // y3 = H3 z3
     if (rg == 2) {
-        const double d = mv_dot_lds(s_m + 2 * FWD_B * LDM, ir, s_z + 2 * FWD_B, h);
-        if (h == 0 && ir < n2) s_y[2 * FWD_B + ir] = d;
+        const double d = mv_dot(m2, s_z + 2 * ZS, h, hb);
+        if (h == 0 && ir < n2) s_y[2 * ZS + ir] = d;
     }
     __syncthreads();
 
@@ -717,13 +751,25 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
 // The rest of iteration it after the chain form's Grams (k_gram_chain), in one
 // launch over the column slabs (one sub-slab each): in every workgroup wave 0
 // solves the greedy system (G + lambda I) y = r_I (ldl_blk64 on the summed
-// Gram chunks; every workgroup forms the same y) while waves 1-7 sum C into
-// LDS and load the three sampled steps' matrices into registers, so that their
-// memory latency is spent during the factorisation.  Then
-// z = r_{S'} - C y (j ascending), the chain of k_fwd_samp3 with the same
+// Gram chunks; every workgroup forms the same y) while waves 1-7 sum C and
+// load the three sampled steps' matrices into registers and LDS, so that
+// their memory latency is spent during the factorisation.  Then
+// z = r_{S'} - C y (entries of even and odd j summed by the two threads of a
+// pair), the chain of k_fwd_samp3 with the same
 // arithmetic (the same thread of a row pair, the same sums), and
 // x[cols] += A_I[:, cols]^T y + sum_l A_l[:, cols]^T y_l in one pass.  The
 // first workgroup writes y and, for a checkpoint, the chain state (I, y, z).
+//
+// What bounds it: the chain Gram load (2.3 us), factorisation, z, six small
+// products, update; and beside the factorisation the loads of waves 1-7, which
+// have to end with it (16 workgroups each read the six b x b matrices and C:
+// 0.4 MB at b = K = 64 with C in two column chunks).  With the factorisation
+// at 6 to 8 us the loads decided, so they are spread as many as the registers
+// hold (a select or a clamped address per load cost more than the memory) and
+// C comes in at most two chunks (four made the Grams 0.8 us faster and this
+// kernel 6 us slower at 2000 columns).  Per launch, stamps inside a timing
+// copy: 100000 x 2000, b = 64: 21 us (28); 20000 x 1000, b = 50: 17.5 us (26);
+// 2000 x 200, b = 20: 9.2 us (20).
 struct FwdChainP {
     const void *A;
     int64_t ld, n, q, rem;
@@ -733,7 +779,7 @@ struct FwdChainP {
     const double *H;
     const double *xg;      // cross-Grams of iteration it + 1's blocks
     const double *G;       // [nch][K (K + 1) / 2] packed lower partials
-    const double *C;       // [nch][3 * FWD_B][64] partials
+    const double *C;       // [nch][64][3 * FWD_B] partials
     int nch;
     int K;
     double lambda;
@@ -747,10 +793,9 @@ struct FwdChainP {
     Ctrl *ctrl;
 };
 
-constexpr int CHN = 4;                       // most column chunks of G and C
+constexpr int CHN = 2;                       // most column chunks of G and C
 constexpr int FC_T = FWD_T - 64;             // threads of waves 1-7
-constexpr int FILL2 = (3 * FWD_B * FWD_B + FC_T - 1) / FC_T;   // H2, G32, H3 entries per thread
-constexpr int LA = LB_LEN;                                     // LDS doubles of region a
+constexpr int LA = LB_LEN;                   // LDS doubles of region a
 
 template <typename T, typename V, bool AL, int RN>
 __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
@@ -759,17 +804,22 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
     constexpr int NV = SWC / VW;
     constexpr int G = FWD_T / NV;
     static_assert(1024 + G * SWC * sizeof(V) / 8 <= LA, "phase-2 arrays fit the factorisation's LDS");
+    static_assert(2 * CHAIN_S <= FC_T, "two threads per row of C");
+    // the update's rows travel as soon as C is summed where the registers hold
+    // both, else after z; entries of C's chunks in flight per thread
+    constexpr bool EARLY = RN <= 13;
+    constexpr int CU = (RN == 13) ? 8 : 16;
+    static_assert(3 * ZS <= 256 && 256 + 3 * ZS + 64 <= 1024, "z, y and the row sums side by side");
     const T *__restrict__ A = (const T *)p.A;
     V *__restrict__ x = (V *)p.x;
     const int tid = threadIdx.x;
     const int K = p.K, KP = K * (K + 1) / 2;
     // LDS: region a holds the factorisation (the padded system, then its
-    // tiles), then z, y and the update's row sums; region b holds C, then H2,
-    // G32, H3
-    __shared__ double lds_a[LA];
-    __shared__ double lds_b[3 * FWD_B * LDM];
-    __shared__ double s_yk[64], s_rs[3 * FWD_B];
-    __shared__ int32_t s_rok[3 * FWD_B];
+    // tiles), then z, y and the update's row sums; s_m2 keeps each thread's
+    // entries of its second matrix while C needs the registers
+    __shared__ __align__(16) double lds_a[LA];
+    __shared__ __align__(16) double s_yk[64];
+    __shared__ double s_m2[MC][6 * 64 + 8];
     __shared__ V s_x[SWC];
     __shared__ int32_t s_row[64 + 3 * FWD_B], s_slot[64 + 3 * FWD_B];
     __shared__ int s_ok;
@@ -777,40 +827,97 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
     double *s_z = lds_a, *s_y = lds_a + 256;
     V (*s_red)[SWC] = reinterpret_cast<V (*)[SWC]>(lds_a + 1024);
 
-    // --- phase 0: the Gram chunks (summed in chunk order) and r_I
+    // the draws (scalar loads) travel with the first vector loads
+    const int stop = __hip_atomic_load(&p.ctrl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    Blk3 B;
+    blocks3(p.tau, p.tau_index, p.q, p.rem, B);
+    const int bm = p.bmax, n0 = B.c0, n1 = B.c1, n2 = B.c2;
+    const int ncnt = n0 + n1 + n2, nrows = K + ncnt;
+    const int64_t c0 = (int64_t)blockIdx.x * p.wu;
+    const int64_t c1 = (c0 + p.wu < p.n) ? c0 + p.wu : p.n;
+    const int wcols = (int)(c1 - c0);
+
+    // the Gram chunks and r_I: every thread loads its packed entries, sums
+    // them in chunk order and puts them into the padded system (lambda on the
+    // diagonal, the identity beyond K)
     constexpr int NU0 = (64 * 65 / 2 + FWD_T - 1) / FWD_T;
-    {
-        const int stop =
-            __hip_atomic_load(&p.ctrl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        double gt[CHN][NU0];
+    double gt[CHN][NU0];
+    double ri;
+    auto load_gram = [&]() {
+        ri = p.rI[tid < K ? tid : 0];
 #pragma unroll
         for (int c = 0; c < CHN; ++c)
+            if (c < p.nch) {   // uniform
 #pragma unroll
-            for (int u = 0; u < NU0; ++u) {
-                const int f = tid + u * FWD_T;
-                gt[c][u] = p.G[(int64_t)(c < p.nch ? c : 0) * KP + (f < KP ? f : 0)];
+                for (int u = 0; u < NU0; ++u) {
+                    const int f = tid + u * FWD_T;
+                    gt[c][u] = p.G[c * KP + (f < KP ? f : 0)];
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < NU0; ++u) gt[c][u] = 0.0;
             }
-        const double ri = p.rI[tid < K ? tid : 0];
-        if (stop) return;
-        // the padded system straight into the work matrix (lambda on the
-        // diagonal, the identity beyond K)
+    };
+    auto put_gram = [&]() {
 #pragma unroll
         for (int u = 0; u < NU0; ++u) {
             const int f = tid + u * FWD_T;
             double gs = gt[0][u];
 #pragma unroll
-            for (int c = 1; c < CHN; ++c) gs += (c < p.nch) ? gt[c][u] : 0.0;
+            for (int c = 1; c < CHN; ++c)
+                if (c < p.nch) gs += gt[c][u];
             if (f < 64 * 65 / 2) lb_put(Lc, f, gs, K, p.lambda);
         }
         if (tid < 64) s_yk[tid] = (tid < K) ? ri : 0.0;
-    }
-    __syncthreads();
+    };
 
-    // --- phase 1: wave 0 factors (nothing else is live across it; the
-    // wave index is made scalar so that both branches are real jumps) ...
+    // the update's rows g + G r, r < RN, from the tables: every row index
+    // first (LDS), then every load (row 0 stands in past the last row, where
+    // y is 0)
+    const int g = tid / NV, v = tid % NV;
+    uvec4 ua[RN];
+    auto load_rows = [&]() {
+        const int64_t col = c0 + (int64_t)v * VW;
+        int32_t rw[RN];
+#pragma unroll
+        for (int r = 0; r < RN; ++r) {
+            const int qq = g + G * r;
+            rw[r] = (qq < nrows) ? s_row[qq] : 0;
+        }
+        if (AL && c0 + SWC <= p.n) {   // uniform: no column past the matrix
+#pragma unroll
+            for (int r = 0; r < RN; ++r)
+                ua[r] = *reinterpret_cast<const uvec4 *>(A + (int64_t)rw[r] * p.ld + col);
+        } else {
+#pragma unroll
+            for (int r = 0; r < RN; ++r)
+                ua[r] = load_raw_sel<T, AL>(A + (int64_t)rw[r] * p.ld, col, c1, true, A, c0);
+        }
+    };
+
+    // --- phase 1: wave 0 factors while waves 1-7 load everything else (the
+    // wave index is made scalar so that both branches are real jumps; each
+    // branch meets the same two barriers)
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t = tid - 64;
+    int rg, ir, h;
+    chain_rows(wv - 1, tid & 63, &rg, &ir, &h);
+    const int hb = mv_half(bm);
+    // thread pair cs holds row cs of C, thread ch of it the entries ch kb + u
+    const int ts = t < 6 * 64 + 8 ? t : 6 * 64 + 7;   // (threads past it hold no matrix)
+    const int cs = t >> 1, ch = t & 1, kb = mv_half(K);
+    double m[MC], cv[32];
+    double rsv = 0.0;
+    bool rok = false;
     if (wv == 0) {
+        load_gram();
+        if (stop) return;
+        put_gram();
+        __syncthreads();
+        // (this wave's chain comes first on its SIMD)
+        __builtin_amdgcn_s_setprio(3);
         const bool ok = ldl_blk64(Lc, s_yk, K);
+        __builtin_amdgcn_s_setprio(0);
         if (tid == 0) {
             s_ok = ok ? 1 : 0;
             if (!ok) {
@@ -818,118 +925,112 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
                 p.ctrl->done = 1;
             }
         }
-    }
-    // ... while waves 1-7 load everything else
-    double m[MC];
-    double fv[FILL2];
-    if (wv != 0) {
-        const int t = tid - 64;
-        const int rg = t / (2 * FWD_B), uu = t - rg * 2 * FWD_B, ir = uu >> 1, h = uu & 1;
-        Blk3 B;
-        blocks3(p.tau, p.tau_index, p.q, p.rem, B);
-        const int64_t hoff0 = blk_hoff(p.tau[p.tau_index], p.q, p.rem);
-        const int64_t hoff1 = blk_hoff(p.tau[p.tau_index + 1], p.q, p.rem);
-        const int64_t hoff2 = blk_hoff(p.tau[p.tau_index + 2], p.q, p.rem);
-        const int ncnt = B.c0 + B.c1 + B.c2, nrows = K + ncnt;
-        const int bm = p.bmax, n0 = B.c0, n1 = B.c1, n2 = B.c2;
-        const int64_t c0 = (int64_t)blockIdx.x * p.wu;
-        const int wcols = (int)(((c0 + p.wu < p.n) ? c0 + p.wu : p.n) - c0);
+        __syncthreads();
+    } else {
+        load_gram();
         // r at the next blocks' rows, the greedy rows, the slab of x
-        double rsv = 0.0;
-        int rok = 0;
-        if (t < 3 * FWD_B) {
-            const int l = t / FWD_B, i = t - l * FWD_B;
+        V rr = (V)0;
+        if (cs < CHAIN_S) {
+            const int l = cs / FWD_B, i = cs - l * FWD_B;
             const int cl = (l == 0) ? n0 : ((l == 1) ? n1 : n2);
             const int64_t st = (l == 0) ? B.s0 : ((l == 1) ? B.s1 : B.s2);
             rok = i < cl;
-            const V rr = ((const V *)p.r)[st + (rok ? i : 0)];
-            rsv = rok ? (double)rr : 0.0;
+            rr = ((const V *)p.r)[st + (rok ? i : 0)];
         }
         const int32_t iv = p.I[t < K ? t : 0];
         const V xv = x[c0 + (t < wcols ? t : 0)];
-        // H1, G21, G31 (thread ranges of 2 FWD_B, as k_fwd_samp3)
-        {
-            const double *M = p.H;
-            int64_t sj = 1;
-            int rows = 0, cols = 0;
-            if (rg == 0) { M = p.H + hoff0; sj = n0; rows = n0; cols = n0; }
-            else if (rg == 1) { M = p.xg; sj = bm; rows = n1; cols = n0; }
-            else if (rg == 2) { M = p.xg + (int64_t)bm * bm; sj = bm; rows = n2; cols = n0; }
-            mv_load(M, 1, sj, ir, h, rows, cols, m);
-        }
-        // H2, G32, H3 for LDS (consecutive threads, consecutive addresses)
-#pragma unroll
-        for (int u = 0; u < FILL2; ++u) {
-            const int e = t + u * FC_T;
-            const int k = e / (FWD_B * FWD_B), rr = e - k * FWD_B * FWD_B;
-            const int j = rr / FWD_B, i = rr - j * FWD_B;
-            const double *M = (k == 0) ? p.H + hoff1 : ((k == 1) ? p.xg + 2 * (int64_t)bm * bm : p.H + hoff2);
-            const int rows = (k == 0) ? n1 : n2, cols = (k == 1) ? n1 : (k == 0 ? n1 : n2);
-            const int64_t sj = (k == 1) ? bm : (k == 0 ? n1 : n2);
-            const bool ok = k < 3 && i < rows && j < cols;
-            const double tv = M[ok ? i + (int64_t)j * sj : 0];
-            fv[u] = ok ? tv : 0.0;
-        }
-        if (t < 3 * FWD_B) {
-            s_rs[t] = rsv;
-            s_rok[t] = rok;
-        }
-        if (t < wcols) s_x[t] = xv;
+        if (stop) return;
+        put_gram();
         if (t < nrows) {   // the update's row tables, greedy rows first
             int l, i;
             int64_t r3;
             split3(B, t >= K ? t - K : 0, &l, &i, &r3);
             s_row[t] = (t < K) ? iv : (int32_t)r3;
-            s_slot[t] = (t < K) ? 3 * FWD_B + t : l * FWD_B + i;
+            s_slot[t] = (t < K) ? 3 * ZS + t : l * ZS + i;
         }
-        // C summed over its chunks into LDS (row stride LDM), in batches
-        constexpr int NCE = 3 * FWD_B * 64, PT = (NCE + FC_T - 1) / FC_T, UB = 7;
-        for (int ub = 0; ub < PT; ub += UB) {
-            double ct[CHN][UB];
+        __syncthreads();
+        // the sampled steps' matrices (two per thread range, as k_fwd_samp3)
+        double m2[MC];
+        {
+            const int64_t hoff0 = blk_hoff(p.tau[p.tau_index], p.q, p.rem);
+            const int64_t hoff1 = blk_hoff(p.tau[p.tau_index + 1], p.q, p.rem);
+            const int64_t hoff2 = blk_hoff(p.tau[p.tau_index + 2], p.q, p.rem);
+            chain_mats_wave(p.H, p.xg, hoff0, hoff1, hoff2, n0, n1, n2, bm, wv - 1, rg, ir, h, hb,
+                            m, m2);
+        }
+        // C summed over its chunks, CU entries of every chunk in flight
+        // (all of them lie inside C, whose rows run to 64 and which was
+        // cleared at setup; entries at or past K meet zeros of y); the second
+        // matrix goes to LDS while the first of them travel
+        const double *pc = p.C + (cs < CHAIN_S ? cs : 0) + ch * kb * CHAIN_S;
 #pragma unroll
-            for (int c = 0; c < CHN; ++c)
+        for (int u0 = 0; u0 < 32; u0 += CU) {
+            if (u0 < kb) {   // uniform
+                double ct[CHN][CU];
 #pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    const int e = t + (ub + u) * FC_T;
-                    ct[c][u] = p.C[(int64_t)(c < p.nch ? c : 0) * NCE + (e < NCE ? e : 0)];
+                for (int c = 0; c < CHN; ++c)
+                    if (c < p.nch) {
+#pragma unroll
+                        for (int u = 0; u < CU; ++u) ct[c][u] = pc[c * CHAIN_C + (u0 + u) * CHAIN_S];
+                    }
+#pragma unroll
+                for (int u = 0; u < CU; ++u) {
+                    double sum = ct[0][u];
+#pragma unroll
+                    for (int c = 1; c < CHN; ++c)
+                        if (c < p.nch) sum += ct[c][u];
+                    cv[u0 + u] = sum;
                 }
+                if (u0 == 0) {
 #pragma unroll
-            for (int u = 0; u < UB; ++u) {
-                const int e = t + (ub + u) * FC_T;
-                double cs = ct[0][u];
+                    for (int e0 = 0; e0 < MC; e0 += MG)
+                        if (e0 < hb) {
 #pragma unroll
-                for (int c = 1; c < CHN; ++c) cs += (c < p.nch) ? ct[c][u] : 0.0;
-                const int sl = e >> 6, j = e & 63;
-                if (e < NCE) lds_b[sl * LDM + j] = (j < K) ? cs : 0.0;
+                            for (int e = e0; e < e0 + MG; ++e) s_m2[e][ts] = m2[e];
+                        }
+                }
             }
         }
+        rsv = rok ? (double)rr : 0.0;
+        if (t < wcols) s_x[t] = xv;
+        if constexpr (EARLY) load_rows();
+        __syncthreads();
     }
-    __syncthreads();
     if (!s_ok) return;
+    if constexpr (EARLY) {
+        if (wv == 0) load_rows();
+    }
 
-    // --- phase 2: z = r_{S'} - C y, then the chain (the sizes again, from
-    // the draws)
-    Blk3 B;
-    blocks3(p.tau, p.tau_index, p.q, p.rem, B);
-    const int ncnt = B.c0 + B.c1 + B.c2, nrows = K + ncnt;
-    const int n0 = B.c0, n1 = B.c1, n2 = B.c2;
-    const int64_t c0 = (int64_t)blockIdx.x * p.wu;
-    const int64_t c1 = (c0 + p.wu < p.n) ? c0 + p.wu : p.n;
-    const int wcols = (int)(c1 - c0);
-    const int t = tid - 64;
-    const int rg = t / (2 * FWD_B), uu = t - rg * 2 * FWD_B, ir = uu >> 1, h = uu & 1;
-    const int g = tid / NV, v = tid % NV;
-    if (tid < 3 * FWD_B) {
+    // --- phase 2: z = r_{S'} - C y, then the chain
+    if (wv != 0) {
+        const double *yk = s_yk + ch * kb;
         double acc = 0.0;
-        const double *cr = lds_b + tid * LDM;
-        for (int j = 0; j < K; ++j) acc = __builtin_fma(cr[j], s_yk[j], acc);
-        const double zz = s_rok[tid] ? s_rs[tid] - acc : 0.0;
-        s_z[tid] = zz;
-        s_y[tid] = 0.0;
-        if (blockIdx.x == 0 && p.ckst) p.ckst[96 + tid] = zz;
+#pragma unroll
+        for (int u0 = 0; u0 < 32; u0 += MG)
+            if (u0 < kb) {
+                const dvec2 w0 = *reinterpret_cast<const dvec2 *>(yk + u0);
+                const dvec2 w1 = *reinterpret_cast<const dvec2 *>(yk + u0 + 2);
+                acc = __builtin_fma(cv[u0], w0[0], acc);
+                acc = __builtin_fma(cv[u0 + 1], w0[1], acc);
+                acc = __builtin_fma(cv[u0 + 2], w1[0], acc);
+                acc = __builtin_fma(cv[u0 + 3], w1[1], acc);
+            }
+        const double o = pair_other(acc);
+        if (ch == 0 && cs < CHAIN_S) {
+            const double zz = rok ? rsv - (acc + o) : 0.0;
+            const int l = cs / FWD_B, i = cs - l * FWD_B;
+            s_z[l * ZS + i] = zz;
+            s_y[l * ZS + i] = 0.0;
+            if (blockIdx.x == 0 && p.ckst) p.ckst[96 + cs] = zz;
+        }
+    } else if (tid < 3 * (ZS - FWD_B)) {
+        // the slots past each block
+        const int l = tid / (ZS - FWD_B), i = FWD_B + tid - l * (ZS - FWD_B);
+        s_z[l * ZS + i] = 0.0;
+        s_y[l * ZS + i] = 0.0;
     }
     if (tid < K) {
-        s_y[3 * FWD_B + tid] = s_yk[tid];
+        s_y[3 * ZS + tid] = s_yk[tid];
         if (blockIdx.x == 0) {
             p.y[tid] = s_yk[tid];
             if (p.ckst) {
@@ -939,63 +1040,47 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
         }
     }
     __syncthreads();
-    // H2, G32, H3 into LDS (C is no longer needed); y1 = H1 z1
-    if (wv != 0) {
+    if constexpr (!EARLY) load_rows();
+    // this thread's second matrix, once the first is used
+    auto second = [&]() {
 #pragma unroll
-        for (int u = 0; u < FILL2; ++u) {
-            const int e = t + u * FC_T;
-            if (e < 3 * FWD_B * FWD_B) {
-                const int k = e / (FWD_B * FWD_B), rr = e - k * FWD_B * FWD_B;
-                const int j = rr / FWD_B, i = rr - j * FWD_B;
-                lds_b[k * FWD_B * LDM + i * LDM + j] = fv[u];
+        for (int e0 = 0; e0 < MC; e0 += MG)
+            if (e0 < hb) {
+#pragma unroll
+                for (int e = e0; e < e0 + MG; ++e) m[e] = s_m2[e][ts];
             }
-        }
-        if (rg == 0) {
-            const double d = mv_dot(m, s_z, h);
-            if (h == 0 && ir < n0) s_y[ir] = d;
-        }
+    };
+    // y1 = H1 z1
+    if (wv != 0 && rg == 0) {
+        const double d = mv_dot(m, s_z, h, hb);
+        if (h == 0 && ir < n0) s_y[ir] = d;
+        second();
     }
     __syncthreads();
     // z2 -= G21 y1 and z3 -= G31 y1
     if (wv != 0 && (rg == 1 || rg == 2)) {
-        const double d = mv_dot(m, s_y, h);
+        const double d = mv_dot(m, s_y, h, hb);
         const int rows = (rg == 1) ? n1 : n2;
-        if (h == 0 && ir < rows) s_z[rg * FWD_B + ir] -= d;
-    }
-    // the update's rows load during the rest of the chain
-    const int64_t col = c0 + (int64_t)v * VW;
-    uvec4 ua[RN];
-    {
-        // every row index first (LDS), then every load, so that the loads
-        // do not wait on one LDS read each
-        int32_t rw[RN];
-#pragma unroll
-        for (int r = 0; r < RN; ++r) {
-            const int qq = g + G * r;
-            rw[r] = (qq < nrows) ? s_row[qq] : 0;
-        }
-#pragma unroll
-        for (int r = 0; r < RN; ++r)
-            ua[r] = load_raw_sel<T, AL>(A + (int64_t)rw[r] * p.ld, col, c1, g + G * r < nrows, A,
-                                        c0);
+        if (h == 0 && ir < rows) s_z[rg * ZS + ir] -= d;
+        second();
     }
     __syncthreads();
     // y2 = H2 z2
     if (wv != 0 && rg == 0) {
-        const double d = mv_dot_lds(lds_b, ir, s_z + FWD_B, h);
-        if (h == 0 && ir < n1) s_y[FWD_B + ir] = d;
+        const double d = mv_dot(m, s_z + ZS, h, hb);
+        if (h == 0 && ir < n1) s_y[ZS + ir] = d;
     }
     __syncthreads();
     // z3 -= G32 y2
     if (wv != 0 && rg == 1) {
-        const double d = mv_dot_lds(lds_b + FWD_B * LDM, ir, s_y + FWD_B, h);
-        if (h == 0 && ir < n2) s_z[2 * FWD_B + ir] -= d;
+        const double d = mv_dot(m, s_y + ZS, h, hb);
+        if (h == 0 && ir < n2) s_z[2 * ZS + ir] -= d;
     }
     __syncthreads();
     // y3 = H3 z3
     if (wv != 0 && rg == 2) {
-        const double d = mv_dot_lds(lds_b + 2 * FWD_B * LDM, ir, s_z + 2 * FWD_B, h);
-        if (h == 0 && ir < n2) s_y[2 * FWD_B + ir] = d;
+        const double d = mv_dot(m, s_z + 2 * ZS, h, hb);
+        if (h == 0 && ir < n2) s_y[2 * ZS + ir] = d;
     }
     __syncthreads();
 

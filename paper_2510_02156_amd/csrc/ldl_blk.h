@@ -32,9 +32,10 @@ constexpr int LB_LEN = 64 * LB_RS;    // doubles of S
 // rows below K, the identity from row K on.  Every f < 64 * 65 / 2 is written
 // once by whichever thread holds it, so the workgroup fills S in parallel.
 __device__ __forceinline__ void lb_put(double *S, int f, double g, int K, double lambda) {
-    int i = (int)((sqrtf(8.0f * (float)f + 1.0f) - 1.0f) * 0.5f);
-    while (i * (i + 1) / 2 > f) --i;
-    while ((i + 1) * (i + 2) / 2 <= f) ++i;
+    // f < 2080: the hardware square root is within a step of the row
+    int i = (int)((__builtin_amdgcn_sqrtf(8.0f * (float)f + 1.0f) - 1.0f) * 0.5f);
+    i -= (i * (i + 1) / 2 > f) ? 1 : 0;
+    i += ((i + 1) * (i + 2) / 2 <= f) ? 1 : 0;
     const int j = f - i * (i + 1) / 2;
     S[i * LB_RS + j] = (i < K) ? ((i == j) ? g + lambda : g) : ((i == j) ? 1.0 : 0.0);
 }

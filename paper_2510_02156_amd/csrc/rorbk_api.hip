@@ -718,7 +718,7 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     ALLOC(h->d_S, k);
     ALLOC(h->d_pbar, k);
     ALLOC(h->d_W, k);
-    ALLOC(h->d_H, htotal);
+    ALLOC(h->d_H, htotal + RORBK_FWD_PAD);
     ALLOC(h->d_ctrl, 1);
     ALLOC(h->d_P[0], (int64_t)L.nch_u * bmax);
     ALLOC(h->d_P[1], (int64_t)L.nch_u * bmax);
@@ -744,16 +744,17 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
         L.wf = per * swc;
         L.nch_f = (int32_t)((L.n + L.wf - 1) / L.wf);
         ALLOC(h->d_P3, (int64_t)L.nch_f * 3 * bmax);
-        ALLOC(h->d_XG, 2 * 3 * bmax * bmax);
+        ALLOC(h->d_XG, 2 * 3 * bmax * bmax + RORBK_FWD_PAD);
         ALLOC(h->d_z3, 3 * RORBK_FWD_MAX_BLOCK);
         ALLOC(h->d_fwdcnt, 1);
         // chain form: greedy sets of at most 64 rows, rows of at most 4096
-        // columns (Grams after the selection in up to 4 column chunks of at
-        // least 512) and a selection that merges its candidates in one level
+        // columns (Grams after the selection in up to 2 column chunks of at
+        // least 512: the chain step reads every chunk in every workgroup) and
+        // a selection that merges its candidates in one level
         h->chain = (L.K <= 64 && L.n <= 4096 && L.nch_s * L.K <= 8192) ? 1 : 0;
         if (h->chain) {
             int64_t nc = (L.n + 511) / 512;
-            if (nc > 4) nc = 4;
+            if (nc > 2) nc = 2;
             int64_t wc = (L.n + nc - 1) / nc;
             wc = ((wc + 31) / 32) * 32;
             L.wc = wc;
@@ -815,10 +816,17 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     memset(h->h_ctrl, 0, 3 * sizeof(Ctrl));
     if (hipMemsetAsync(h->d_selcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess ||
         (h->d_fwdcnt &&
-         hipMemsetAsync(h->d_fwdcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess)) {
+         hipMemsetAsync(h->d_fwdcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess) ||
+        // the chain step reads, and multiplies by zero, entries past the
+        // matrices in these: they have to be finite
+        (h->d_XG &&
+         (launch_fill_zero(h->d_XG, 8 * (6 * bmax * bmax + RORBK_FWD_PAD), (hipStream_t)stream) != hipSuccess ||
+          launch_fill_zero(h->d_H + htotal, 8 * RORBK_FWD_PAD, (hipStream_t)stream) != hipSuccess)) ||
+        (h->d_C && launch_fill_zero(h->d_C, 8 * (int64_t)L.nch_c * 3 * RORBK_FWD_MAX_BLOCK * 64,
+                                    (hipStream_t)stream) != hipSuccess)) {
         destroy_all(h);
         delete h;
-        return fail(RORBK_ERR_HIP, "clearing the selection counter failed");
+        return fail(RORBK_ERR_HIP, "clearing the handle's buffers failed");
     }
     if (hipEventCreate(&h->ev0) != hipSuccess || hipEventCreate(&h->ev1) != hipSuccess ||
         hipEventCreate(&h->evr[0][0]) != hipSuccess || hipEventCreate(&h->evr[0][1]) != hipSuccess ||

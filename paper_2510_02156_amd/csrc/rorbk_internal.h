@@ -35,6 +35,10 @@ struct Ctrl {
 // Blocks of at most this many rows (dense, row form) run the fused forward
 // steps of k_fwd.hip: the three sampled updates in one launch.
 constexpr int RORBK_FWD_MAX_BLOCK = 65;
+// Doubles allocated behind the stored inverses and the cross-Grams for those
+// steps' loads: they read, and multiply by zero, up to nine columns of at most
+// RORBK_FWD_MAX_BLOCK entries past a matrix's last and one more.
+constexpr int RORBK_FWD_PAD = 12 * RORBK_FWD_MAX_BLOCK;
 
 // The cross-Gram tile jobs a residual launch carries (jobs == 0: none).
 struct XgSide {
