@@ -1,7 +1,7 @@
 // k_common.hip -- format-independent ROR-BK kernels: partition, sampler,
 // norms, residual-driven selection (per-block norms, stop test, top-K) and the
 // greedy block's Cholesky solve.
-#include "ldl_blk.h"
+#include "ldl_wg.h"
 #include "rorbk_device.h"
 #include "xgram.h"
 
@@ -804,8 +804,10 @@ hipError_t launch_select(const rorbk_handle_s *h, const SelectArgs &a, hipStream
 // ------------------------------------------------------ greedy block solve --
 // (A_I A_I^T + lambda I) y = rhs, the greedy step of Algorithm 1, rhs = r_I
 // (forward) or, for the adjoint, -(sum of the partial products A_I g).  Greedy
-// sets of at most 64 rows are solved by k_chol_wave below; larger ones by the
-// blocked Cholesky on 32 x 32 tiles (one launch per tile column, k_big.hip).
+// sets of at most 64 rows are solved by k_chol_wave below (one wave: its few
+// tiles cost less than the barriers of a workgroup), of 65 to 161 rows by
+// k_chol_wg (the tiles fill one workgroup's LDS), larger ones by the blocked
+// Cholesky on 32 x 32 tiles (one launch per tile column, k_big.hip).
 // A pivot that is not positive (or not finite) sets RORBK_ERR_NOT_SPD.
 
 // Packed Gram partials summed in chunk order into LDS, KP <= NU * 256: thread
@@ -895,14 +897,140 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int q = threadIdx.x; q < K; q += 64) y[q] = z[q];
 }
 
+// 65 to 161 rows: the solve in one workgroup's LDS (ldl_wg.h), the Gram chunks
+// summed in order and put straight into the tiles.  K = 128 with one chunk:
+// 17 us, where the blocked factorisation in global memory (an unpacking
+// launch, one per 32 columns and a backward solve) took 59.
+constexpr int CW_NW = 16;
+template <int P>
+__global__ __launch_bounds__(64 * CW_NW) void k_chol_wg(
+    const double *__restrict__ Gpart, int nch, int K, double lambda,
+    const double *__restrict__ rI, const double *__restrict__ Pin, int nchP, int bmax,
+    double *__restrict__ y, Ctrl *__restrict__ ctrl) {
+    constexpr int NTH = 64 * CW_NW, U = (16 * P * (16 * P + 1) / 2 + NTH - 1) / NTH;
+    __shared__ __align__(16) double T[wl_tiles(P) * WT];
+    __shared__ double rd[16 * P], z[16 * P];
+    const int stop = __hip_atomic_load(&ctrl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int KP = K * (K + 1) / 2;
+    double g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[u] = 0.0;
+    for (int c = 0; c < nch; ++c) {
+        const double *gc = Gpart + (int64_t)c * KP;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = threadIdx.x + u * NTH;
+            g[u] += gc[f < KP ? f : KP - 1];
+        }
+    }
+    if (threadIdx.x < 16 * P) {
+        const int q = threadIdx.x;
+        double v = 0.0;
+        if (q < K) {
+            if (rI) {
+                v = rI[q];
+            } else {
+                for (int c = 0; c < nchP; ++c) v += Pin[(int64_t)c * bmax + q];
+                v = -v;
+            }
+        }
+        z[q] = v;
+    }
+    if (stop) return;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int f = threadIdx.x + u * NTH;
+        if (f < KP) wl_put(T, P, f, g[u], lambda);
+    }
+    wl_pad(T, P, K);
+    if (!wl_factor<P, CW_NW, true>(T, rd, z)) {
+        if (threadIdx.x == 0) {
+            ctrl->status = RORBK_ERR_NOT_SPD;
+            ctrl->done = 1;
+        }
+        return;
+    }
+    wl_back<P, CW_NW>(T, rd, z);
+    if (threadIdx.x < K) y[threadIdx.x] = z[threadIdx.x];
+}
+
+// Stored inverses (A_t A_t^T + lambda I)^{-1} of fixed blocks of at most 161
+// rows from their packed Grams, a workgroup per block, all of it in LDS: bound
+// by the factorisation's chain of tile eliminations, which the blocks sharing
+// a CU overlap.  781 blocks of 64 rows: 532 us on the kernel that eliminated
+// column by column and formed L^{-1} with four threads a column; 781 of 128
+// rows: 7.2 ms with the inverse formed through global memory.
+template <int P>
+constexpr int bi_waves() { return P < 4 ? 4 : P; }
+template <int P>
+__global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
+    const double *__restrict__ Gs, int64_t kpmax, int64_t q, int64_t rem, double lambda,
+    double *__restrict__ H, int32_t *__restrict__ fail) {
+    constexpr int NW = bi_waves<P>(), NTH = 64 * NW;
+    __shared__ __align__(16) double T[wl_tiles(P) * WT];
+    __shared__ double rd[16 * P];
+    const int64_t t = blockIdx.x;
+    const int K = blk_rows(t, q, rem);
+    const int KP = K * (K + 1) / 2;
+    const double *g = Gs + t * kpmax;
+    constexpr int U = 4;
+    for (int f0 = threadIdx.x; f0 < KP; f0 += U * NTH) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = g[f0 + u * NTH < KP ? f0 + u * NTH : KP - 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (f0 + u * NTH < KP) wl_put(T, P, f0 + u * NTH, v[u], lambda);
+    }
+    wl_pad(T, P, K);
+    if (!wl_factor<P, NW, false>(T, rd, nullptr)) {
+        if (threadIdx.x == 0) *fail = 1;
+        return;
+    }
+    wl_inverse<P, NW>(T, rd, K, H + blk_hoff(t, q, rem));
+}
+
+template <int P>
+static void block_inverse_p(const rorbk_handle_s *h, const double *Gs, int64_t kp, int32_t *d_fail,
+                            hipStream_t s) {
+    const Layout &L = h->L;
+    if ((L.bmax + 15) / 16 == P)
+        hipLaunchKernelGGL(k_block_inverse<P>, dim3((unsigned)L.k), dim3(64 * bi_waves<P>()), 0, s,
+                           Gs, kp, L.q, L.rem, h->lambda, h->d_H, d_fail);
+    else if constexpr (P < WL_MAXP)
+        block_inverse_p<P + 1>(h, Gs, kp, d_fail, s);
+}
+
+hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const double *Gs, int64_t kp,
+                                            int32_t *d_fail, hipStream_t s) {
+    if (h->L.bmax > MAXB) return launch_big_block_inverses(h, Gs, kp, d_fail, s);
+    block_inverse_p<1>(h, Gs, kp, d_fail, s);
+    return hipGetLastError();
+}
+
+template <int P>
+static void chol_wg_p(const rorbk_handle_s *h, const double *Gpart, int K, const double *rI,
+                      const double *Pin, double *y, hipStream_t s) {
+    const Layout &L = h->L;
+    if ((K + 15) / 16 == P)
+        hipLaunchKernelGGL(k_chol_wg<P>, dim3(1), dim3(64 * CW_NW), 0, s, Gpart, (int)L.nch_g, K,
+                           h->lambda, rI, Pin, (int)L.nch_u, (int)L.bmax, y, h->d_ctrl);
+    else if constexpr (P < WL_MAXP)
+        chol_wg_p<P + 1>(h, Gpart, K, rI, Pin, y, s);
+}
+
 hipError_t launch_chol_solve(const rorbk_handle_s *h, const double *Gpart, int K,
                              const double *rI, const double *Pin, double *y, hipStream_t s) {
     const Layout &L = h->L;
-    if (K > 64) {
+    if (K > MAXB) {
         // the handle holds the blocked factorisation's buffers for every
-        // greedy set of more than 64 rows
+        // greedy set that does not fit one workgroup
         if (!h->d_bigG) return hipErrorInvalidValue;
         return launch_big_chol_solve(h, Gpart, K, rI, Pin, y, s);
+    }
+    if (K > 64) {
+        chol_wg_p<5>(h, Gpart, K, rI, Pin, y, s);
+        return hipGetLastError();
     }
     hipLaunchKernelGGL(k_chol_wave, dim3(1), dim3(256), 0, s, Gpart, L.nch_g, K, h->lambda, rI,
                        Pin, L.nch_u, (int)L.bmax, y, h->d_ctrl);

@@ -725,116 +725,6 @@ __global__ __launch_bounds__(256) void k_block_gram64(const T *__restrict__ A, i
     gram64_store(acc, bi, bj, bt, Gs + t * kpmax);
 }
 
-// Stored inverse of each fixed block: (G_t + lambda I)^{-1} from the LDL^T
-// factor (LDS), column j by thread j (forward with unit L, scale by D^{-1},
-// backward with L^T), written row-major (the inverse is symmetric).
-template <int MT>
-__global__ __launch_bounds__(256) void k_block_inverse(const double *__restrict__ Gs, int64_t kpmax,
-                                                       int64_t q, int64_t rem, double lambda,
-                                                       double *__restrict__ H,
-                                                       int32_t *__restrict__ fail) {
-    __shared__ double Gp[PACKED_MAX];
-    __shared__ double z[MAXB];
-    __shared__ double colbuf[2 * MAXB];
-    __shared__ double invd[MAXB];
-    const int64_t t = blockIdx.x;
-    const int K = blk_rows(t, q, rem);
-    const int KP = K * (K + 1) / 2;
-    for (int f = threadIdx.x; f < KP; f += blockDim.x) Gp[f] = Gs[t * kpmax + f];
-    for (int i = threadIdx.x; i < K; i += blockDim.x) z[i] = 0.0;
-    __syncthreads();
-    for (int i = threadIdx.x; i < K; i += blockDim.x) Gp[pk(i, i)] += lambda;
-    __syncthreads();
-    if (!ldl_solve<MT>(Gp, z, K, colbuf)) {
-        if (threadIdx.x == 0) *fail = 1;
-        return;
-    }
-    for (int i = threadIdx.x; i < K; i += blockDim.x) invd[i] = 1.0 / Gp[pk(i, i)];
-    __syncthreads();
-    double *Hb = H + blk_hoff(t, q, rem);
-    for (int j = threadIdx.x; j < K; j += blockDim.x) {
-        double *h = Hb + (int64_t)j * K;
-        for (int i = 0; i < j; ++i) h[i] = 0.0;
-        for (int i = j; i < K; ++i) {          // unit lower: z_i = e_j - sum l_ip z_p
-            double s = (i == j) ? 1.0 : 0.0;
-            for (int p2 = j; p2 < i; ++p2) s -= Gp[pk(i, p2)] * invd[p2] * h[p2];
-            h[i] = s;
-        }
-        for (int i = j; i < K; ++i) h[i] *= invd[i];
-        for (int i = K - 1; i >= 0; --i) {     // L^T h = D^{-1} z
-            double s = h[i];
-            for (int p2 = i + 1; p2 < K; ++p2) s -= Gp[pk(p2, i)] * invd[i] * h[p2];
-            h[i] = s;
-        }
-    }
-}
-
-// Blocks of at most KM rows: the same LDL^T (ldl_solve on 4 x 4 tiles), then the inverse in
-// LDS: M = L^{-1} column by column (four threads per column j:
-// m_ij = [i == j] - sum_{p<i} l_ip m_pj, thread q of the four summing the
-// p = q mod 4 terms in order, the four partials added by a fixed butterfly;
-// all columns run the same i, so l_ip is a broadcast read), and
-// H = M^T D^{-1} M entry by entry (h_ij = sum_{p >= max(i,j)} (m_pi m_pj) / d_p,
-// the product taken in an order-free way so that H is exactly symmetric),
-// written row-major with consecutive threads on consecutive entries.
-template <int KM>
-__global__ __launch_bounds__(4 * KM) void k_block_inverse_lds(const double *__restrict__ Gs,
-                                                           int64_t kpmax, int64_t q, int64_t rem,
-                                                           double lambda, double *__restrict__ H,
-                                                           int32_t *__restrict__ fail) {
-    __shared__ double Gp[KM * (KM + 1) / 2];
-    __shared__ double z[KM];
-    __shared__ double colbuf[2 * MAXB];
-    __shared__ double invd[KM];
-    __shared__ double M[KM][KM + 1];
-    const int64_t t = blockIdx.x;
-    const int K = blk_rows(t, q, rem);
-    const int KP = K * (K + 1) / 2;
-    for (int f = threadIdx.x; f < KP; f += blockDim.x) Gp[f] = Gs[t * kpmax + f];
-    for (int i = threadIdx.x; i < K; i += blockDim.x) z[i] = 0.0;
-    __syncthreads();
-    for (int i = threadIdx.x; i < K; i += blockDim.x) Gp[pk(i, i)] += lambda;
-    __syncthreads();
-    static_assert(((KM + 3) / 4) * ((KM + 3) / 4 + 1) / 2 <= 256, "4 x 4 tiles cover the block");
-    if (!ldl_solve<4>(Gp, z, K, colbuf)) {
-        if (threadIdx.x == 0) *fail = 1;
-        return;
-    }
-    for (int i = threadIdx.x; i < K; i += blockDim.x) invd[i] = 1.0 / Gp[pk(i, i)];
-    __syncthreads();
-    // unit lower factor: l_ip = g_ip / d_p (i > p)
-    for (int f = threadIdx.x; f < KP; f += blockDim.x) {
-        int i = 0;
-        while (pk(i + 1, 0) <= f) ++i;
-        const int p2 = f - pk(i, 0);
-        if (p2 < i) Gp[f] *= invd[p2];
-    }
-    __syncthreads();
-    // M = L^{-1}, four threads per column (consecutive lanes of one wave)
-    {
-        const int j = threadIdx.x >> 2, qq = threadIdx.x & 3;
-        const int jc = (j < K) ? j : 0;
-        for (int i = 0; i < K; ++i) {
-            double part = 0.0;
-            for (int p2 = qq; p2 < i; p2 += 4) part = __builtin_fma(Gp[pk(i, p2)], M[p2][jc], part);
-            part += __shfl_xor(part, 1, 4);
-            part += __shfl_xor(part, 2, 4);
-            const double mij = (i > j) ? -part : ((i == j) ? 1.0 : 0.0);
-            if (j < K && qq == (i & 3)) M[i][j] = mij;
-        }
-    }
-    __syncthreads();
-    // H = M^T D^{-1} M
-    double *Hb = H + blk_hoff(t, q, rem);
-    for (int e = threadIdx.x; e < K * K; e += blockDim.x) {
-        const int i = e / K, j = e - i * K;
-        const int p0 = i > j ? i : j;
-        double sacc = 0.0;
-        for (int p2 = p0; p2 < K; ++p2) sacc = __builtin_fma(M[p2][i] * M[p2][j], invd[p2], sacc);
-        Hb[e] = sacc;
-    }
-}
-
 hipError_t launch_block_inverses_dense(const rorbk_handle_s *h, const void *A, int dt, int aligned,
                                        int32_t *d_fail, hipStream_t s) {
     const Layout &L = h->L;
@@ -870,22 +760,6 @@ hipError_t launch_block_inverses_dense(const rorbk_handle_s *h, const void *A, i
     if (e == hipSuccess) e = launch_block_inverses_from_grams(h, Gs, kp, d_fail, s);
     hipError_t e2 = hipFreeAsync(Gs, s);
     return e != hipSuccess ? e : e2;
-}
-
-hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const double *Gs, int64_t kp,
-                                            int32_t *d_fail, hipStream_t s) {
-    const Layout &L = h->L;
-    if (L.bmax > MAXB) return launch_big_block_inverses(h, Gs, kp, d_fail, s);
-    if (L.bmax <= 64)
-        hipLaunchKernelGGL(k_block_inverse_lds<64>, dim3((unsigned)L.k), dim3(256), 0, s, Gs, kp,
-                           L.q, L.rem, h->lambda, h->d_H, d_fail);
-    else if (L.bmax <= 72)
-        hipLaunchKernelGGL(k_block_inverse_lds<72>, dim3((unsigned)L.k), dim3(288), 0, s, Gs, kp,
-                           L.q, L.rem, h->lambda, h->d_H, d_fail);
-    else
-        hipLaunchKernelGGL(k_block_inverse<8>, dim3((unsigned)L.k), dim3(256), 0, s, Gs, kp, L.q,
-                           L.rem, h->lambda, h->d_H, d_fail);
-    return hipGetLastError();
 }
 
 }  // namespace rorbk

@@ -316,114 +316,4 @@ __device__ __forceinline__ void tile_of(int t, int nt, int *bi, int *bj) {
     *bj = t - base;
 }
 
-// Symmetric positive definite solve (G + diag) y = r for K <= MAXB in one
-// workgroup of 256 threads, G given packed lower in LDS (Gp, overwritten),
-// r in LDS (z, overwritten by y).  Factorisation G = L D L^T (unit L) by
-// right-looking elimination: thread t keeps one MT x MT tile of the lower
-// triangle in registers; at step k the owners of column k publish it to LDS
-// (double-buffered), and after one barrier everyone applies the rank-1 update
-// a_ij -= g_ik g_jk / d_k, which also carries the right-hand side through the
-// forward substitution.  Column k is kept in Gp (unscaled) for the backward
-// substitution y_k = z_k / d_k - sum_{i>k} (g_ik / d_k) y_i, run by wave 0.
-// Returns false (uniformly) if a pivot d_k is not positive.
-template <int MT>
-__device__ bool ldl_solve(double *Gp, double *z, int K, double *colbuf /* 2*MAXB */) {
-    __shared__ int s_bad;
-    const int nt = (K + MT - 1) / MT;
-    int bi = -1, bj = -1;
-    if ((int)threadIdx.x < nt * (nt + 1) / 2) tile_of(threadIdx.x, nt, &bi, &bj);
-    double a[MT][MT];
-#pragma unroll
-    for (int u = 0; u < MT; ++u)
-#pragma unroll
-        for (int v = 0; v < MT; ++v) {
-            const int i = bi * MT + u, j = bj * MT + v;
-            a[u][v] = (bi >= 0 && i < K && j <= i) ? Gp[pk(i, j)] : 0.0;
-        }
-    if (threadIdx.x == 0) s_bad = 0;
-    // column 0 comes straight from Gp
-    for (int i = threadIdx.x; i < K; i += blockDim.x) colbuf[i] = Gp[pk(i, 0)];
-    __syncthreads();
-    for (int k = 0; k < K; ++k) {
-        const double *col = colbuf + (k & 1) * MAXB;
-        double *nxt = colbuf + ((k + 1) & 1) * MAXB;
-        const double d = col[k];
-        if (!(d > 0.0)) {
-            if (threadIdx.x == 0) s_bad = 1;
-            break;  // uniform: every thread reads the same pivot
-        }
-        const double inv = 1.0 / d;
-        // right-hand side (forward substitution with unit L)
-        const double zk = z[k];
-        if (bi >= 0) {
-            double ci[MT], cj[MT];
-#pragma unroll
-            for (int u = 0; u < MT; ++u) {
-                const int i = bi * MT + u, j = bj * MT + u;
-                ci[u] = (i > k && i < K) ? col[i] : 0.0;
-                cj[u] = (j > k && j < K) ? col[j] * inv : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < MT; ++u)
-#pragma unroll
-                for (int v = 0; v < MT; ++v) a[u][v] = __builtin_fma(-ci[u], cj[v], a[u][v]);
-            // publish column k+1 (owners: tiles whose column block holds k+1)
-            const int kk = k + 1;
-            if (kk < K && kk / MT == bj) {
-#pragma unroll
-                for (int u = 0; u < MT; ++u) {
-                    const int i = bi * MT + u;
-#pragma unroll
-                    for (int v = 0; v < MT; ++v)
-                        if (bj * MT + v == kk && i >= kk && i < K) nxt[i] = a[u][v];
-                }
-            }
-        }
-        // keep column k (unscaled) for the backward pass; update z
-        for (int i = k + threadIdx.x; i < K; i += blockDim.x) {
-            Gp[pk(i, k)] = col[i];
-            if (i > k) z[i] = __builtin_fma(-col[i] * inv, zk, z[i]);
-        }
-        __syncthreads();
-    }
-    __syncthreads();
-    if (s_bad) return false;
-    // backward: y_k = z_k / d_k - sum_{i>k} (g_ik / d_k) y_i, column oriented
-    if (threadIdx.x < WAVE) {
-        const int lane = threadIdx.x;
-        double w[3], invd[3];
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const int i = lane + 64 * s;
-            invd[s] = (i < K) ? 1.0 / Gp[pk(i, i)] : 0.0;
-            w[s] = (i < K) ? z[i] * invd[s] : 0.0;
-        }
-        for (int k = K - 1; k >= 0; --k) {
-            const int s = k >> 6, src = k & 63;
-            double yk = (s == 0) ? w[0] : (s == 1 ? w[1] : w[2]);
-            yk = __shfl(yk, src, WAVE);
-#pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                const int i = lane + 64 * t;
-                if (i < k) w[t] = __builtin_fma(-Gp[pk(k, i)] * invd[t], yk, w[t]);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const int i = lane + 64 * s;
-            if (i < K) z[i] = w[s];
-        }
-    }
-    __syncthreads();
-    return true;
-}
-
-// Broadcast lane `src` (wave-uniform) of a double to the whole wave.
-__device__ __forceinline__ double bcast64(double v, int src) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffffLL), src);
-    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), src);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 }  // namespace rorbk
