@@ -1,6 +1,6 @@
 // rorbk_device.h -- device-side building blocks shared by the ROR-BK kernels:
-// element types, 16-byte vector loads, deterministic wave reductions and the
-// packed lower-triangular Cholesky used for every block Gram.
+// element types, 16-byte vector loads, FP64 MFMA Gram tiles and deterministic
+// reductions.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -14,7 +14,6 @@ namespace rorbk {
 
 constexpr int WAVE = 64;
 constexpr int MAXB = RORBK_MAX_BLOCK_ROWS + 1;          // largest block (rows)
-constexpr int PACKED_MAX = MAXB * (MAXB + 1) / 2;       // packed lower size
 constexpr int BIGB = RORBK_MAX_BIG_BLOCK_ROWS;          // largest block, dense large-block path
 constexpr int MAXK = BIGB > MAXB ? BIGB : MAXB;         // largest greedy set
 
@@ -55,66 +54,6 @@ template <typename V> __device__ __forceinline__ V to_v(bf16_t a) { return (V)bf
 __device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
-// Load VW consecutive elements starting at column c of a row (converted to V).
-// ALIGNED: the row start is 16-byte aligned and c is a multiple of VW, so a
-// full vector is one 16-byte load; the ragged tail (c + VW > n) is read
-// element by element with zeros past n.
-template <typename T, typename V, bool ALIGNED>
-__device__ __forceinline__ void load_vec(const T *__restrict__ row, int64_t c, int64_t n,
-                                         V (&out)[Tr<T>::VW]) {
-    constexpr int VW = Tr<T>::VW;
-    if (ALIGNED && c + VW <= n) {
-        if constexpr (sizeof(T) == 8) {
-            double2 v = *reinterpret_cast<const double2 *>(row + c);
-            out[0] = (V)v.x;
-            out[1] = (V)v.y;
-        } else if constexpr (sizeof(T) == 4) {
-            float4 v = *reinterpret_cast<const float4 *>(row + c);
-            out[0] = (V)v.x; out[1] = (V)v.y; out[2] = (V)v.z; out[3] = (V)v.w;
-        } else {
-            uint4 v = *reinterpret_cast<const uint4 *>(row + c);
-            uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                out[2 * e] = (V)__uint_as_float(w[e] << 16);
-                out[2 * e + 1] = (V)__uint_as_float(w[e] & 0xffff0000u);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < VW; ++e) out[e] = (c + e < n) ? to_v<V>(row[c + e]) : (V)0;
-    }
-}
-
-// Streaming variant for the residual pass: A is read once per pass, so the
-// loads carry the non-temporal hint.
-template <typename T, typename V, bool ALIGNED>
-__device__ __forceinline__ void load_vec_nt(const T *__restrict__ row, int64_t c, int64_t n,
-                                            V (&out)[Tr<T>::VW]) {
-    constexpr int VW = Tr<T>::VW;
-    if (ALIGNED && c + VW <= n) {
-        if constexpr (sizeof(T) == 8) {
-            dvec2 v = __builtin_nontemporal_load(reinterpret_cast<const dvec2 *>(row + c));
-            out[0] = (V)v.x;
-            out[1] = (V)v.y;
-        } else if constexpr (sizeof(T) == 4) {
-            fvec4 v = __builtin_nontemporal_load(reinterpret_cast<const fvec4 *>(row + c));
-            out[0] = (V)v.x; out[1] = (V)v.y; out[2] = (V)v.z; out[3] = (V)v.w;
-        } else {
-            uvec4 v = __builtin_nontemporal_load(reinterpret_cast<const uvec4 *>(row + c));
-            uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                out[2 * e] = (V)__uint_as_float(w[e] << 16);
-                out[2 * e + 1] = (V)__uint_as_float(w[e] & 0xffff0000u);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < VW; ++e) out[e] = (c + e < n) ? to_v<V>(row[c + e]) : (V)0;
-    }
-}
-
 // Elements of a raw 16-byte vector (VW elements from column c) at or past
 // `lim` set to zero, by selects (no branch).
 template <typename T>
@@ -145,20 +84,58 @@ __device__ __forceinline__ uvec4 mask_raw(uvec4 w, int64_t c, int64_t lim) {
 // multiple of VW elements, c a multiple of VW): one 16-byte load, which stays
 // inside the row's stride even when it crosses lim (c < lim <= n <= stride),
 // and the tail masked by selects, so the code has no branch around the load.
-// Otherwise a full vector whose address is 8-byte aligned (rows of 16- or
-// 32-bit values whose stride is a multiple of 8 bytes) is read as two 8-byte
-// loads, anything else element by element.
-template <typename T, bool ALIGNED>
+// Otherwise one 16-byte load at the element's own alignment (gfx950 reads any
+// byte address; a line that two loads share is read from the cache the second
+// time): of the vector at c, or, where that would cross lim, of the last whole
+// vector before lim, moved down by tail_shift.  Where no lane of the wave
+// crosses lim the shift is skipped by a scalar branch.  Rows of fewer than VW
+// elements are read one by one.
+typedef uvec4 uvec4_a2 __attribute__((aligned(2)));
+typedef uvec4 uvec4_a4 __attribute__((aligned(4)));
+typedef uvec4 uvec4_a8 __attribute__((aligned(8)));
+template <typename T, bool NT>
+__device__ __forceinline__ uvec4 load_any(const T *__restrict__ p) {
+    if constexpr (sizeof(T) == 2) {
+        const uvec4_a2 *q = reinterpret_cast<const uvec4_a2 *>(p);
+        return NT ? __builtin_nontemporal_load(q) : *q;
+    } else if constexpr (sizeof(T) == 4) {
+        const uvec4_a4 *q = reinterpret_cast<const uvec4_a4 *>(p);
+        return NT ? __builtin_nontemporal_load(q) : *q;
+    } else {
+        const uvec4_a8 *q = reinterpret_cast<const uvec4_a8 *>(p);
+        return NT ? __builtin_nontemporal_load(q) : *q;
+    }
+}
+
+// The vector at c from the one read at min(c, lim - VW): its elements moved
+// down by c - (lim - VW) places, zeros at or past lim (all zero for c >= lim).
+template <typename T>
+__device__ __forceinline__ uvec4 tail_shift(uvec4 w, int64_t c, int64_t lim) {
+    constexpr int VW = Tr<T>::VW;
+    const int64_t over = c - (lim - VW);
+    const uint32_t sh = over <= 0 ? 0u : (over >= VW ? 16u : (uint32_t)over * (uint32_t)sizeof(T));
+    if (sh & 8u) w = uvec4{w[2], w[3], 0u, 0u};
+    if (sh & 4u) w = uvec4{w[1], w[2], w[3], 0u};
+    if constexpr (sizeof(T) == 2) {
+        if (sh & 2u)
+            w = uvec4{(w[0] >> 16) | (w[1] << 16), (w[1] >> 16) | (w[2] << 16),
+                      (w[2] >> 16) | (w[3] << 16), w[3] >> 16};
+    }
+    return (sh & 16u) ? uvec4{0u, 0u, 0u, 0u} : w;
+}
+
+template <typename T, bool ALIGNED, bool NT = false>
 __device__ __forceinline__ uvec4 load_raw(const T *__restrict__ row, int64_t c, int64_t lim) {
     constexpr int VW = Tr<T>::VW;
-    if constexpr (ALIGNED) return mask_raw<T>(*reinterpret_cast<const uvec4 *>(row + c), c, lim);
-    if constexpr (!ALIGNED && sizeof(T) < 8) {
-        if (c + VW <= lim && (reinterpret_cast<uintptr_t>(row + c) & 7) == 0) {
-            const uint2 lo = *reinterpret_cast<const uint2 *>(row + c);
-            const uint2 hi = *reinterpret_cast<const uint2 *>(row + c + VW / 2);
-            const uvec4 v = {lo.x, lo.y, hi.x, hi.y};
-            return v;
-        }
+    if constexpr (ALIGNED) {
+        const uvec4 *pv = reinterpret_cast<const uvec4 *>(row + c);
+        return mask_raw<T>(NT ? __builtin_nontemporal_load(pv) : *pv, c, lim);
+    }
+    if (lim >= VW) {   // uniform
+        const bool full = c + VW <= lim;
+        uvec4 w = load_any<T, NT>(row + (full ? c : lim - VW));
+        if (__ballot(!full) != 0ull) w = tail_shift<T>(w, c, lim);
+        return w;
     }
     uvec4 w = {0u, 0u, 0u, 0u};
     if constexpr (sizeof(T) == 8) {
@@ -181,16 +158,6 @@ __device__ __forceinline__ uvec4 load_raw(const T *__restrict__ row, int64_t c, 
     return w;
 }
 
-// As load_raw, with the full 16-byte load marked non-temporal (streamed
-// once, not kept in the caches).
-template <typename T, bool ALIGNED>
-__device__ __forceinline__ uvec4 load_raw_nt(const T *__restrict__ row, int64_t c, int64_t lim) {
-    if constexpr (ALIGNED)
-        return mask_raw<T>(__builtin_nontemporal_load(reinterpret_cast<const uvec4 *>(row + c)),
-                           c, lim);
-    return load_raw<T, ALIGNED>(row, c, lim);
-}
-
 // load_raw of (row, c) when `ok` and c < lim, else zero, with no branch
 // around the load: otherwise the vector at (srow, sc) is read instead (any
 // vector known to lie inside the matrix, sc < lim) and dropped by a select.
@@ -210,7 +177,7 @@ template <typename T, bool ALIGNED>
 __device__ __forceinline__ uvec4 load_raw_nt_sel(const T *__restrict__ row, int64_t c, int64_t lim,
                                                  bool ok, const T *__restrict__ srow, int64_t sc) {
     const bool g = ok && c < lim;
-    const uvec4 w = load_raw_nt<T, ALIGNED>(g ? row : srow, g ? c : sc, lim);
+    const uvec4 w = load_raw<T, ALIGNED, true>(g ? row : srow, g ? c : sc, lim);
     const uvec4 z = {0u, 0u, 0u, 0u};
     return g ? w : z;
 }
