@@ -20,8 +20,9 @@
 //    products.  A greedy step replaces the first two by the factorisation and
 //    a backward solve.
 // Every sum is taken in a fixed order, so results are reproducible.
-#include "rorbk_device.h"
 #include "gram_tiles.h"
+#include "ldl_blk.h"
+#include "rorbk_device.h"
 
 namespace rorbk {
 
@@ -103,170 +104,93 @@ __device__ __forceinline__ double rsq_nr(double d) {
 }
 
 // 16 x 16 MFMA product on one wave from LDS (row strides RA, RB):
-// acc += A B^T (TRANSB) or A B.  Result element (i, j) sits in register i / 4
-// of lane (i % 4) * 16 + j; k is summed in steps of 4, in order.
-template <bool TRANSB>
+// acc += A B^T.  Result element (i, j) sits in register i / 4 of lane
+// (i % 4) * 16 + j; k is summed in steps of 4, in order.
 __device__ __forceinline__ dvec4 mm16(const double *A, int RA, const double *B, int RB, dvec4 acc) {
     const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
 #pragma unroll
-    for (int k0 = 0; k0 < 16; k0 += 4) {
-        const double a = A[li * RA + k0 + lk];
-        const double b = TRANSB ? B[li * RB + k0 + lk] : B[(k0 + lk) * RB + li];
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
+    for (int k0 = 0; k0 < 16; k0 += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[li * RA + k0 + lk], B[li * RB + k0 + lk], acc,
+                                                   0, 0, 0);
     return acc;
 }
 
-__device__ __forceinline__ void st16(double *D, int RD, dvec4 v, double scale) {
+__device__ __forceinline__ void st16(double *D, int RD, dvec4 v) {
     const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) D[(lk + 4 * r) * RD + li] = scale * v[r];
+    for (int r = 0; r < 4; ++r) D[(lk + 4 * r) * RD + li] = v[r];
 }
 
-// Broadcast of lane J of each 16-lane row to the whole row (DPP row_newbcast,
-// one 64-bit move, the value stays in vector registers).
-template <int J>
-__device__ __forceinline__ double rowbc(double v) {
-    return __builtin_amdgcn_mov_dpp(v, 0x150 + J, 0xf, 0xf, false);
-}
-
-// Pieces of one elimination step of f16 (compile-time indices, so every
-// register index is static): the trailing update of row i of the block and
-// the update of row i of the running transformation.
-// acc += (src of lane J of the 16-lane row) * mul.
-template <int J>
-__device__ __forceinline__ void fmac_bc(double &acc, double src, double mul) {
-    acc = __builtin_fma(rowbc<J>(src), mul, acc);
-}
-
-template <int k, int J>
-__device__ __forceinline__ void f16_a1(double (&a)[16], double nl, double akk) {
-    if constexpr (J > k) fmac_bc<J>(a[J], akk, nl);
-}
-template <int k, int J>
-__device__ __forceinline__ void f16_e1(double (&e)[16], double nle) {
-    if constexpr (J <= k) fmac_bc<k>(e[J], e[J], nle);
-}
-
-// Elimination step k of the LDL^T factorisation (unit lower factor U, pivots
-// d_k).  Lane i holds row i of the block (a) and row i of the running
-// transformation T (e, from the identity).  With u_ik = a_ik / d_k: rows
-// i > k take a_ij -= u_ik a_jk (j > k) and e_ij -= u_ik e_kj (j <= k); u_ik is
-// kept in a_ik.  1 / d_k is the hardware reciprocal r0 refined by Newton's
-// iteration, r1 = r0 (2 - d r0) and r2 = r1 (2 - d r1), with the last step
-// folded into its uses (u = a r1 + a r1 (1 - d r1)).  The next pivot is formed
-// straight from this one, d_{k+1} = a_{k+1,k+1} - a_{k+1,k}^2 / d_k, so the
-// chain from pivot to pivot is a few dependent operations; the broadcasts of
-// the a_jk do not wait for it.  After the last step a holds U below the
-// diagonal and e holds U^{-1}; `down` holds the lane's own pivot.
-template <int k, int... J>
-__device__ __forceinline__ void f16_step(double (&a)[16], double (&e)[16], double &down,
-                                         double &dnext, int i, bool &ok,
-                                         std::integer_sequence<int, J...>) {
-    const double d = rowbc<k>(dnext);
-    ok = ok && (d > 0.0) && isfinite(d);
-    const double r0 = __builtin_amdgcn_rcp(d);
-    const double e0 = __builtin_fma(-d, r0, 1.0);
-    const double r1 = __builtin_fma(r0, e0, r0);
-    const double e1 = __builtin_fma(-d, r1, 1.0);
-    const double akk = a[k];
-    const double m1 = akk * r1;
-    const double l = __builtin_fma(m1, e1, m1);
-    if constexpr (k + 1 < 16) {
-        const double t = akk * akk;
-        const double tr1 = t * r1;
-        const double u = __builtin_fma(-t, r1, a[k + 1]);
-        dnext = __builtin_fma(-tr1, e1, u);
-    }
-    (f16_a1<k, J>(a, -l, akk), ...);
-    const double nle = (i > k) ? -l : 0.0;   // transformation rows below the pivot only
-    (f16_e1<k, J>(e, nle), ...);
-    a[k] = (i == k) ? akk : l;
-    down = (i == k) ? d : down;
-}
-
-template <int J>
-__device__ __forceinline__ void f16_scale1(double (&a)[16], double sq) {
-    a[J] *= rowbc<J>(sq);
-}
-
-template <int... K>
-__device__ __forceinline__ void f16_steps(double (&a)[16], double (&e)[16], double &down, int i,
-                                          bool &ok, std::integer_sequence<int, K...>) {
-    double dnext = a[0];
-    (f16_step<K>(a, e, down, dnext, i, ok, std::make_integer_sequence<int, 16>{}), ...);
-}
-
-template <int... J>
-__device__ __forceinline__ void f16_scale(double (&a)[16], double sq,
-                                          std::integer_sequence<int, J...>) {
-    (f16_scale1<J>(a, sq), ...);
-}
-
-// Cholesky factor and inverse of a 16 x 16 SPD block in LDS (row stride RS) on
-// one wave, lane i & 15 holding row i (every 16-lane row of the wave carries
-// the same copy), from the LDL^T elimination: L = U D^{1/2} and L^{-1} =
-// D^{-1/2} U^{-1}, with 1 / sqrt(d_i) from rsq_nr.  The block is overwritten
-// by L (zeros above the diagonal) and Wl receives L^{-1}.
-__device__ __forceinline__ void f16(double *S, int RS, double *Wl, bool &ok) {
-    const int lane = threadIdx.x & 63, i = lane & 15;
-    double a[16], e[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        a[j] = (j <= i) ? S[i * RS + j] : 0.0;
-        e[j] = (j == i) ? 1.0 : 0.0;
-    }
-    double down = 1.0;
-    f16_steps(a, e, down, i, ok, std::make_integer_sequence<int, 16>{});
-    const double s = rsq_nr(down), sq = down * s;   // 1 / sqrt(d_i), sqrt(d_i)
-    f16_scale(a, sq, std::make_integer_sequence<int, 16>{});   // u_ij sqrt(d_j)
-    wsync();
-    if (lane < 16) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            S[i * RS + j] = (j < i) ? a[j] : ((j == i) ? sq : 0.0);
-            Wl[i * RS + j] = (j <= i) ? e[j] * s : 0.0;
-        }
-    }
-    wsync();
-}
-
-// Cholesky factor L and inverse W = L^{-1} of a 32 x 32 SPD tile in LDS (lower
-// part read; overwritten by L with zeros above), in two levels of 16:
-// L11, W11; L21 = A21 W11^T; A22 -= L21 L21^T; L22, W22; W21 = -W22 L21 W11.
-// Runs on wave 0; ends with a workgroup barrier.  Returns false (to wave 0) if
-// a pivot is not positive.
-__device__ bool tile_factor32(double (*S)[TB + 1], double (*Wl)[TB + 1]) {
+// W = L^{-1} of the Cholesky factor L of a 32 x 32 SPD tile in LDS (lower part
+// read), in two levels of 16 on wave 0 (lb_tile, ldl_blk.h: A = U D U^T with
+// E = U^{-1} formed beside it, so W_pp = D_p^{-1/2} E_p):
+// Y = E_1 A_21^T, A_22 -= Y^T D_1^{-1} Y, W_21 = -D_2^{-1/2} E_2 (Y^T D_1^{-1}) E_1,
+// on FP64 MFMA with the results left in registers.  (No one reads the
+// diagonal tiles of L.)  Ends with a workgroup barrier.  Returns false (to
+// wave 0) if a pivot is not positive.  One wave's instruction chain: 2.6 us,
+// 6.2 us when both levels carried the whole inverse in every lane and passed
+// their products through LDS.
+__device__ bool tile_inverse32(double (*S)[TB + 1], double (*Wl)[TB + 1]) {
+    __shared__ double rd[TB];
+    __shared__ __align__(16) double sE[256];
     bool ok = true;
     if (threadIdx.x < 64) {
-        constexpr int RS = TB + 1;
-        const dvec4 z4 = {0.0, 0.0, 0.0, 0.0};
-        f16(&S[0][0], RS, &Wl[0][0], ok);
-        const dvec4 l21 = mm16<true>(&S[16][0], RS, &Wl[0][0], RS, z4);
-        wsync();
-        st16(&S[16][0], RS, l21, 1.0);
-        wsync();
-        const dvec4 u = mm16<true>(&S[16][0], RS, &S[16][0], RS, z4);
-        {
-            const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+        const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
+        double a[16], e1[4], e2[4], none = 0.0;
+        dvec4 t12, t22;   // A_21^T and A_22, entry (lk + 4 r, li) in register r
 #pragma unroll
-            for (int r = 0; r < 4; ++r) S[16 + lk + 4 * r][16 + li] -= u[r];
+        for (int r = 0; r < 4; ++r) {
+            const int i = lk + 4 * r;
+            t12[r] = S[16 + li][i];
+            t22[r] = (i >= li) ? S[16 + i][16 + li] : S[16 + li][16 + i];
         }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] = (j <= li) ? S[li][j] : S[j][li];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e1[q] = e2[q] = (li == 4 * q + lk) ? 1.0 : 0.0;
         wsync();
-        f16(&S[16][16], RS, &Wl[16][16], ok);
-        const dvec4 t1 = mm16<false>(&S[16][0], RS, &Wl[0][0], RS, z4);     // L21 W11
+        lb_tile(std::make_integer_sequence<int, 16>{}, a, e1, none, rd, li);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sE[li * 16 + 4 * q + lk] = e1[q];
         wsync();
-        st16(&Wl[16][0], RS, t1, 1.0);
+        dvec4 y = {0.0, 0.0, 0.0, 0.0}, v;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y = __builtin_amdgcn_mfma_f64_16x16x4f64(e1[q], t12[q], y, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = -y[q] * rd[4 * q + lk];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t22 = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q], y[q], t22, 0, 0, 0);
+        // -(Y^T D_1^{-1}) E_1 in the shadow of the row turn of A_22
+        dvec4 b = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[lk + 4 * r][li] = t22[r];
         wsync();
-        const dvec4 w21 = mm16<false>(&Wl[16][16], RS, &Wl[16][0], RS, z4);  // W22 (L21 W11)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] = S[j][li];   // symmetric: row li
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            b = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q], sE[(4 * q + lk) * 16 + li], b, 0, 0, 0);
+        none = 0.0;
+        lb_tile(std::make_integer_sequence<int, 16>{}, a, e2, none, rd + 16, li);
         wsync();
-        st16(&Wl[16][0], RS, w21, -1.0);
-        {
-            const int l = threadIdx.x & 63;
-            for (int e = l; e < 256; e += 64) {
-                S[e >> 4][16 + (e & 15)] = 0.0;
-                Wl[e >> 4][16 + (e & 15)] = 0.0;
-            }
+        dvec4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x = __builtin_amdgcn_mfma_f64_16x16x4f64(e2[q], b[q], x, 0, 0, 0);
+        // lane l < 32: 1 / sqrt(d_l) = sqrt(r_l)
+        const double r = rd[lane & 31];
+        ok = __ballot(!(r > 0.0 && r < __builtin_inf())) == 0ull;
+        const double sq = r * rsq_nr(r);
+        wsync();
+        if (lane < TB) rd[lane] = sq;
+        wsync();
+        const double s1 = rd[li], s2 = rd[16 + li];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int j = 4 * q + lk;
+            Wl[li][j] = e1[q] * s1;
+            Wl[16 + li][16 + j] = e2[q] * s2;
+            Wl[16 + j][li] = x[q] * rd[16 + j];
+            Wl[li][16 + j] = 0.0;
         }
         wsync();
     }
@@ -279,13 +203,13 @@ __device__ bool tile_factor32(double (*S)[TB + 1], double (*Wl)[TB + 1]) {
 __device__ __forceinline__ dvec4 mm32_abt(const double (*A)[TB + 1], const double (*B)[TB + 1]) {
     const int w = threadIdx.x >> 6, R = w >> 1, C = w & 1;
     const dvec4 z4 = {0.0, 0.0, 0.0, 0.0};
-    dvec4 acc = mm16<true>(&A[R * 16][0], TB + 1, &B[C * 16][0], TB + 1, z4);
-    return mm16<true>(&A[R * 16][16], TB + 1, &B[C * 16][16], TB + 1, acc);
+    dvec4 acc = mm16(&A[R * 16][0], TB + 1, &B[C * 16][0], TB + 1, z4);
+    return mm16(&A[R * 16][16], TB + 1, &B[C * 16][16], TB + 1, acc);
 }
 
 __device__ __forceinline__ void st32(double (*D)[TB + 1], dvec4 v) {
     const int w = threadIdx.x >> 6, R = w >> 1, C = w & 1;
-    st16(&D[R * 16][C * 16], TB + 1, v, 1.0);
+    st16(&D[R * 16][C * 16], TB + 1, v);
 }
 
 // 32 x 32 tiles on 256 threads: thread t takes entries t + 256 u (u < 4); the
@@ -337,7 +261,7 @@ __device__ __forceinline__ void tile_store(double *dst, int ld, const double (*S
 //   needs; the (I, p + 1) workgroups store L_Ip in Lf),
 //   G_IJ -= L_Ip L_Jp^T,
 // and the workgroup of the new diagonal tile (p + 1, p + 1) factors it at once
-// into Lf and its inverse into W.  Launch p = -1 factors tile (0, 0).  In the
+// and puts the factor's inverse into W.  Launch p = -1 factors tile (0, 0).  In the
 // greedy form (PR = P + 1) tile row P is the right-hand side, whose last slot
 // (P, P) only completes L_{P, P-1}; G keeps the updated, unscaled tiles.
 __global__ __launch_bounds__(256) void k_big_chol_col(double *__restrict__ G,
@@ -399,8 +323,8 @@ __global__ __launch_bounds__(256) void k_big_chol_col(double *__restrict__ G,
         __syncthreads();
     }
     if (I == J && (p < 0 || J == p + 1)) {
-        // the new diagonal tile: factor in place, inverse into sW
-        const bool ok = tile_factor32(sT, sW);
+        // the new diagonal tile: its factor's inverse into sW
+        const bool ok = tile_inverse32(sT, sW);
         if (threadIdx.x == 0 && !ok) {
             if (fail) *fail = 1;
             if (ctrl) {
@@ -408,7 +332,6 @@ __global__ __launch_bounds__(256) void k_big_chol_col(double *__restrict__ G,
                 ctrl->done = 1;
             }
         }
-        tile_store(Lb + (int64_t)(J * TB) * ld + J * TB, ld, sT);
         double *Wj = W + ((int64_t)bt * P + J) * TB * TB;
         for (int e = threadIdx.x; e < TB * TB; e += blockDim.x) Wj[e] = sW[e / TB][e % TB];
     } else {
