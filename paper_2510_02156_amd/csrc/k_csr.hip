@@ -231,17 +231,33 @@ __global__ __launch_bounds__(256) void k_csr_centroid(const int64_t *__restrict_
 //      chunk by one thread;
 //   3. Pout[i] = A_{S'} x for the next step's rows S' (entry products summed in
 //      entry order per row).
-// Everything that does not depend on y or on the new x is fetched first: the
-// row offsets, the first chunk's entries and their hash slots, and the next
-// rows' entries (when they fit CSR_NCAP), so the dependent part is the stored
-// inverse product, one read-modify-write of x and one gather of x.
+// What bounds it is latency: one workgroup, a chain of memory and LDS round
+// trips.  So everything that does not depend on y is done before y is known,
+// for the first chunk (blocks of at most CSR_CHUNK entries have no other): the
+// entries with their hash slots, the entry lists of the columns with several
+// terms in row order, the old x of the block's columns, and the next rows'
+// entries with the old x of their columns and the slots of those that this
+// step changes.  Half of the waves do that while the other half hold the
+// stored inverse in registers and form y: in one wave the two would not fit
+// the registers, and every spilled load is a wait.  After y only LDS work is
+// left: the terms, the sums, and the products, which take a changed column's
+// new value from LDS.  128-row blocks of 13 entries a row: 23 us with the
+// gathers of x behind y, a scan of the chunk per repeated column and a binary
+// search per entry, 19 us so.
 // With b == NULL the step is the adjoint one: gb[S] -= y.
-constexpr int CSR_STEP_T = 512;
+constexpr int CSR_STEP_T = 1024;
 constexpr int CSR_CHUNK = 2048;         // entries per update chunk
 constexpr int CSR_HASH = 4096;          // hash slots (a power of two >= 2 * CSR_CHUNK)
 constexpr int CSR_HASH_BITS = 12;
-constexpr int CSR_NCAP = 2048;          // next-row entries prefetched (4 per thread)
+constexpr int CSR_NCAP = 2048;          // next-row entries prefetched
 constexpr int CSR_TPR = 4;              // threads per row of the stored-inverse product
+constexpr int CSR_HG = 4;               // its entries per group
+constexpr int CSR_HU = ((MAXB + CSR_TPR - 1) / CSR_TPR + CSR_HG - 1) / CSR_HG * CSR_HG;
+constexpr int CSR_HT = CSR_STEP_T / 2;  // threads of the product; the others take the entries
+constexpr int CSR_ET = CSR_STEP_T - CSR_HT;
+static_assert(MAXB <= 2 * CSR_HT / CSR_TPR, "two rows per thread group");
+static_assert(CSR_HU * CSR_TPR * MAXB - MAXB * MAXB + MAXB <= RORBK_CSR_PAD,
+              "columns read past a stored inverse stay inside the allocation");
 
 struct CsrStepP {
     const int64_t *rowptr;
@@ -349,11 +365,25 @@ __device__ __forceinline__ void csr_apply_chunk(V *__restrict__ x, int ne, const
     __syncthreads();
 }
 
+__device__ __forceinline__ uint32_t csr_hash(int32_t c) {
+    return ((uint32_t)c * 2654435761u) >> (32 - CSR_HASH_BITS);
+}
+
+// Rows of the entries [0, cap) of a row set into LDS, CSR_TPR threads per row.
+__device__ __forceinline__ void csr_entry_rows(const int64_t *off, const int64_t *len, int R,
+                                               int cap, int16_t *row) {
+    for (int i = threadIdx.x / CSR_TPR; i < R; i += CSR_STEP_T / CSR_TPR) {
+        const int64_t o = off[i];
+        const int64_t e1 = (o + len[i] < cap) ? o + len[i] : cap;
+        for (int64_t e = o + threadIdx.x % CSR_TPR; e < e1; e += CSR_TPR) row[e] = (int16_t)i;
+    }
+}
+
 template <typename T, typename V>
 __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     const int tid = threadIdx.x;
     const T *__restrict__ val = (const T *)p.val;
-    V *__restrict__ x = (V *)p.x;
+    V *x = (V *)p.x;
     const V *__restrict__ b = (const V *)p.b;
     int tc = -1, cnt = 0, ncnt = 0;
     int64_t cst = 0, nst = 0;
@@ -374,18 +404,22 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     if (p.ctrl->done) return;
     const bool upd = p.ymode != 2 && cnt > 0;
 
-    __shared__ double s_r[MAXB], s_y[MAXB];
+    __shared__ double s_r[CSR_HU * CSR_TPR], s_y[MAXB];
     __shared__ int64_t s_len[MAXB], s_off[MAXB + 1], s_p0[MAXB];
     __shared__ int64_t n_len[MAXB], n_off[MAXB + 1], n_p0[MAXB];
     __shared__ int32_t e_col[CSR_CHUNK], e_slot[CSR_CHUNK], s_dup[CSR_CHUNK];
-    __shared__ int16_t e_row[CSR_CHUNK];
+    __shared__ int16_t e_row[CSR_CHUNK], n_row[CSR_NCAP];
     __shared__ V e_val[CSR_CHUNK];
     __shared__ V n_prod[CSR_NCAP];
     __shared__ int32_t h_key[CSR_HASH], h_head[CSR_HASH];
     __shared__ uint32_t h_cnt[CSR_HASH];
     __shared__ int s_ndup;
+    // lists of the columns with several terms, laid over s_dup: entries in
+    // arrival order, then in row order
+    int16_t *l_any = (int16_t *)s_dup, *l_ord = l_any + CSR_CHUNK;
 
     // A. row offsets of both row sets; b - Pin or the given y
+    if (tid < CSR_HU * CSR_TPR) s_r[tid] = 0.0;
     if (upd) {
         for (int i = tid; i < cnt; i += CSR_STEP_T) {
             const int64_t row = (p.cur.kind == 1) ? (int64_t)p.cur.idx[i] : cst + i;
@@ -396,7 +430,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
             else s_y[i] = p.ygiven[i];
         }
     }
-    for (int i = tid; i < ncnt; i += CSR_STEP_T) {
+    for (int i = tid - CSR_STEP_T / 2; i >= 0 && i < ncnt; i += CSR_STEP_T) {
         const int64_t row = (p.nxt.kind == 1) ? (int64_t)p.nxt.idx[i] : nst + i;
         const int64_t p0 = p.rowptr[row];
         n_p0[i] = p0;
@@ -425,90 +459,231 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     __syncthreads();
     const int64_t tot = upd ? s_off[cnt] : 0;
     const int64_t ntot = (ncnt > 0) ? n_off[ncnt] : 0;
-    // B. the next rows' entries (x-independent) into registers
     const bool npre = ntot <= CSR_NCAP;
-    constexpr int NU = CSR_NCAP / CSR_STEP_T;
-    int32_t ncol[NU];
-    T nval[NU];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        const int e = tid + u * CSR_STEP_T;
-        ncol[u] = 0;
-        nval[u] = (T)0;
-        if (npre && e < ntot) {
-            const int r = row_of_entry(n_off, ncnt, e);
-            const int64_t pp = n_p0[r] + (e - n_off[r]);
-            ncol[u] = p.colidx[pp];
-            nval[u] = val[pp];
-        }
-    }
-    // C. the first chunk of this block's entries with their hash slots
     const int ne0 = (int)((tot < CSR_CHUNK) ? tot : CSR_CHUNK);
-    if (upd)
-        csr_stage_chunk<T, V>(p.colidx, val, s_off, s_p0, cnt, 0, ne0, e_col, e_val, e_row,
-                              e_slot, h_key, h_head, h_cnt);
-    // D. y = H_t r_S: CSR_TPR threads per row, rows i0 and i0 + 128 per thread,
-    //    every load of both rows in flight at once
-    if (upd && p.ymode == 0) {
-        const double *__restrict__ H = p.H + blk_hoff(tc, p.q, p.rem);
-        constexpr int HU = (MAXB + CSR_TPR - 1) / CSR_TPR;
-        constexpr int RPP = CSR_STEP_T / CSR_TPR;   // rows per pass (MAXB <= 2 * RPP)
-        static_assert(MAXB <= 2 * RPP, "two row slots per thread cover a block");
-        const int qd = tid % CSR_TPR, i0 = tid / CSR_TPR, i1 = i0 + RPP;
-        double h0[HU], h1[HU];
+    const int nn = npre ? (int)ntot : 0;
+    if (upd) csr_entry_rows(s_off, s_len, cnt, CSR_CHUNK, e_row);
+    if (npre) csr_entry_rows(n_off, n_len, ncnt, CSR_NCAP, n_row);
+    __syncthreads();
+    constexpr int EU = CSR_CHUNK / CSR_ET, NU = CSR_NCAP / CSR_ET;
+    int32_t ec[EU], nc[NU];
+    T ev[EU], nv[NU];
+    int er[EU], es[EU], eb[EU], ns[NU];
+    uint32_t ek[EU], em[EU];   // arrival number, then rank, in the column; its terms
+    V ex[EU], nx[NU];
+    const bool own_y = upd && p.ymode == 0;
+    const bool entries = __builtin_amdgcn_readfirstlane(tid) >= CSR_HT;   // scalar
+    const int t1 = tid - CSR_HT;
+    bool multi;
+    if (!entries) {
+        // B. y = H_t r_S: row tid / 4 (and that + 128 of larger blocks),
+        // columns tid % 4 + 4 u (columns past it, finite, meet zeros of s_r);
+        // the loads travel through the other half's barriers
+        const int qd = tid % CSR_TPR;
+        int hi = tid / CSR_TPR;
+        double hv[CSR_HU];
+        auto load_row = [&]() {
+            const double *ph = p.H + blk_hoff(tc, p.q, p.rem) + (int64_t)qd * cnt + (hi < cnt ? hi : 0);
+            const int64_t st = (int64_t)CSR_TPR * cnt;
 #pragma unroll
-        for (int u = 0; u < HU; ++u) {
-            const int j = qd + CSR_TPR * u;
-            h0[u] = (i0 < cnt && j < cnt) ? H[(int64_t)j * cnt + i0] : 0.0;
-            h1[u] = (i1 < cnt && j < cnt) ? H[(int64_t)j * cnt + i1] : 0.0;
-        }
-        double s0 = 0.0, s1 = 0.0;
+            for (int u0 = 0; u0 < CSR_HU; u0 += CSR_HG)
+                if (CSR_TPR * u0 < cnt) {   // uniform
 #pragma unroll
-        for (int u = 0; u < HU; ++u) {
-            const int j = qd + CSR_TPR * u;
-            if (j < cnt) {
-                s0 = __builtin_fma(h0[u], s_r[j], s0);
-                s1 = __builtin_fma(h1[u], s_r[j], s1);
+                    for (int u = u0; u < u0 + CSR_HG; ++u) {
+                        hv[u] = *ph;
+                        ph += st;
+                    }
+                }
+        };
+        auto dot_row = [&]() {
+            double s0 = 0.0;
+#pragma unroll
+            for (int u0 = 0; u0 < CSR_HU; u0 += CSR_HG)
+                if (CSR_TPR * u0 < cnt) {
+#pragma unroll
+                    for (int u = u0; u < u0 + CSR_HG; ++u)
+                        s0 = __builtin_fma(hv[u], s_r[qd + CSR_TPR * u], s0);
+                }
+            s0 = group_sum(s0, CSR_TPR);
+            if (qd == 0 && hi < cnt) s_y[hi] = s0;
+        };
+        if (own_y) load_row();
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+        multi = s_ndup > 0;
+        if (multi) __syncthreads();
+        if (own_y) {
+            dot_row();
+            if (cnt > CSR_HT / CSR_TPR) {   // uniform
+                hi += CSR_HT / CSR_TPR;
+                load_row();
+                dot_row();
             }
         }
-        s0 = group_sum(s0, CSR_TPR);
-        s1 = group_sum(s1, CSR_TPR);
-        if (qd == 0) {
-            if (i0 < cnt) s_y[i0] = s0;
-            if (i1 < cnt) s_y[i1] = s1;
+    } else {
+        // C. the first chunk's entries and the next rows' (a thread past the
+        // end loads the last entry again and drops it, so that no load sits
+        // behind a lane's branch), then the old x
+        if (ne0 > 0) {   // uniform
+            int64_t pp[EU];
+#pragma unroll
+            for (int u = 0; u < EU; ++u) {
+                const int e = t1 + u * CSR_ET, ee = e < ne0 ? e : ne0 - 1;
+                er[u] = e_row[ee];
+                pp[u] = s_p0[er[u]] + (ee - s_off[er[u]]);
+            }
+#pragma unroll
+            for (int u = 0; u < EU; ++u) ec[u] = p.colidx[pp[u]];
+#pragma unroll
+            for (int u = 0; u < EU; ++u) ev[u] = val[pp[u]];
+        }
+        if (nn > 0) {
+            int64_t pp[NU];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const int e = t1 + u * CSR_ET, ee = e < nn ? e : nn - 1;
+                const int r = n_row[ee];
+                pp[u] = n_p0[r] + (ee - n_off[r]);
+            }
+#pragma unroll
+            for (int u = 0; u < NU; ++u) nc[u] = p.colidx[pp[u]];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) nv[u] = val[pp[u]];
+        }
+        if (ne0 > 0) {
+#pragma unroll
+            for (int u = 0; u < EU; ++u) ex[u] = x[ec[u]];
+        }
+        if (nn > 0) {
+#pragma unroll
+            for (int u = 0; u < NU; ++u) nx[u] = x[nc[u]];
+        }
+        // hash slots and arrival numbers
+#pragma unroll
+        for (int u = 0; u < EU; ++u) {
+            const int e = t1 + u * CSR_ET;
+            es[u] = 0;
+            ek[u] = 0;
+            if (e < ne0) {
+                uint32_t sl = csr_hash(ec[u]);
+                while (true) {
+                    const int32_t old = atomicCAS(&h_key[sl], -1, ec[u]);
+                    if (old == -1 || old == ec[u]) break;
+                    sl = (sl + 1) & (CSR_HASH - 1);
+                }
+                es[u] = (int)sl;
+                ek[u] = atomicAdd(&h_cnt[sl], 1u);
+                atomicMin(&h_head[sl], e);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < EU; ++u) em[u] = (t1 + u * CSR_ET < ne0) ? h_cnt[es[u]] : 0u;
+        // the slots of the next rows' columns (-1: not changed by this chunk)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            ns[u] = -1;
+            if (upd && t1 + u * CSR_ET < nn) {
+                uint32_t sl = csr_hash(nc[u]);
+                while (true) {
+                    const int32_t key = h_key[sl];
+                    if (key == nc[u]) ns[u] = (int)sl;
+                    if (key == nc[u] || key == -1) break;
+                    sl = (sl + 1) & (CSR_HASH - 1);
+                }
+            }
+        }
+        // entry lists of the columns with several terms: a segment per column
+        // (h_key holds its start from here on), the entries in arrival order,
+        // then each to its rank, the number of smaller ones in its segment
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < EU; ++u)
+            if (em[u] > 1u && ek[u] == 0u) h_key[es[u]] = atomicAdd(&s_ndup, (int)em[u]);
+        __syncthreads();
+        multi = s_ndup > 0;
+        if (multi) {   // uniform
+#pragma unroll
+            for (int u = 0; u < EU; ++u) {
+                eb[u] = (em[u] > 1u) ? h_key[es[u]] : 0;
+                if (em[u] > 1u) l_any[eb[u] + (int)ek[u]] = (int16_t)(t1 + u * CSR_ET);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < EU; ++u)
+                if (em[u] > 1u) {
+                    const int e = t1 + u * CSR_ET;
+                    int rank = 0;
+                    for (int i = 0; i < (int)em[u]; ++i) rank += (l_any[eb[u] + i] < e) ? 1 : 0;
+                    l_ord[eb[u] + rank] = (int16_t)e;
+                    ek[u] = (uint32_t)rank;
+                }
         }
     }
     __syncthreads();
-    if (upd && p.gb) {
+    if (upd && p.gb && !entries) {
         V *gb = (V *)p.gb;
-        for (int i = tid; i < cnt; i += CSR_STEP_T) {
+        for (int i = tid; i < cnt; i += CSR_HT) {
             const int64_t row = (p.cur.kind == 1) ? (int64_t)p.cur.idx[i] : cst + i;
             gb[row] -= (V)s_y[i];
         }
     }
-    // E. x += A_S^T y, chunk by chunk
-    if (upd) {
-        csr_apply_chunk<V>(x, ne0, s_y, e_col, e_val, e_row, e_slot, h_head, h_cnt, s_dup,
-                           &s_ndup);
-        for (int64_t base = CSR_CHUNK; base < tot; base += CSR_CHUNK) {
-            const int ne = (int)((tot - base < CSR_CHUNK) ? tot - base : CSR_CHUNK);
-            csr_clear_hash(h_key, h_head, h_cnt);
-            if (tid == 0) s_ndup = 0;
-            __syncthreads();
-            csr_stage_chunk<T, V>(p.colidx, val, s_off, s_p0, cnt, base, ne, e_col, e_val, e_row,
-                                  e_slot, h_key, h_head, h_cnt);
-            __syncthreads();
-            csr_apply_chunk<V>(x, ne, s_y, e_col, e_val, e_row, e_slot, h_head, h_cnt, s_dup,
-                               &s_ndup);
+    // D. x += A_S^T y: the terms, then the new x of each column, which stays in
+    // its first entry's place
+    V et[EU];
+    if (entries) {
+#pragma unroll
+        for (int u = 0; u < EU; ++u) {
+            const int e = t1 + u * CSR_ET;
+            if (e < ne0) {
+                et[u] = (V)ev[u] * (V)s_y[er[u]];
+                if (em[u] > 1u) e_val[e] = et[u];
+            }
         }
     }
-    // F. products of the next rows with the updated x
+    if (multi) __syncthreads();
+    if (entries) {
+#pragma unroll
+        for (int u = 0; u < EU; ++u) {
+            const int e = t1 + u * CSR_ET;
+            if (em[u] == 1u || (em[u] > 1u && ek[u] == 0u)) {
+                V add = et[u];
+                if (em[u] > 1u) {
+                    add = (V)0;
+                    for (int i = 0; i < (int)em[u]; ++i) add = add + e_val[l_ord[eb[u] + i]];
+                }
+                const V xn = ex[u] + add;
+                x[ec[u]] = xn;
+                e_val[e] = xn;
+            }
+        }
+    }
+    __syncthreads();
+    // further chunks of a block with more entries, one after the other
+    for (int64_t base = CSR_CHUNK; base < tot; base += CSR_CHUNK) {
+        const int ne = (int)((tot - base < CSR_CHUNK) ? tot - base : CSR_CHUNK);
+        csr_clear_hash(h_key, h_head, h_cnt);
+        if (tid == 0) s_ndup = 0;
+        __syncthreads();
+        csr_stage_chunk<T, V>(p.colidx, val, s_off, s_p0, cnt, base, ne, e_col, e_val, e_row,
+                              e_slot, h_key, h_head, h_cnt);
+        __syncthreads();
+        csr_apply_chunk<V>(x, ne, s_y, e_col, e_val, e_row, e_slot, h_head, h_cnt, s_dup, &s_ndup);
+    }
+    // E. products of the next rows with the updated x
     if (ncnt > 0) {
         if (npre) {
+            const bool one = tot <= CSR_CHUNK;   // the old x and the first chunk's changes hold
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
-                const int e = tid + u * CSR_STEP_T;
-                if (e < ntot) n_prod[e] = (V)nval[u] * x[ncol[u]];
+                const int e = t1 + u * CSR_ET;
+                if (entries && e < nn) {
+                    V xv;
+                    if (one) xv = (ns[u] >= 0) ? e_val[h_head[ns[u]]] : nx[u];
+                    else xv = x[nc[u]];
+                    n_prod[e] = (V)nv[u] * xv;
+                }
             }
             __syncthreads();
             for (int i = tid; i < ncnt; i += CSR_STEP_T) {

@@ -718,7 +718,8 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     ALLOC(h->d_S, k);
     ALLOC(h->d_pbar, k);
     ALLOC(h->d_W, k);
-    ALLOC(h->d_H, htotal + RORBK_FWD_PAD);
+    const int64_t hpad = L.format == RORBK_CSR ? RORBK_CSR_PAD : RORBK_FWD_PAD;
+    ALLOC(h->d_H, htotal + hpad);
     ALLOC(h->d_ctrl, 1);
     ALLOC(h->d_P[0], (int64_t)L.nch_u * bmax);
     ALLOC(h->d_P[1], (int64_t)L.nch_u * bmax);
@@ -816,11 +817,11 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     if (hipMemsetAsync(h->d_selcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess ||
         (h->d_fwdcnt &&
          hipMemsetAsync(h->d_fwdcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess) ||
-        // the chain step reads, and multiplies by zero, entries past the
-        // matrices in these: they have to be finite
-        (h->d_XG &&
-         (launch_fill_zero(h->d_XG, 8 * (6 * bmax * bmax + RORBK_FWD_PAD), (hipStream_t)stream) != hipSuccess ||
-          launch_fill_zero(h->d_H + htotal, 8 * RORBK_FWD_PAD, (hipStream_t)stream) != hipSuccess)) ||
+        // the chain step and the CSR step read, and multiply by zero, entries
+        // past the matrices in these: they have to be finite
+        launch_fill_zero(h->d_H + htotal, 8 * hpad, (hipStream_t)stream) != hipSuccess ||
+        (h->d_XG && launch_fill_zero(h->d_XG, 8 * (6 * bmax * bmax + RORBK_FWD_PAD),
+                                     (hipStream_t)stream) != hipSuccess) ||
         (h->d_C && launch_fill_zero(h->d_C, 8 * (int64_t)L.nch_c * 3 * RORBK_FWD_MAX_BLOCK * 64,
                                     (hipStream_t)stream) != hipSuccess)) {
         destroy_all(h);

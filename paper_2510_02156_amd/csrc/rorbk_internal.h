@@ -39,6 +39,9 @@ constexpr int RORBK_FWD_MAX_BLOCK = 65;
 // steps' loads: they read, and multiply by zero, up to nine columns of at most
 // RORBK_FWD_MAX_BLOCK entries past a matrix's last and one more.
 constexpr int RORBK_FWD_PAD = 12 * RORBK_FWD_MAX_BLOCK;
+// The same behind the stored inverses of CSR blocks, whose step reads whole
+// groups of 16 columns.
+constexpr int RORBK_CSR_PAD = 17 * (RORBK_MAX_BLOCK_ROWS + 1);
 
 // The cross-Gram tile jobs a residual launch carries (jobs == 0: none).
 struct XgSide {
