@@ -907,22 +907,9 @@ __global__ __launch_bounds__(64 * CW_NW) void k_chol_wg(
     const double *__restrict__ Gpart, int nch, int K, double lambda,
     const double *__restrict__ rI, const double *__restrict__ Pin, int nchP, int bmax,
     double *__restrict__ y, Ctrl *__restrict__ ctrl) {
-    constexpr int NTH = 64 * CW_NW, U = (16 * P * (16 * P + 1) / 2 + NTH - 1) / NTH;
     __shared__ __align__(16) double T[wl_tiles(P) * WT];
     __shared__ double rd[16 * P], z[16 * P];
     const int stop = __hip_atomic_load(&ctrl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int KP = K * (K + 1) / 2;
-    double g[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) g[u] = 0.0;
-    for (int c = 0; c < nch; ++c) {
-        const double *gc = Gpart + (int64_t)c * KP;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int f = threadIdx.x + u * NTH;
-            g[u] += gc[f < KP ? f : KP - 1];
-        }
-    }
     if (threadIdx.x < 16 * P) {
         const int q = threadIdx.x;
         double v = 0.0;
@@ -937,12 +924,7 @@ __global__ __launch_bounds__(64 * CW_NW) void k_chol_wg(
         z[q] = v;
     }
     if (stop) return;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int f = threadIdx.x + u * NTH;
-        if (f < KP) wl_put(T, P, f, g[u], lambda);
-    }
-    wl_pad(T, P, K);
+    wl_load<P, CW_NW>(T, Gpart, nch, K, lambda);
     if (!wl_factor<P, CW_NW, true>(T, rd, z)) {
         if (threadIdx.x == 0) {
             ctrl->status = RORBK_ERR_NOT_SPD;
@@ -966,23 +948,12 @@ template <int P>
 __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
     const double *__restrict__ Gs, int64_t kpmax, int64_t q, int64_t rem, double lambda,
     double *__restrict__ H, int32_t *__restrict__ fail) {
-    constexpr int NW = bi_waves<P>(), NTH = 64 * NW;
+    constexpr int NW = bi_waves<P>();
     __shared__ __align__(16) double T[wl_tiles(P) * WT];
     __shared__ double rd[16 * P];
     const int64_t t = blockIdx.x;
     const int K = blk_rows(t, q, rem);
-    const int KP = K * (K + 1) / 2;
-    const double *g = Gs + t * kpmax;
-    constexpr int U = 4;
-    for (int f0 = threadIdx.x; f0 < KP; f0 += U * NTH) {
-        double v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = g[f0 + u * NTH < KP ? f0 + u * NTH : KP - 1];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (f0 + u * NTH < KP) wl_put(T, P, f0 + u * NTH, v[u], lambda);
-    }
-    wl_pad(T, P, K);
+    wl_load<P, NW>(T, Gs + t * kpmax, 1, K, lambda);
     if (!wl_factor<P, NW, false>(T, rd, nullptr)) {
         if (threadIdx.x == 0) *fail = 1;
         return;

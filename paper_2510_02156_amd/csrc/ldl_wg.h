@@ -4,13 +4,14 @@
 // (Section 3.1).  Internal to the library.
 //
 // The matrix is kept as the upper 16 x 16 tiles T_pJ (p <= J) of its padded
-// size 16 P, row-major, in LDS.  Tile row p: wave 0 eliminates the diagonal
+// size 16 P in LDS, entry (r, c) of a tile at 16 r + (c xor r), so that rows and
+// columns are both read without bank conflicts.  Tile row p: wave 0 eliminates the diagonal
 // tile in registers (lb_tile, ldl_blk.h) and leaves E_p^T in its place; the
 // waves form W_J = E_p T_pJ; then T_IJ -= W_I^T D_p^{-1} W_J on FP64 MFMA, wave
 // 0 taking the next diagonal tile and going on to eliminate it while the
-// others update the rest.  All operands are read as rows of 16 consecutive
-// doubles, the layout the MFMA results are written in, so nothing is
-// transposed.  What bounds it is the chain of eliminations, 1.4 us per tile
+// others update the rest.  All operands are read as rows, the layout the MFMA
+// results are written in, so nothing is transposed; only the backward pass
+// reads columns.  What bounds it is the chain of eliminations, 1.4 us per tile
 // row with its two barriers; the products fit beside it.
 #pragma once
 
@@ -21,33 +22,69 @@ namespace rorbk {
 constexpr int WT = 256;                                    // doubles of a tile
 constexpr int WL_MAXP = (MAXB + 15) / 16;                  // 11: blocks of 161 rows
 constexpr int wl_tiles(int P) { return P * (P + 1) / 2; }
+__device__ __forceinline__ int wl_at(int r, int c) { return r * 16 + (c ^ r); }
 __device__ __forceinline__ int wl_tile(int P, int p, int J) {
     return (p * P - p * (p - 1) / 2 + J - p) * WT;
 }
 
-// Entry f of the packed lower triangle (value g) into the tiles: (j, i) of the
-// upper triangle, both halves of a diagonal tile; lambda on the diagonal.
-__device__ __forceinline__ void wl_put(double *T, int P, int f, double g, double lambda) {
-    int i = (int)((__builtin_amdgcn_sqrtf(8.0f * (float)f + 1.0f) - 1.0f) * 0.5f);
-    i -= (i * (i + 1) / 2 > f) ? 1 : 0;
-    i += ((i + 1) * (i + 2) / 2 <= f) ? 1 : 0;
-    const int j = f - i * (i + 1) / 2;
-    double *t = T + wl_tile(P, j >> 4, i >> 4);
-    const double v = (i == j) ? g + lambda : g;
-    t[(j & 15) * 16 + (i & 15)] = v;
-    if ((j >> 4) == (i >> 4)) t[(i & 15) * 16 + (j & 15)] = v;
-}
-
-// The identity in rows K .. 16 P - 1, by the whole workgroup.
-__device__ __forceinline__ void wl_pad(double *T, int P, int K) {
-    const int pad = 16 * P - K;   // at most 16 rows: the last tile column
-    for (int e = threadIdx.x; e < pad * 16 * P; e += blockDim.x) {
-        const int i = K + e / (16 * P), j = e % (16 * P);
-        if (j > i) continue;
-        double *t = T + wl_tile(P, j >> 4, i >> 4);
-        const double v = (i == j) ? 1.0 : 0.0;
-        t[(j & 15) * 16 + (i & 15)] = v;
-        if ((j >> 4) == (i >> 4)) t[(i & 15) * 16 + (j & 15)] = v;
+// The packed lower triangle (the sum of nch chunks of K (K + 1) / 2 doubles, in
+// chunk order) into the tiles, lambda on the diagonal and the identity from
+// row K on, by NW waves: a wave a row, its columns over the lanes, so that an
+// entry costs a load and two or three address operations (the row from a
+// packed index takes a square root: 2 us for 128 rows).  (i, j), j <= i, goes to
+// (j, i) of the upper triangle, in a diagonal tile to both.
+template <int P, int NW>
+__device__ __forceinline__ void wl_load(double *T, const double *__restrict__ G, int nch, int K,
+                                        double lambda) {
+    constexpr int RW = (16 * P + NW - 1) / NW, JG = (16 * P + 63) / 64, RB = 4;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int KP = K * (K + 1) / 2;
+    int at[JG], jx[JG];   // of row j in tile row j / 16, tile column 0; j mod 16
+#pragma unroll
+    for (int g = 0; g < JG; ++g) {
+        const int j = lane + 64 * g, t = j >> 4;
+        at[g] = (t * P - t * (t - 1) / 2 - t) * WT + (j & 15) * 16;
+        jx[g] = j & 15;
+    }
+#pragma unroll 1
+    for (int r0 = 0; r0 < RW; r0 += RB) {
+        double v[RB][JG];
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int g = 0; g < JG; ++g) v[r][g] = 0.0;
+        for (int c = 0; c < nch; ++c) {
+            double w[RB][JG];
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                const int i = wv + NW * (r0 + r), ii = i < K ? i : K - 1;   // scalar
+                const double *gi = G + (int64_t)c * KP + ii * (ii + 1) / 2;
+#pragma unroll
+                for (int g = 0; g < JG; ++g) w[r][g] = gi[lane + 64 * g < ii ? lane + 64 * g : ii];
+            }
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int g = 0; g < JG; ++g) v[r][g] += w[r][g];
+        }
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int i = wv + NW * (r0 + r);
+            if (i < 16 * P) {   // scalar
+#pragma unroll
+                for (int g = 0; g < JG; ++g) {
+                    const int j = lane + 64 * g;
+                    if (j <= i) {
+                        const double x = (i < K) ? ((i == j) ? v[r][g] + lambda : v[r][g])
+                                                 : ((i == j) ? 1.0 : 0.0);
+                        T[at[g] + (i >> 4) * WT + ((i & 15) ^ jx[g])] = x;
+                        if ((j >> 4) == (i >> 4))
+                            T[wl_tile(P, j >> 4, j >> 4) + wl_at(i & 15, jx[g])] = x;
+                    }
+                }
+            }
+        }
     }
 }
 
@@ -60,7 +97,9 @@ template <int P, int NW, bool RHS>
 __device__ __forceinline__ bool wl_factor(double *T, double *rd, double *z) {
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int at = lk * 16 + li;   // + 64 q: entry (4 q + lk, li) of a tile
+    int at[4];   // entry (4 q + lk, li) of a tile
+#pragma unroll
+    for (int q = 0; q < 4; ++q) at[q] = wl_at(4 * q + lk, li);
     __syncthreads();
 #pragma unroll 1
     for (int p = 0; p < P; ++p) {
@@ -68,21 +107,21 @@ __device__ __forceinline__ bool wl_factor(double *T, double *rd, double *z) {
         if (wv == 0) {
             double a[16], e[4];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) a[j] = Tp[j * 16 + li];
+            for (int j = 0; j < 16; ++j) a[j] = Tp[wl_at(j, li)];
 #pragma unroll
             for (int q = 0; q < 4; ++q) e[q] = (li == 4 * q + lk) ? 1.0 : 0.0;
             double zz = RHS ? z[16 * p + li] : 0.0;
             lb_tile(std::make_integer_sequence<int, 16>{}, a, e, zz, rd + 16 * p, li);
             if (RHS && lk == 0) z[16 * p + li] = zz;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) Tp[64 * q + at] = e[q];
+            for (int q = 0; q < 4; ++q) Tp[at[q]] = e[q];
         }
         __syncthreads();
         if (p + 1 == P) break;   // uniform
         double e[4], r[4], u[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            e[q] = Tp[64 * q + at];
+            e[q] = Tp[at[q]];
             r[q] = rd[16 * p + 4 * q + lk];
             u[q] = RHS ? z[16 * p + 4 * q + lk] : 0.0;
         }
@@ -91,11 +130,11 @@ __device__ __forceinline__ bool wl_factor(double *T, double *rd, double *z) {
             dvec4 w = {0.0, 0.0, 0.0, 0.0};
             double b[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) b[q] = t[64 * q + at];
+            for (int q = 0; q < 4; ++q) b[q] = t[at[q]];
 #pragma unroll
             for (int q = 0; q < 4; ++q) w = __builtin_amdgcn_mfma_f64_16x16x4f64(e[q], b[q], w, 0, 0, 0);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) t[64 * q + at] = w[q];
+            for (int q = 0; q < 4; ++q) t[at[q]] = w[q];
             if (RHS) {
                 double s = 0.0;
 #pragma unroll
@@ -105,9 +144,14 @@ __device__ __forceinline__ bool wl_factor(double *T, double *rd, double *z) {
             }
         }
         __syncthreads();
-        // the next diagonal tile on wave 0, the others dealt to the rest
+        // the next diagonal tile on wave 0, the others dealt to the rest: with
+        // more than four waves to those of the other three SIMDs (wave w runs
+        // on SIMD w mod 4), whose MFMA does not hold up wave 0
         const int n = P - p - 1;
-        int I = 0, J = (wv == 0) ? 0 : wv;
+        constexpr bool APART = NW > 4;
+        constexpr int NR = APART ? NW - (NW + 3) / 4 : NW - 1;
+        if (APART && wv != 0 && (wv & 3) == 0) continue;
+        int I = 0, J = (wv == 0) ? 0 : (APART ? wv - (wv >> 2) : wv);
         while (true) {
             while (I < n && J >= n) { ++I; J -= n - I; }   // tile (I, J) in row order
             if (I >= n) break;
@@ -117,17 +161,17 @@ __device__ __forceinline__ bool wl_factor(double *T, double *rd, double *z) {
             dvec4 acc;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                av[q] = -wi[64 * q + at] * r[q];
-                bv[q] = wj[64 * q + at];
-                acc[q] = t[64 * q + at];
+                av[q] = -wi[at[q]] * r[q];
+                bv[q] = wj[at[q]];
+                acc[q] = t[at[q]];
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q], bv[q], acc, 0, 0, 0);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) t[64 * q + at] = acc[q];
+            for (int q = 0; q < 4; ++q) t[at[q]] = acc[q];
             if (wv == 0) break;
-            J += NW - 1;
+            J += NR;
         }
     }
     bool ok = true;
@@ -137,34 +181,51 @@ __device__ __forceinline__ bool wl_factor(double *T, double *rd, double *z) {
 }
 
 // y = L^{-T} D^{-1} z after wl_factor with RHS, into z: from the last tile row,
-// y_p = E_p^T w_p on wave 0, then w_I -= L_pI^T y_p for the rows above, a wave
-// each.  Ends with a barrier.
+// y_p = E_p^T w_p on wave 0, then w_I -= L_pI^T y_p for the rows above, wave 0
+// taking the row that it needs next (so that one barrier a tile row is
+// enough), the other waves the rest.  Ends with a barrier.
 template <int P, int NW>
 __device__ __forceinline__ void wl_back(const double *T, const double *rd, double *z) {
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // sum over k of tile entry (li, k) and v_k, k = 4 q + lk, in every 16-lane row
+    auto row_dot = [&](const double (&t)[4], const double *v) -> double {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s = __builtin_fma(t[q], v[4 * q + lk], s);
+        return lb_rowsum(s);
+    };
+    auto row_load = [&](const double *tile, double (&t)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t[q] = tile[wl_at(li, 4 * q + lk)];
+    };
     for (int i = threadIdx.x; i < 16 * P; i += blockDim.x) z[i] *= rd[i];
+    __syncthreads();
+    double e[4], w[4];
+    if (wv == 0) row_load(T + wl_tile(P, P - 1, P - 1), e);
 #pragma unroll 1
     for (int p = P - 1; p >= 0; --p) {
-        double l[16];
         if (wv == 0) {
-            const double *E = T + wl_tile(P, p, p) + li * 16;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) l[j] = E[j];
-        }
-        __syncthreads();
-        if (wv == 0) {
-            const double y = lb_dot(0.0, l, z[16 * p + li]);
+            if (p > 0) row_load(T + wl_tile(P, p - 1, p), w);
+            const double y = row_dot(e, z + 16 * p);
             if (lk == 0) z[16 * p + li] = y;
+            if (p > 0) row_load(T + wl_tile(P, p - 1, p - 1), e);
         }
         __syncthreads();
-        for (int I = wv; I < p; I += NW) {
-            const double *w = T + wl_tile(P, I, p) + li * 16 + lk;
-            double s = 0.0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) s = __builtin_fma(w[4 * q], z[16 * p + 4 * q + lk], s);
-            s = lb_rowsum(s);
-            if (lk == 0) z[16 * I + li] = __builtin_fma(-rd[16 * I + li], s, z[16 * I + li]);
+        if (wv == 0) {
+            if (p > 0) {
+                const int i = 16 * (p - 1) + li;
+                const double s = row_dot(w, z + 16 * p);
+                if (lk == 0) z[i] = __builtin_fma(-rd[i], s, z[i]);
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else {
+            for (int I = wv - 1; I < p - 1; I += NW - 1) {
+                double t[4];
+                row_load(T + wl_tile(P, I, p), t);
+                const double s = row_dot(t, z + 16 * p);
+                if (lk == 0) z[16 * I + li] = __builtin_fma(-rd[16 * I + li], s, z[16 * I + li]);
+            }
         }
     }
     __syncthreads();
@@ -181,16 +242,18 @@ __device__ __forceinline__ void wl_inverse(double *T, const double *rd, int K,
     static_assert(NW >= P, "a wave per tile column");
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int at = lk * 16 + li;
+    int at[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) at[q] = wl_at(4 * q + lk, li);
     dvec4 X[P];
     if (wv < P) {
         const int J = wv;
 #pragma unroll
         for (int I = 0; I < P; ++I) {
             if (I == J) {
-                const double *E = T + wl_tile(P, J, J) + li * 16 + lk;
+                const double *E = T + wl_tile(P, J, J);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) X[I][r] = E[4 * r];
+                for (int r = 0; r < 4; ++r) X[I][r] = E[wl_at(li, 4 * r + lk)];
             } else if (I > J) {
                 dvec4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -200,13 +263,13 @@ __device__ __forceinline__ void wl_inverse(double *T, const double *rd, int K,
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
                             acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                                -w[64 * q + at] * rd[16 * k + 4 * q + lk], X[k][q], acc, 0, 0, 0);
+                                -w[at[q]] * rd[16 * k + 4 * q + lk], X[k][q], acc, 0, 0, 0);
                     }
                 const double *E = T + wl_tile(P, I, I);
                 X[I] = dvec4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    X[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(E[64 * q + at], acc[q], X[I], 0, 0, 0);
+                    X[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(E[at[q]], acc[q], X[I], 0, 0, 0);
             }
         }
     }
@@ -218,7 +281,7 @@ __device__ __forceinline__ void wl_inverse(double *T, const double *rd, int K,
             if (I >= J) {
                 double *t = T + wl_tile(P, J, I);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) t[64 * r + at] = X[I][r];
+                for (int r = 0; r < 4; ++r) t[at[r]] = X[I][r];
             }
     }
     __syncthreads();
@@ -231,8 +294,8 @@ __device__ __forceinline__ void wl_inverse(double *T, const double *rd, int K,
             const double *xi = T + wl_tile(P, I, k), *xj = T + wl_tile(P, J, k);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[64 * q + at] * rd[16 * k + 4 * q + lk],
-                                                           xj[64 * q + at], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[at[q]] * rd[16 * k + 4 * q + lk],
+                                                           xj[at[q]], acc, 0, 0, 0);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
