@@ -83,9 +83,22 @@ hipError_t launch_copy_tau(const int32_t *src, int32_t *dst, int64_t count, hipS
 // ||v||^2 in a fixed order: one workgroup, thread t summing entries t,
 // t + 1024, ... in order (each load instruction reads consecutive entries,
 // eight in flight per thread), then the workgroup sum.
+// With c it also starts the control block of a solve on that right-hand side
+// (stop threshold tol ||v||), which saves the launch of k_init_ctrl.
+__device__ __forceinline__ void ctrl_start(Ctrl *c, double tol, double bnorm2) {
+    c->done = 0;
+    c->status = 0;
+    c->conv_it = -1;
+    c->bnorm2 = bnorm2;
+    c->thr = tol * sqrt(bnorm2);
+    c->rnorm2 = 0.0;
+    c->last_it = -1;
+}
+
 template <typename V>
 __global__ __launch_bounds__(1024) void k_norm2(const V *__restrict__ v, int64_t len,
-                                                double *__restrict__ out) {
+                                                double *__restrict__ out, Ctrl *__restrict__ c,
+                                                double tol) {
     __shared__ double sh[16];
     constexpr int U = 8;
     const int64_t st = blockDim.x;
@@ -103,16 +116,20 @@ __global__ __launch_bounds__(1024) void k_norm2(const V *__restrict__ v, int64_t
         s = __builtin_fma(t, t, s);
     }
     s = block_sum(s, sh);
-    if (threadIdx.x == 0) *out = s;
+    if (threadIdx.x == 0) {
+        *out = s;
+        if (c) ctrl_start(c, tol, s);
+    }
 }
 
-hipError_t launch_norm2(const void *v, int vec, int64_t len, double *red, double *out,
+hipError_t launch_norm2(const void *v, int vec, int64_t len, double *out, Ctrl *c, double tol,
                         hipStream_t s) {
-    (void)red;
     if (vec == VEC_F64)
-        hipLaunchKernelGGL(k_norm2<double>, dim3(1), dim3(1024), 0, s, (const double *)v, len, out);
+        hipLaunchKernelGGL(k_norm2<double>, dim3(1), dim3(1024), 0, s, (const double *)v, len, out,
+                           c, tol);
     else
-        hipLaunchKernelGGL(k_norm2<float>, dim3(1), dim3(1024), 0, s, (const float *)v, len, out);
+        hipLaunchKernelGGL(k_norm2<float>, dim3(1), dim3(1024), 0, s, (const float *)v, len, out, c,
+                           tol);
     return hipGetLastError();
 }
 
@@ -383,7 +400,7 @@ __device__ __forceinline__ void select_final(const uint64_t *__restrict__ ckey, 
                              const V *__restrict__ r, Ctrl *__restrict__ ctrl, int stop_test,
                              int do_topk, int64_t it, double *rec_rrn, int32_t *rec_I,
                              const int32_t *replay_I, int32_t *I_out, double *rI_out,
-                             int32_t *ids, double *s_cn) {
+                             int32_t *ids, double *s_cn, Ctrl *mirror) {
     __shared__ int s_stop;
     __shared__ uint64_t fk[MAXK];
     __shared__ int32_t fi[MAXK];
@@ -434,6 +451,13 @@ __device__ __forceinline__ void select_final(const uint64_t *__restrict__ ckey, 
             ctrl->conv_it = it;
         }
         s_stop = stop;
+        if (mirror) {   // pinned host memory: no copy after the kernel
+            mirror->done = stop;
+            mirror->status = ctrl->status;
+            mirror->bnorm2 = bn2;
+            mirror->rnorm2 = rn2;
+            __threadfence_system();
+        }
     }
     __syncthreads();
     if (s_stop || !I_out) return;
@@ -460,7 +484,7 @@ __global__ __launch_bounds__(SEL_T) void k_select_merge(
     __shared__ double s_cn[SEL_NCN];
     if (final_level) {
         select_final<V>(ckey, cidx, nlists, K, cn, ncn, r, ctrl, stop_test, do_topk, it, rec_rrn,
-                        rec_I, replay_I, I_out, rI_out, ids, s_cn);
+                        rec_I, replay_I, I_out, rI_out, ids, s_cn, nullptr);
         return;
     }
     const int l0 = blockIdx.x * lists_per_group;
@@ -479,6 +503,7 @@ struct SelFinal {
     int ncn;
     Ctrl *ctrl;
     int stop_test;
+    Ctrl *mirror;
     int64_t it;
     double *rec_rrn;
     int32_t *rec_I;
@@ -660,7 +685,7 @@ __device__ __forceinline__ void select_chunk(
     select_final<V>(ckey, cidx, fin.nlists, K, fin.cn, fin.ncn, r, fin.ctrl, fin.stop_test,
                     do_topk, fin.it, fin.rec_rrn, fin.rec_I, fin.replay_I, fin.I_out, fin.rI_out,
                     reinterpret_cast<int32_t *>(sel_lds),
-                    reinterpret_cast<double *>(sel_lds + MAXK / 2));
+                    reinterpret_cast<double *>(sel_lds + MAXK / 2), fin.mirror);
 }
 
 template <typename V>
@@ -720,6 +745,7 @@ hipError_t launch_select(const rorbk_handle_s *h, const SelectArgs &a, hipStream
             fin.cn = h->d_cn;                                                                   \
             fin.ncn = L.nch_s;                                                                  \
             fin.ctrl = h->d_ctrl;                                                               \
+            fin.mirror = a.mirror;                                                              \
             fin.stop_test = a.stop_test;                                                        \
             fin.it = a.it;                                                                      \
             fin.rec_rrn = a.record_rrn ? a.rec_rrn : nullptr;                                   \
@@ -955,27 +981,36 @@ __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
     const int K = blk_rows(t, q, rem);
     wl_load<P, NW>(T, Gs + t * kpmax, 1, K, lambda);
     if (!wl_factor<P, NW, false>(T, rd, nullptr)) {
-        if (threadIdx.x == 0) *fail = 1;
+        if (threadIdx.x == 0) *fail = RORBK_ERR_NOT_SPD;
         return;
     }
     wl_inverse<P, NW>(T, rd, K, H + blk_hoff(t, q, rem));
 }
 
+// k matrices of q or q + 1 (the first rem) rows, bmax at most.
 template <int P>
-static void block_inverse_p(const rorbk_handle_s *h, const double *Gs, int64_t kp, int32_t *d_fail,
+static void block_inverse_p(const double *Gs, int64_t kp, int64_t k, int64_t bmax, int64_t q,
+                            int64_t rem, double lambda, double *H, int32_t *d_fail,
                             hipStream_t s) {
-    const Layout &L = h->L;
-    if ((L.bmax + 15) / 16 == P)
-        hipLaunchKernelGGL(k_block_inverse<P>, dim3((unsigned)L.k), dim3(64 * bi_waves<P>()), 0, s,
-                           Gs, kp, L.q, L.rem, h->lambda, h->d_H, d_fail);
+    if ((bmax + 15) / 16 == P)
+        hipLaunchKernelGGL(k_block_inverse<P>, dim3((unsigned)k), dim3(64 * bi_waves<P>()), 0, s,
+                           Gs, kp, q, rem, lambda, H, d_fail);
     else if constexpr (P < WL_MAXP)
-        block_inverse_p<P + 1>(h, Gs, kp, d_fail, s);
+        block_inverse_p<P + 1>(Gs, kp, k, bmax, q, rem, lambda, H, d_fail, s);
 }
 
 hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const double *Gs, int64_t kp,
                                             int32_t *d_fail, hipStream_t s) {
-    if (h->L.bmax > MAXB) return launch_big_block_inverses(h, Gs, kp, d_fail, s);
-    block_inverse_p<1>(h, Gs, kp, d_fail, s);
+    const Layout &L = h->L;
+    if (L.bmax > MAXB) return launch_big_block_inverses(h, Gs, kp, d_fail, s);
+    block_inverse_p<1>(Gs, kp, L.k, L.bmax, L.q, L.rem, h->lambda, h->d_H, d_fail, s);
+    return hipGetLastError();
+}
+
+// (G_t + lambda I)^{-1} of `sets` packed K x K Grams, K <= MAXB, at H + t K^2.
+hipError_t launch_inverse_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *H,
+                               int32_t *d_fail, hipStream_t s) {
+    block_inverse_p<1>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->lambda, H, d_fail, s);
     return hipGetLastError();
 }
 
@@ -1142,13 +1177,7 @@ __global__ void k_refine_ctrl(Ctrl *c, double tol, double eta, const double *__r
 }
 
 __global__ void k_init_ctrl(Ctrl *c, double tol, const double *__restrict__ bnorm2) {
-    c->done = 0;
-    c->status = 0;
-    c->conv_it = -1;
-    c->bnorm2 = *bnorm2;
-    c->thr = tol * sqrt(*bnorm2);
-    c->rnorm2 = 0.0;
-    c->last_it = -1;
+    ctrl_start(c, tol, *bnorm2);
 }
 
 hipError_t launch_init_ctrl(Ctrl *c, double tol, const double *bnorm2, hipStream_t s) {

@@ -192,6 +192,8 @@ __global__ __launch_bounds__(256) void k_csr_gram(const int64_t *__restrict__ ro
                                                   const Ctrl *__restrict__ ctrl) {
     if (ctrl && ctrl->done) return;
     const int64_t KP = (int64_t)K * (K + 1) / 2;
+    idx += (int64_t)blockIdx.y * K;   // grid y: row sets
+    G += blockIdx.y * KP;
     const int64_t f0 = (int64_t)blockIdx.x * 256;
     const int64_t f1 = (f0 + 256 < KP) ? f0 + 256 : KP;
     sparse_gram<T>(rowptr, colidx, val, idx, 0, K, f0, f1, G);
@@ -273,6 +275,7 @@ struct CsrStepP {
     void *x;
     void *gb;
     const double *ygiven;
+    const double *Hsel;    // stored inverse of a gathered row set (NULL: the block's)
     RowSel nxt;
     double *Pout;
     const Ctrl *ctrl;
@@ -483,7 +486,8 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
         int hi = tid / CSR_TPR;
         double hv[CSR_HU];
         auto load_row = [&]() {
-            const double *ph = p.H + blk_hoff(tc, p.q, p.rem) + (int64_t)qd * cnt + (hi < cnt ? hi : 0);
+            const double *ph = (p.Hsel ? p.Hsel : p.H + blk_hoff(tc, p.q, p.rem)) +
+                               (int64_t)qd * cnt + (hi < cnt ? hi : 0);
             const int64_t st = (int64_t)CSR_TPR * cnt;
 #pragma unroll
             for (int u0 = 0; u0 < CSR_HU; u0 += CSR_HG)
@@ -754,6 +758,7 @@ hipError_t launch_step_csr(const rorbk_handle_s *h, const StepArgs &a, hipStream
     p.x = a.x;
     p.gb = a.gb;
     p.ygiven = a.ygiven;
+    p.Hsel = a.Hsel;
     p.nxt = a.nxt;
     p.Pout = a.Pout;
     p.ctrl = h->d_ctrl;
@@ -768,14 +773,14 @@ hipError_t launch_step_csr(const rorbk_handle_s *h, const StepArgs &a, hipStream
 }
 
 hipError_t launch_gram_csr(const rorbk_handle_s *h, const void *vals, int dt, const int32_t *idx,
-                           int K, double *G, hipStream_t s) {
+                           int K, int sets, double *G, hipStream_t s) {
     const int64_t KP = (int64_t)K * (K + 1) / 2;
-    const unsigned grid = (unsigned)((KP + 255) / 256);
+    const dim3 grid((unsigned)((KP + 255) / 256), (unsigned)sets);
     if (dt == RORBK_F64)
-        hipLaunchKernelGGL(k_csr_gram<double>, dim3(grid), dim3(256), 0, s, h->rowptr, h->colidx,
+        hipLaunchKernelGGL(k_csr_gram<double>, grid, dim3(256), 0, s, h->rowptr, h->colidx,
                            (const double *)vals, idx, K, G, (const Ctrl *)h->d_ctrl);
     else
-        hipLaunchKernelGGL(k_csr_gram<float>, dim3(grid), dim3(256), 0, s, h->rowptr, h->colidx,
+        hipLaunchKernelGGL(k_csr_gram<float>, grid, dim3(256), 0, s, h->rowptr, h->colidx,
                            (const float *)vals, idx, K, G, (const Ctrl *)h->d_ctrl);
     return hipGetLastError();
 }

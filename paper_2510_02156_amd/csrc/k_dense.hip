@@ -33,6 +33,7 @@ struct StepP {
     const void *b;
     void *x;
     void *gb;
+    const double *Hsel;    // stored inverse of a gathered row set (NULL: the block's)
     const double *ygiven;
     RowSel nxt;
     double *Pout;
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(STEP_T) void k_step_dense(StepP p) {
     for (int c = tid; c < wcols; c += NT) s_x[c] = x[c0 + c];
 
     if (p.ymode == 0) {
-        const double *__restrict__ H = p.H + blk_hoff(tc, p.q, p.rem);
+        const double *__restrict__ H = p.Hsel ? p.Hsel : p.H + blk_hoff(tc, p.q, p.rem);
         // prefetch the first HP stored-inverse terms of row tid / TPR
         constexpr int HP = (64 / TPR < 16) ? 64 / TPR : 16;
         double hpre[HP];
@@ -295,6 +296,9 @@ __global__ __launch_bounds__(256) void k_gram_mfma(const T *__restrict__ A, int6
                                                    int64_t wg, double *__restrict__ Gpart,
                                                    const Ctrl *__restrict__ ctrl) {
     if (ctrl && ctrl->done) return;
+    // grid z: row sets, K indices and gridDim.y packed chunks each
+    idx += (int64_t)blockIdx.z * K;
+    Gpart += (int64_t)blockIdx.z * gridDim.y * (K * (K + 1) / 2);
     constexpr int E = (sizeof(T) == 8) ? 4 : Tr<T>::VW;
     const int nt = (K + 15) / 16;
     int bi, bj;
@@ -368,6 +372,7 @@ static hipError_t step_typed(const rorbk_handle_s *h, const StepArgs &a, hipStre
     p.x = a.x;
     p.gb = a.gb;
     p.ygiven = a.ygiven;
+    p.Hsel = a.Hsel;
     p.nxt = a.nxt;
     p.Pout = a.Pout;
     p.wu = L.wu;
@@ -384,25 +389,38 @@ hipError_t launch_step_dense(const rorbk_handle_s *h, const StepArgs &a, hipStre
 
 template <typename T>
 static hipError_t gram_typed(const rorbk_handle_s *h, const void *A, int aligned,
-                             const int32_t *idx, int K, double *Gpart, hipStream_t s) {
+                             const int32_t *idx, int K, int sets, int nch, int64_t wg,
+                             double *Gpart, hipStream_t s) {
     const Layout &L = h->L;
     const int nt = (K + 15) / 16;
-    dim3 grid((unsigned)(nt * (nt + 1) / 2), (unsigned)L.nch_g);
+    dim3 grid((unsigned)(nt * (nt + 1) / 2), (unsigned)nch, (unsigned)sets);
     if (aligned)
         hipLaunchKernelGGL((k_gram_mfma<T, true>), grid, dim3(256), 0, s, (const T *)A, L.ld, L.n,
-                           idx, K, L.wg, Gpart, (const Ctrl *)h->d_ctrl);
+                           idx, K, wg, Gpart, (const Ctrl *)h->d_ctrl);
     else
         hipLaunchKernelGGL((k_gram_mfma<T, false>), grid, dim3(256), 0, s, (const T *)A, L.ld,
-                           L.n, idx, K, L.wg, Gpart, (const Ctrl *)h->d_ctrl);
+                           L.n, idx, K, wg, Gpart, (const Ctrl *)h->d_ctrl);
     return hipGetLastError();
+}
+
+// The Grams of `sets` row sets of K rows each, one packed chunk per set (the
+// sets fill the chip, so their columns are not split further).
+hipError_t launch_gram_sets_dense(const rorbk_handle_s *h, const void *A, int dt,
+                                  const int32_t *idx, int K, int sets, double *G, hipStream_t s) {
+    const int al = h->aligned;
+    const int64_t n = h->L.n;
+    if (dt == RORBK_F64) return gram_typed<double>(h, A, al, idx, K, sets, 1, n, G, s);
+    if (dt == RORBK_F32) return gram_typed<float>(h, A, al, idx, K, sets, 1, n, G, s);
+    return gram_typed<bf16_t>(h, A, al, idx, K, sets, 1, n, G, s);
 }
 
 hipError_t launch_gram_dense(const rorbk_handle_s *h, const void *A, int dt, const int32_t *idx,
                              int K, double *Gpart, hipStream_t s) {
     const int al = h->aligned;
-    if (dt == RORBK_F64) return gram_typed<double>(h, A, al, idx, K, Gpart, s);
-    if (dt == RORBK_F32) return gram_typed<float>(h, A, al, idx, K, Gpart, s);
-    return gram_typed<bf16_t>(h, A, al, idx, K, Gpart, s);
+    const Layout &L = h->L;
+    if (dt == RORBK_F64) return gram_typed<double>(h, A, al, idx, K, 1, L.nch_g, L.wg, Gpart, s);
+    if (dt == RORBK_F32) return gram_typed<float>(h, A, al, idx, K, 1, L.nch_g, L.wg, Gpart, s);
+    return gram_typed<bf16_t>(h, A, al, idx, K, 1, L.nch_g, L.wg, Gpart, s);
 }
 
 // ------------------------------------------------------------------ setup --

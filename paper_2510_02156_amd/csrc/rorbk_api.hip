@@ -247,6 +247,8 @@ void destroy_all(rorbk_handle_s *h) {
     dfree(h->d_r64);
     dfree(h->d_rep_tau);
     dfree(h->d_rep_I);
+    dfree(h->d_advG);
+    dfree(h->d_advH);
     free_solve_buffers(h);
     if (h->ev0) (void)hipEventDestroy(h->ev0);
     if (h->ev1) (void)hipEventDestroy(h->ev1);
@@ -272,7 +274,7 @@ hipError_t residual(const rorbk_handle_s *h, const void *A, int dt, int aligned,
 hipError_t gram(const rorbk_handle_s *h, const void *A, int dt, int aligned, const int32_t *idx,
                 int K, double *G) {
     (void)aligned;
-    if (h->L.format == RORBK_CSR) return launch_gram_csr(h, A, dt, idx, K, G, h->stream);
+    if (h->L.format == RORBK_CSR) return launch_gram_csr(h, A, dt, idx, K, 1, G, h->stream);
     if (K > RORBK_MAX_BLOCK_ROWS + 1) return launch_gram_big(h, A, dt, idx, K, G, h->stream);
     return launch_gram_dense(h, A, dt, idx, K, G, h->stream);
 }
@@ -807,7 +809,8 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
         h->d_dxp = p2;
     }
 #undef ALLOC
-    hipError_t e = hipHostMalloc((void **)&h->h_ctrl, 3 * sizeof(Ctrl), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void **)&h->h_ctrl, 3 * sizeof(Ctrl), hipHostMallocMapped);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&h->m_ctrl, h->h_ctrl, 0);
     if (e != hipSuccess) {
         destroy_all(h);
         delete h;
@@ -1011,9 +1014,7 @@ int ror_bk_residual(rorbk_handle h, const void *b, const void *x, void *r, doubl
     }
     if (vec == VEC_F32 && dt == RORBK_F64)
         return fail(RORBK_ERR_INVALID_ARG, "float vectors need F32 or BF16 storage");
-    HIPCHK(hipMemsetAsync(h->d_ctrl, 0, sizeof(Ctrl), h->stream));
-    HIPCHK(launch_norm2(b, vec, L.m, h->d_red, h->d_red, h->stream));
-    HIPCHK(launch_init_ctrl(h->d_ctrl, 0.0, h->d_red, h->stream));
+    HIPCHK(launch_norm2(b, vec, L.m, h->d_red, h->d_ctrl, 0.0, h->stream));
     HIPCHK(residual(h, A, dt, al, vec, x, h->d_axp));
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -1023,10 +1024,10 @@ int ror_bk_residual(rorbk_handle h, const void *b, const void *x, void *r, doubl
     sa.nseg = L.nseg;
     sa.r = r;
     sa.skip_topk = 1;
-    HIPCHK(launch_select(h, sa, h->stream));
-    if (block_norm2)
-        HIPCHK(hipMemcpyAsync(block_norm2, h->d_bn, 8 * L.k, hipMemcpyDeviceToDevice, h->stream));
-    HIPCHK(hipMemcpyAsync(h->h_ctrl, h->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, h->stream));
+    sa.mirror = h->m_ctrl;
+    rorbk_handle_s hh = *h;   // the block norms straight into the caller's buffer
+    if (block_norm2) hh.d_bn = block_norm2;
+    HIPCHK(launch_select(&hh, sa, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     const Ctrl &c = *h->h_ctrl;
     if (rrn_host) *rrn_host = c.bnorm2 > 0 ? std::sqrt(c.rnorm2 / c.bnorm2) : 0.0;
@@ -1082,7 +1083,7 @@ int ror_bk_fabgmres(rorbk_handle h, const double *b, double *x, uint64_t seed, d
     GCHK(launch_fill_zero(small, (int64_t)(sizeof(double) * nsmall), s));
     GCHK(launch_fill_zero(Z, (int64_t)(sizeof(double) * n * max_outer), s));
     // ||b|| and r0 = b - A x0, v_1 = r0 / beta
-    GCHK(launch_norm2(b, VEC_F64, m, h->d_red, h->d_red + 1, s));
+    GCHK(launch_norm2(b, VEC_F64, m, h->d_red + 1, nullptr, 0.0, s));
     GCHK(hipMemsetAsync(h->d_ctrl, 0, sizeof(Ctrl), s));
     GCHK(residual(h, h->A, RORBK_F64, h->aligned, VEC_F64, x, h->d_axp));
     GCHK(launch_gmres_start(b, h->d_axp, L.nseg, m, V, g, beta_d, s));
@@ -1099,8 +1100,7 @@ int ror_bk_fabgmres(rorbk_handle h, const double *b, double *x, uint64_t seed, d
             // z_k: ROR-BK on A z = v_k from zero, sampler counter from k * inner_iters
             int prc = prepare_tau(h, seed, k * inner_iters, inner_iters, false);
             if (prc) { cleanup(); return prc; }
-            GCHK(launch_norm2(vk, VEC_F64, m, h->d_red, h->d_red + 2, s));
-            GCHK(launch_init_ctrl(h->d_ctrl, eta, h->d_red + 2, s));
+            GCHK(launch_norm2(vk, VEC_F64, m, h->d_red + 2, h->d_ctrl, eta, s));
             RunOpts o;
             memset(&o, 0, sizeof(o));
             o.vec = VEC_F64;
@@ -1302,8 +1302,7 @@ int ror_bk_solve(rorbk_handle h, const void *b, void *x, uint64_t seed, double t
     CHK(ensure_solve_buffers(h, max_iters, record || ckpt, slots, vec));
     CHK(prepare_tau(h, seed, start_iter, max_iters, replay));
     // ||b|| and the stop threshold
-    HIPCHK(launch_norm2(b, vec, L.m, h->d_red, h->d_red + 1, s));
-    HIPCHK(launch_init_ctrl(h->d_ctrl, tol, h->d_red + 1, s));
+    HIPCHK(launch_norm2(b, vec, L.m, h->d_red + 1, h->d_ctrl, tol, s));
     hipEvent_t t0, t1;
     HIPCHK(hipEventCreate(&t0));
     HIPCHK(hipEventCreate(&t1));
@@ -1354,8 +1353,8 @@ int ror_bk_solve(rorbk_handle h, const void *b, void *x, uint64_t seed, double t
                 sa.nseg = L.nseg;
                 sa.r = h->d_r;
                 sa.skip_topk = 1;
+                sa.mirror = h->m_ctrl;
                 HIPCHK(launch_select(h, sa, s));
-                HIPCHK(hipMemcpyAsync(h->h_ctrl, h->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
                 HIPCHK(hipStreamSynchronize(s));
                 const Ctrl &cf = *h->h_ctrl;
                 if (cf.status) return fail(cf.status, "non-finite residual of the returned x");
@@ -1396,8 +1395,8 @@ int ror_bk_solve(rorbk_handle h, const void *b, void *x, uint64_t seed, double t
             sa.nseg = L.nseg;
             sa.r = h->d_r64;
             sa.skip_topk = 1;
+            sa.mirror = h->m_ctrl;
             HIPCHK(launch_select(h, sa, s));
-            HIPCHK(hipMemcpyAsync(&h->h_ctrl[0], h->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             if (h->profile) {
                 float ms = 0.f;
@@ -1469,6 +1468,41 @@ int ror_bk_solve(rorbk_handle h, const void *b, void *x, uint64_t seed, double t
 // A_S g of its rows, produced by the previous kernel.
 namespace {
 
+// The recorded greedy sets are known before the adjoint starts, so their
+// regularised Grams are inverted many at a time (as many workgroups as sets
+// instead of one, 15 us for the solve and 4 for the Gram of every step) and a
+// greedy step then takes its y from a stored inverse as a sampled one does.
+// Sets in one go: at most 64, in at most 64 MiB.
+int64_t adjoint_sets(const Layout &L, int64_t iters) {
+    const int64_t per = 8 * (L.K * L.K + L.K * (L.K + 1) / 2);
+    return std::max<int64_t>(1, std::min<int64_t>({64, iters, ((int64_t)64 << 20) / per}));
+}
+
+int adjoint_inverses(rorbk_handle_s *h, int64_t it0, int sets) {
+    const Layout &L = h->L;
+    const int K = (int)L.K;
+    if (h->adv_sets < sets) {
+        // (the larger buffers replace the old ones once the work on those is done)
+        HIPCHK(hipStreamSynchronize(h->stream));
+        dfree(h->d_advG);
+        dfree(h->d_advH);
+        h->adv_sets = 0;
+        CHK(dalloc(&h->d_advG, (size_t)sets * K * (K + 1) / 2));
+        CHK(dalloc(&h->d_advH, (size_t)sets * K * K + RORBK_CSR_PAD));
+        // the CSR step reads past the last inverse
+        HIPCHK(launch_fill_zero(h->d_advH + (size_t)sets * K * K, 8 * RORBK_CSR_PAD, h->stream));
+        h->adv_sets = sets;
+    }
+    const int32_t *idx = h->d_recI + it0 * K;
+    if (L.format == RORBK_CSR)
+        HIPCHK(launch_gram_csr(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
+    else
+        HIPCHK(launch_gram_sets_dense(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
+    // a set that is not positive definite leaves its code in the control block
+    HIPCHK(launch_inverse_sets(h, h->d_advG, K, sets, h->d_advH, &h->d_ctrl->status, h->stream));
+    return RORBK_OK;
+}
+
 int backward_range(rorbk_handle_s *h, int64_t a, int64_t bnd, bool last_conv_in_range,
                    void *g, void *gb, int vec, int *ping_io, bool first) {
     const Layout &L = h->L;
@@ -1518,14 +1552,26 @@ int backward_range(rorbk_handle_s *h, int64_t a, int64_t bnd, bool last_conv_in_
     sa.Pout = h->d_P[ping ^ 1];
     HIPCHK(step(h, sa));
     ping ^= 1;
+    const bool batched = !h->big && !h->col;
+    const int64_t batch = adjoint_sets(L, bnd - a);
+    int64_t blo = bnd;   // inverses of the greedy sets of iterations blo .. are at hand
     for (size_t i = 0; i < steps.size(); ++i) {
         const St &st = steps[i];
         sa.cur = st.r;
+        sa.Hsel = nullptr;
         if (h->col) {
             // column form: y = -A_S (A_S^T A_S + lambda I)^{-1} g, gb[S] -= y
             HIPCHK(launch_col_adjoint(h, st.r, vec, g, gb, h->d_bigr, s));
             sa.ymode = 3;
             sa.ygiven = h->d_bigr;
+        } else if (st.greedy && batched) {
+            if (st.it < blo) {
+                blo = std::max(a, st.it - batch + 1);
+                CHK(adjoint_inverses(h, blo, (int)(st.it - blo + 1)));
+            }
+            sa.ymode = 0;
+            sa.Pin = h->d_P[ping];
+            sa.Hsel = h->d_advH + (st.it - blo) * L.K * L.K;
         } else if (st.greedy) {
             HIPCHK(gram(h, h->A, L.dtype, h->aligned, st.r.idx, (int)L.K, h->d_G));
             HIPCHK(launch_chol_solve(h, h->d_G, (int)L.K, nullptr, h->d_P[ping], h->d_y, s));
@@ -1580,8 +1626,7 @@ int ror_bk_backward(rorbk_handle h, const void *grad_x, void *grad_b, void *grad
             // recompute the segment's greedy sets from its checkpoint
             hipError_t he = hipMemcpyAsync(xw, (char *)h->d_ckpt + (size_t)sg * L.n * vs, L.n * vs,
                                            hipMemcpyDeviceToDevice, s);
-            if (he == hipSuccess) he = launch_norm2(h->rec_b, vec, L.m, h->d_red, bn2, s);
-            if (he == hipSuccess) he = launch_init_ctrl(h->d_ctrl, 0.0, bn2, s);
+            if (he == hipSuccess) he = launch_norm2(h->rec_b, vec, L.m, bn2, h->d_ctrl, 0.0, s);
             if (he != hipSuccess) { rc = fail(RORBK_ERR_HIP, "checkpoint restore failed"); break; }
             // same threshold as the recorded solve
             Ctrl hc;
@@ -1791,8 +1836,7 @@ extern "C" int ror_bk_residual_noalloc(const rorbk_matrix *A, int64_t block_rows
     hipStream_t s = hh.stream;
     // the counter must start at zero (a fill kernel, not a memset node)
     HIPCHK(launch_fill_zero(hh.d_selcnt, 4, s));
-    HIPCHK(launch_norm2(b, vec, L.m, hh.d_red, hh.d_red, s));
-    HIPCHK(launch_init_ctrl(hh.d_ctrl, 0.0, hh.d_red, s));
+    HIPCHK(launch_norm2(b, vec, L.m, hh.d_red, hh.d_ctrl, 0.0, s));
     HIPCHK(residual(&hh, Am, dt, al, vec, x, hh.d_axp));
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));

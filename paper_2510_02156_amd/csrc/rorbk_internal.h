@@ -109,6 +109,9 @@ struct rorbk_handle_s {
     // per-solve workspaces (owned)
     rorbk::Ctrl *d_ctrl;
     rorbk::Ctrl *h_ctrl;      // pinned mirror
+    double *d_advG, *d_advH;  // adjoint: Grams and inverses of adv_sets greedy sets
+    int64_t adv_sets;
+    rorbk::Ctrl *m_ctrl;      // its device address
     uint32_t *d_selcnt;       // selection workgroups done (fused merge), 0 between launches
     double *d_ysum;           // sum of the rows of A (n), for the initial solution
     float *d_ysum32;          // the same in FP32 (allocated on first use)
@@ -195,8 +198,8 @@ hipError_t launch_partition(int64_t m, int64_t k, int64_t *off, int64_t *hoff,
 hipError_t launch_sample(uint64_t seed, int64_t j0, int64_t count,
                          const double *W, int64_t k, int32_t *tau, hipStream_t s);
 
-hipError_t launch_norm2(const void *v, int vec, int64_t len, double *red,
-                        double *out, hipStream_t s);
+hipError_t launch_norm2(const void *v, int vec, int64_t len, double *out, Ctrl *c, double tol,
+                        hipStream_t s);
 
 hipError_t launch_copy_tau(const int32_t *src, int32_t *dst, int64_t count,
                            hipStream_t s);
@@ -237,6 +240,7 @@ struct StepArgs {
                           // x += A_S^T y in either form (column-form adjoint)
     const double *Pin;    // partials of the current step
     const double *ygiven;
+    const double *Hsel;   // ymode 0 on a gathered row set: its stored inverse
     RowSel nxt;           // rows whose partial products are produced
     double *Pout;
 };
@@ -259,6 +263,8 @@ struct SelectArgs {
     double *rI_out;
     int stop_test;        // 1: compare with thr2 and set done
     int skip_topk;        // 1: only norms (refinement outer residual)
+    Ctrl *mirror;         // skip_topk: NULL, or pinned host memory that takes done,
+                          // status and the two norms (not written if done was set before)
     // spare workgroups (may be unset): the cross-Grams of the blocks drawn at
     // tau[xg_ti .. xg_ti+2] into xg_out, computed alongside the selection
     double *xg_out;
@@ -359,12 +365,16 @@ static_assert(96 + 3 * RORBK_FWD_MAX_BLOCK <= CKST_DOUBLES, "a checkpoint's chai
 // in one launch (a.I: greedy rows, a.tau_index / a.xg: iteration it + 1)
 hipError_t launch_fwd_chain(const rorbk_handle_s *h, const FwdArgs &a, const void *r,
                             double *ckst, hipStream_t s);
+hipError_t launch_gram_sets_dense(const rorbk_handle_s *h, const void *A, int dt,
+                                  const int32_t *idx, int K, int sets, double *G, hipStream_t s);
+hipError_t launch_inverse_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *H,
+                               int32_t *d_fail, hipStream_t s);
 hipError_t launch_gram_dense(const rorbk_handle_s *h, const void *A, int dt,
                              const int32_t *idx, int K, double *Gpart, hipStream_t s);
 hipError_t launch_step_csr(const rorbk_handle_s *h, const StepArgs &a, hipStream_t s);
 hipError_t launch_residual_csr(const rorbk_handle_s *h, const void *vals, int dt, int vec,
                                const void *x, double *axp, hipStream_t s);
-hipError_t launch_gram_csr(const rorbk_handle_s *h, const void *vals, int dt,
-                           const int32_t *idx, int K, double *Gpart, hipStream_t s);
+hipError_t launch_gram_csr(const rorbk_handle_s *h, const void *vals, int dt, const int32_t *idx,
+                           int K, int sets, double *G, hipStream_t s);
 
 }  // namespace rorbk
