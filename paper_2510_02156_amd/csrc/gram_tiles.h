@@ -58,8 +58,9 @@ __device__ __forceinline__ void gram64_accumulate(const T *const (&pa)[4], const
                         xb[u][s2][h] = same ? zu : *reinterpret_cast<const uvec4 *>(pb[s2] + cc);
                     } else {
                         // rows are valid even where va / vb are false
-                        xa[u][s2][h] = load_raw_sel<T, AL>(pa[s2], cc, wb, va[s2], pa[s2], wa);
-                        xb[u][s2][h] = load_raw_sel<T, AL>(pb[s2], cc, wb, !same && vb[s2], pb[s2], wa);
+                        xa[u][s2][h] = load_gram_sel<T, AL>(pa[s2], cc, wb, va[s2], pa[s2], wa);
+                        xb[u][s2][h] = load_gram_sel<T, AL>(pb[s2], cc, wb, !same && vb[s2], pb[s2],
+                                                               wa);
                     }
                 }
             }

@@ -811,8 +811,9 @@ __global__ __launch_bounds__(256) void k_gram32(const T *__restrict__ A, int64_t
                 const int64_t cc = col + h * VW;
 #pragma unroll
                 for (int s2 = 0; s2 < 2; ++s2) {
-                    xa[u][s2][h] = load_raw_sel<T, AL>(pa[s2], cc, wb, va[s2], pa[s2], wa);
-                    xb[u][s2][h] = load_raw_sel<T, AL>(pb[s2], cc, wb, !same && vb[s2], pb[s2], wa);
+                    xa[u][s2][h] = load_gram_sel<T, AL>(pa[s2], cc, wb, va[s2], pa[s2], wa);
+                    xb[u][s2][h] = load_gram_sel<T, AL>(pb[s2], cc, wb, !same && vb[s2], pb[s2],
+                                                               wa);
                 }
             }
         }

@@ -173,6 +173,30 @@ __device__ __forceinline__ uvec4 load_raw_sel(const T *__restrict__ row, int64_t
     return g ? w : z;
 }
 
+// load_raw_sel for the Gram kernels, whose lanes read pieces of 16 different
+// rows: FP64 rows of 8-byte alignment take two 8-byte loads there, as 16-byte
+// ones that start between two 16-byte words cost such a wave more (block Grams
+// of 300 x 2999: 610 us, 327 with the two; of 11 x 7591: 130 and 61; steps and
+// the residual, whose lanes read along a row, gain from the wide ones: 120-row
+// steps of 1501 columns 57 us with 8-byte loads, 41 with them).
+template <typename T, bool ALIGNED>
+__device__ __forceinline__ uvec4 load_gram_sel(const T *__restrict__ row, int64_t c, int64_t lim,
+                                               bool ok, const T *__restrict__ srow, int64_t sc) {
+    if constexpr (!ALIGNED && sizeof(T) == 8) {
+        const bool g = ok && c < lim;
+        const double *p = g ? row : srow;
+        const int64_t cc = g ? c : sc;
+        double v[2] = {p[cc], 0.0};
+        if (cc + 1 < lim) v[1] = p[cc + 1];
+        if (!g) v[0] = v[1] = 0.0;
+        uvec4 w;
+        __builtin_memcpy(&w, v, 16);
+        return w;
+    } else {
+        return load_raw_sel<T, ALIGNED>(row, c, lim, ok, srow, sc);
+    }
+}
+
 template <typename T, bool ALIGNED>
 __device__ __forceinline__ uvec4 load_raw_nt_sel(const T *__restrict__ row, int64_t c, int64_t lim,
                                                  bool ok, const T *__restrict__ srow, int64_t sc) {
@@ -225,8 +249,9 @@ __device__ __forceinline__ void mfma_gram_tile(const T *__restrict__ X, int64_t 
             const int64_t col = c + (int64_t)u * 4 * E + (int64_t)g * E;
 #pragma unroll
             for (int h = 0; h < NL; ++h) {
-                wa[u][h] = load_raw_sel<T, ALIGNED>(pa, col + h * VW, c1, ra >= 0, X, c0);
-                wb[u][h] = load_raw_sel<T, ALIGNED>(pb, col + h * VW, c1, !same && rb >= 0, X, c0);
+                wa[u][h] = load_gram_sel<T, ALIGNED>(pa, col + h * VW, c1, ra >= 0, X, c0);
+                wb[u][h] = load_gram_sel<T, ALIGNED>(pb, col + h * VW, c1, !same && rb >= 0, X,
+                                                           c0);
             }
         }
 #pragma unroll
