@@ -193,6 +193,14 @@ static hipError_t resid_typed(const rorbk_handle_s *h, const void *A, int aligne
     // more); fewer for short matrices
     constexpr int PER_CU = (SW == SEG && sizeof(T) >= 4) ? 16 : 2;
     int64_t groups = (L.m + 4 * ROWS - 1) / (4 * ROWS);
+    // few rows: one row per wave, so that more of the chip waits for them
+    // (residual call in us, several rows a wave against one: 2000 x 200 FP64
+    // 29.7 / 28.6, BF16 32.4 / 28.4, 3000 x 3000 FP64 44.4 / 41.6; past the line
+    // 400 x 40001 FP64 50 / 53, 20000 x 450 FP32 36.3 / 37.0, 9000 x 1500 BF16 39 / 53)
+    if constexpr (ROWS > 1) {
+        if (groups * L.nseg <= (PER_CU > 2 ? 3 : 1) * (int64_t)h->ncu)
+            return resid_typed<T, V, 1, SW, SH>(h, A, aligned, x, axp, side, s);
+    }
     int64_t cap = PER_CU * (int64_t)h->ncu / L.nseg;
     if (PER_CU > 2) {
         int64_t c3 = L.m / (4 * ROWS * 3);
