@@ -807,22 +807,17 @@ hipError_t launch_setup_proposal_csr(const rorbk_handle_s *h, const void *vals, 
 }
 
 hipError_t launch_block_inverses_csr(const rorbk_handle_s *h, const void *vals, int dt,
-                                     int32_t *d_fail, hipStream_t s) {
+                                     double *Gs, int32_t *d_fail, hipStream_t s) {
     const Layout &L = h->L;
     const int64_t kp = L.bmax * (L.bmax + 1) / 2;
-    double *Gs = nullptr;
-    hipError_t e = hipMallocAsync((void **)&Gs, sizeof(double) * (size_t)(kp * L.k), s);
-    if (e != hipSuccess) return e;
     if (dt == RORBK_F64)
         hipLaunchKernelGGL(k_csr_block_gram<double>, dim3((unsigned)L.k), dim3(256), 0, s,
                            h->rowptr, h->colidx, (const double *)vals, L.q, L.rem, kp, Gs);
     else
         hipLaunchKernelGGL(k_csr_block_gram<float>, dim3((unsigned)L.k), dim3(256), 0, s,
                            h->rowptr, h->colidx, (const float *)vals, L.q, L.rem, kp, Gs);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = launch_block_inverses_from_grams(h, Gs, kp, d_fail, s);
-    hipError_t e2 = hipFreeAsync(Gs, s);
-    return e != hipSuccess ? e : e2;
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_block_inverses_from_grams(h, Gs, kp, d_fail, s);
 }
 
 }  // namespace rorbk

@@ -744,12 +744,9 @@ __global__ __launch_bounds__(256) void k_block_gram64(const T *__restrict__ A, i
 }
 
 hipError_t launch_block_inverses_dense(const rorbk_handle_s *h, const void *A, int dt, int aligned,
-                                       int32_t *d_fail, hipStream_t s) {
+                                       double *Gs, int32_t *d_fail, hipStream_t s) {
     const Layout &L = h->L;
     const int64_t kp = L.bmax * (L.bmax + 1) / 2;
-    double *Gs = nullptr;
-    hipError_t e = hipMallocAsync((void **)&Gs, sizeof(double) * (size_t)(kp * L.k), s);
-    if (e != hipSuccess) return e;
     // 64 x 64 tiles once a block fills most of one (48 rows: the 16 x 16 form
     // has as many products then, each a dependent MFMA chain of its own)
     const bool t64 = L.bmax >= 48;
@@ -774,10 +771,8 @@ hipError_t launch_block_inverses_dense(const rorbk_handle_s *h, const void *A, i
     else if (dt == RORBK_F32) RORBK_BG(float);
     else RORBK_BG(bf16_t);
 #undef RORBK_BG
-    e = hipGetLastError();
-    if (e == hipSuccess) e = launch_block_inverses_from_grams(h, Gs, kp, d_fail, s);
-    hipError_t e2 = hipFreeAsync(Gs, s);
-    return e != hipSuccess ? e : e2;
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_block_inverses_from_grams(h, Gs, kp, d_fail, s);
 }
 
 }  // namespace rorbk

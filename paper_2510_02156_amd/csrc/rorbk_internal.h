@@ -109,9 +109,12 @@ struct rorbk_handle_s {
     // per-solve workspaces (owned)
     rorbk::Ctrl *d_ctrl;
     rorbk::Ctrl *h_ctrl;      // pinned mirror
+    rorbk::Ctrl *m_ctrl;      // its device address
+    char *d_arena;            // the buffers made with the handle: one block of
+    size_t arena_bytes;       // device memory,
+    int32_t arena_dev;        // its device
     double *d_advG, *d_advH;  // adjoint: Grams and inverses of adv_sets greedy sets
     int64_t adv_sets;
-    rorbk::Ctrl *m_ctrl;      // its device address
     uint32_t *d_selcnt;       // selection workgroups done (fused merge), 0 between launches
     double *d_ysum;           // sum of the rows of A (n), for the initial solution
     float *d_ysum32;          // the same in FP32 (allocated on first use)
@@ -209,7 +212,7 @@ hipError_t launch_setup_proposal_dense(const rorbk_handle_s *h, const void *A,
                                        int dt, int aligned, double *scratch,
                                        hipStream_t s);
 hipError_t launch_block_inverses_dense(const rorbk_handle_s *h, const void *A,
-                                       int dt, int aligned, int32_t *d_fail,
+                                       int dt, int aligned, double *Gs, int32_t *d_fail,
                                        hipStream_t s);
 // doubles of device scratch the proposal setup needs (centroids, norms, row
 // sums, centroid Gram parts)
@@ -224,7 +227,7 @@ hipError_t launch_csr_check(const rorbk_handle_s *h, int32_t *bad, hipStream_t s
 hipError_t launch_setup_proposal_csr(const rorbk_handle_s *h, const void *vals, int dt,
                                      double *scratch, hipStream_t s);
 hipError_t launch_block_inverses_csr(const rorbk_handle_s *h, const void *vals, int dt,
-                                     int32_t *d_fail, hipStream_t s);
+                                     double *Gs, int32_t *d_fail, hipStream_t s);
 // iteration kernels (dense or CSR chosen from the handle's format)
 struct StepArgs {
     const void *A;        // matrix values (dtype dt)
