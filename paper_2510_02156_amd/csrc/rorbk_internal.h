@@ -112,6 +112,7 @@ struct rorbk_handle_s {
     rorbk::Ctrl *m_ctrl;      // its device address
     char *d_arena;            // the buffers made with the handle: one block of
     size_t arena_bytes;       // device memory,
+    size_t arena_used;        // the rest for buffers made later,
     int32_t arena_dev;        // its device
     double *d_advG, *d_advH;  // adjoint: Grams and inverses of adv_sets greedy sets
     int64_t adv_sets;
