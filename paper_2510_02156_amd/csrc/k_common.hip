@@ -925,7 +925,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 // 65 to 161 rows: the solve in one workgroup's LDS (ldl_wg.h), the Gram chunks
 // summed in order and put straight into the tiles.  K = 128 with one chunk:
-// 17 us, where the blocked factorisation in global memory (an unpacking
+// 24 us, where the blocked factorisation in global memory (an unpacking
 // launch, one per 32 columns and a backward solve) took 59.
 constexpr int CW_NW = 16;
 template <int P>
@@ -966,8 +966,8 @@ __global__ __launch_bounds__(64 * CW_NW) void k_chol_wg(
 // rows from their packed Grams, a workgroup per block, all of it in LDS: bound
 // by the factorisation's chain of tile eliminations, which the blocks sharing
 // a CU overlap.  781 blocks of 64 rows: 532 us on the kernel that eliminated
-// column by column and formed L^{-1} with four threads a column; 781 of 128
-// rows: 7.2 ms with the inverse formed through global memory.
+// column by column and formed L^{-1} with four threads a column, 44 here; 781
+// of 128 rows: 7.2 ms with the inverse formed through global memory, 185 us here.
 template <int P>
 constexpr int bi_waves() { return P < 4 ? 4 : P; }
 template <int P>

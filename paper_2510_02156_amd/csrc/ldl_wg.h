@@ -11,7 +11,7 @@
 // 0 taking the next diagonal tile and going on to eliminate it while the
 // others update the rest.  All operands are read as rows, the layout the MFMA
 // results are written in, so nothing is transposed; only the backward pass
-// reads columns.  What bounds it is the chain of eliminations, 1.4 us per tile
+// reads columns.  What bounds it is the chain of eliminations, 1.9 us per tile
 // row with its two barriers; the products fit beside it.
 #pragma once
 
