@@ -973,7 +973,7 @@ constexpr int bi_waves() { return P < 4 ? 4 : P; }
 template <int P>
 __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
     const double *__restrict__ Gs, int64_t kpmax, int64_t q, int64_t rem, double lambda,
-    double *__restrict__ H, int32_t *__restrict__ fail) {
+    double *__restrict__ H, int32_t *__restrict__ fail, Ctrl *__restrict__ ctrl) {
     constexpr int NW = bi_waves<P>();
     __shared__ __align__(16) double T[wl_tiles(P) * WT];
     __shared__ double rd[16 * P];
@@ -981,7 +981,13 @@ __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
     const int K = blk_rows(t, q, rem);
     wl_load<P, NW>(T, Gs + t * kpmax, 1, K, lambda);
     if (!wl_factor<P, NW, false>(T, rd, nullptr)) {
-        if (threadIdx.x == 0) *fail = RORBK_ERR_NOT_SPD;
+        if (threadIdx.x == 0) {
+            if (fail) *fail = RORBK_ERR_NOT_SPD;
+            if (ctrl) {   // adjoint: the steps that follow return at once
+                ctrl->status = RORBK_ERR_NOT_SPD;
+                ctrl->done = 1;
+            }
+        }
         return;
     }
     wl_inverse<P, NW>(T, rd, K, H + blk_hoff(t, q, rem));
@@ -990,27 +996,29 @@ __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
 // k matrices of q or q + 1 (the first rem) rows, bmax at most.
 template <int P>
 static void block_inverse_p(const double *Gs, int64_t kp, int64_t k, int64_t bmax, int64_t q,
-                            int64_t rem, double lambda, double *H, int32_t *d_fail,
+                            int64_t rem, double lambda, double *H, int32_t *d_fail, Ctrl *ctrl,
                             hipStream_t s) {
     if ((bmax + 15) / 16 == P)
         hipLaunchKernelGGL(k_block_inverse<P>, dim3((unsigned)k), dim3(64 * bi_waves<P>()), 0, s,
-                           Gs, kp, q, rem, lambda, H, d_fail);
+                           Gs, kp, q, rem, lambda, H, d_fail, ctrl);
     else if constexpr (P < WL_MAXP)
-        block_inverse_p<P + 1>(Gs, kp, k, bmax, q, rem, lambda, H, d_fail, s);
+        block_inverse_p<P + 1>(Gs, kp, k, bmax, q, rem, lambda, H, d_fail, ctrl, s);
 }
 
 hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const double *Gs, int64_t kp,
                                             int32_t *d_fail, hipStream_t s) {
     const Layout &L = h->L;
     if (L.bmax > MAXB) return launch_big_block_inverses(h, Gs, kp, d_fail, s);
-    block_inverse_p<1>(Gs, kp, L.k, L.bmax, L.q, L.rem, h->lambda, h->d_H, d_fail, s);
+    block_inverse_p<1>(Gs, kp, L.k, L.bmax, L.q, L.rem, h->lambda, h->d_H, d_fail, nullptr, s);
     return hipGetLastError();
 }
 
 // (G_t + lambda I)^{-1} of `sets` packed K x K Grams, K <= MAXB, at H + t K^2.
+// One that is not positive definite ends the adjoint (status and done).
 hipError_t launch_inverse_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *H,
-                               int32_t *d_fail, hipStream_t s) {
-    block_inverse_p<1>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->lambda, H, d_fail, s);
+                               hipStream_t s) {
+    block_inverse_p<1>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->lambda, H, nullptr,
+                       h->d_ctrl, s);
     return hipGetLastError();
 }
 

@@ -899,14 +899,14 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     rc = ar.alloc(h);
     if (rc) { destroy_all(h); delete h; return rc; }
 #undef ALLOC
-    hipError_t e = hipHostMalloc((void **)&h->h_ctrl, 3 * sizeof(Ctrl), hipHostMallocMapped);
+    hipError_t e = hipHostMalloc((void **)&h->h_ctrl, 4 * sizeof(Ctrl), hipHostMallocMapped);
     if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&h->m_ctrl, h->h_ctrl, 0);
     if (e != hipSuccess) {
         destroy_all(h);
         delete h;
         return fail(RORBK_ERR_OOM, "pinned allocation failed: %s", hipGetErrorString(e));
     }
-    memset(h->h_ctrl, 0, 3 * sizeof(Ctrl));
+    memset(h->h_ctrl, 0, 4 * sizeof(Ctrl));
     if (hipMemsetAsync(h->d_selcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess ||
         (h->d_fwdcnt &&
          hipMemsetAsync(h->d_fwdcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess) ||
@@ -1581,8 +1581,7 @@ int adjoint_inverses(rorbk_handle_s *h, int64_t it0, int sets) {
         HIPCHK(launch_gram_csr(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
     else
         HIPCHK(launch_gram_sets_dense(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
-    // a set that is not positive definite leaves its code in the control block
-    HIPCHK(launch_inverse_sets(h, h->d_advG, K, sets, h->d_advH, &h->d_ctrl->status, h->stream));
+    HIPCHK(launch_inverse_sets(h, h->d_advG, K, sets, h->d_advH, h->stream));
     return RORBK_OK;
 }
 
@@ -1703,6 +1702,10 @@ int ror_bk_backward(rorbk_handle h, const void *grad_x, void *grad_b, void *grad
         char *xw = nullptr;
         CHK(dalloc(&xw, (size_t)(L.n * vs)));
         double *bn2 = h->d_red + 3;
+        // how each segment's adjoint ended, read once the next one's forward
+        // run (which starts the control block anew) has been waited for
+        const Ctrl *ended = h->h_ctrl + 3;
+        h->h_ctrl[3].status = RORBK_OK;
         int rc = RORBK_OK;
         for (int64_t sg = nseg - 1; sg >= 0 && rc == RORBK_OK; --sg) {
             const int64_t a = sg * c, e = std::min(iters, a + c);
@@ -1763,13 +1766,19 @@ int ror_bk_backward(rorbk_handle h, const void *grad_x, void *grad_b, void *grad
             int64_t ran = 0;
             bool stopped = false;
             rc = run_iterations(h, o, a, e, &ran, &stopped);
-            if (rc) break;
-            HIPCHK(hipMemsetAsync(h->d_ctrl, 0, sizeof(Ctrl), s));
-            rc = backward_range(h, a, e, conv && e == iters, grad_x0, grad_b, vec, &ping, sg == nseg - 1);
+            if (rc || ended->status) break;
+            he = hipMemsetAsync(h->d_ctrl, 0, sizeof(Ctrl), s);
+            if (he == hipSuccess)
+                rc = backward_range(h, a, e, conv && e == iters, grad_x0, grad_b, vec, &ping,
+                                    sg == nseg - 1);
+            if (he == hipSuccess && rc == RORBK_OK)
+                he = hipMemcpyAsync(h->h_ctrl + 3, h->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s);
+            if (he != hipSuccess) rc = fail(RORBK_ERR_HIP, "adjoint of a checkpoint segment failed");
         }
         (void)hipStreamSynchronize(s);
         dfree(xw);
         if (rc) return rc;
+        if (ended->status) return fail(ended->status, "backward failed (block Gram not SPD)");
     }
     HIPCHK(hipMemcpyAsync(h->h_ctrl, h->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));

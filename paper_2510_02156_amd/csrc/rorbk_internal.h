@@ -17,10 +17,12 @@ __host__ __device__ constexpr bool gram64_for(int32_t dtype, int64_t K) {
     return dtype == RORBK_F64 && K >= GRAM64_MIN_K;
 }
 
-// Device-resident control block.  Written only by the single-workgroup
-// selection and solve kernels; every iteration kernel reads `done` first and
-// returns at once when it is set (the stop test, Algorithm 1, ends the solve
-// before the greedy step).
+// Device-resident control block.  Started by the norm of the right-hand side;
+// the selection writes the norms and the stop test's result, and every kernel
+// that factors a block system sets `status` and `done` where a pivot is not
+// positive (of several workgroups any may, with the same values).  Every
+// iteration kernel reads `done` first and returns at once when it is set (the
+// stop test, Algorithm 1, ends the solve before the greedy step).
 struct Ctrl {
     int32_t done;        // 1 once converged or failed
     int32_t status;      // RORBK_OK, RORBK_ERR_NONFINITE or RORBK_ERR_NOT_SPD
@@ -108,7 +110,7 @@ struct rorbk_handle_s {
     double *d_H;              // stored block inverses
     // per-solve workspaces (owned)
     rorbk::Ctrl *d_ctrl;
-    rorbk::Ctrl *h_ctrl;      // pinned mirror
+    rorbk::Ctrl *h_ctrl;      // pinned: mirror, two poll slots, the adjoint's last segment
     rorbk::Ctrl *m_ctrl;      // its device address
     char *d_arena;            // the buffers made with the handle: one block of
     size_t arena_bytes;       // device memory,
@@ -372,7 +374,7 @@ hipError_t launch_fwd_chain(const rorbk_handle_s *h, const FwdArgs &a, const voi
 hipError_t launch_gram_sets_dense(const rorbk_handle_s *h, const void *A, int dt,
                                   const int32_t *idx, int K, int sets, double *G, hipStream_t s);
 hipError_t launch_inverse_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *H,
-                               int32_t *d_fail, hipStream_t s);
+                               hipStream_t s);
 hipError_t launch_gram_dense(const rorbk_handle_s *h, const void *A, int dt,
                              const int32_t *idx, int K, double *Gpart, hipStream_t s);
 hipError_t launch_step_csr(const rorbk_handle_s *h, const StepArgs &a, hipStream_t s);
