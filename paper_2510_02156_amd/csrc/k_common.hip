@@ -968,9 +968,10 @@ __global__ __launch_bounds__(64 * CW_NW) void k_chol_wg(
 // a CU overlap.  781 blocks of 64 rows: 532 us on the kernel that eliminated
 // column by column and formed L^{-1} with four threads a column, 44 here; 781
 // of 128 rows: 7.2 ms with the inverse formed through global memory, 185 us here.
+// FAC: the factored form instead, for the adjoint's greedy sets.
 template <int P>
 constexpr int bi_waves() { return P < 4 ? 4 : P; }
-template <int P>
+template <int P, bool FAC>
 __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
     const double *__restrict__ Gs, int64_t kpmax, int64_t q, int64_t rem, double lambda,
     double *__restrict__ H, int32_t *__restrict__ fail, Ctrl *__restrict__ ctrl) {
@@ -990,35 +991,38 @@ __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
         }
         return;
     }
-    wl_inverse<P, NW>(T, rd, K, H + blk_hoff(t, q, rem));
+    double *Ht = H + blk_hoff(t, q, rem);
+    if constexpr (FAC) wl_put_factor<P, NW>(T, rd, K, Ht);
+    else wl_inverse<P, NW>(T, rd, K, Ht);
 }
 
 // k matrices of q or q + 1 (the first rem) rows, bmax at most.
-template <int P>
+template <int P, bool FAC>
 static void block_inverse_p(const double *Gs, int64_t kp, int64_t k, int64_t bmax, int64_t q,
                             int64_t rem, double lambda, double *H, int32_t *d_fail, Ctrl *ctrl,
                             hipStream_t s) {
     if ((bmax + 15) / 16 == P)
-        hipLaunchKernelGGL(k_block_inverse<P>, dim3((unsigned)k), dim3(64 * bi_waves<P>()), 0, s,
+        hipLaunchKernelGGL((k_block_inverse<P, FAC>), dim3((unsigned)k), dim3(64 * bi_waves<P>()), 0, s,
                            Gs, kp, q, rem, lambda, H, d_fail, ctrl);
     else if constexpr (P < WL_MAXP)
-        block_inverse_p<P + 1>(Gs, kp, k, bmax, q, rem, lambda, H, d_fail, ctrl, s);
+        block_inverse_p<P + 1, FAC>(Gs, kp, k, bmax, q, rem, lambda, H, d_fail, ctrl, s);
 }
 
 hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const double *Gs, int64_t kp,
                                             int32_t *d_fail, hipStream_t s) {
     const Layout &L = h->L;
     if (L.bmax > MAXB) return launch_big_block_inverses(h, Gs, kp, d_fail, s);
-    block_inverse_p<1>(Gs, kp, L.k, L.bmax, L.q, L.rem, h->lambda, h->d_H, d_fail, nullptr, s);
+    block_inverse_p<1, false>(Gs, kp, L.k, L.bmax, L.q, L.rem, h->lambda, h->d_H, d_fail, nullptr, s);
     return hipGetLastError();
 }
 
-// (G_t + lambda I)^{-1} of `sets` packed K x K Grams, K <= MAXB, at H + t K^2.
+// (G_t + lambda I)^{-1} of `sets` packed K x K Grams, K <= MAXB, in the factored
+// form (wl_put_factor) at M + t K^2.
 // One that is not positive definite ends the adjoint (status and done).
-hipError_t launch_inverse_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *H,
-                               hipStream_t s) {
-    block_inverse_p<1>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->lambda, H, nullptr,
-                       h->d_ctrl, s);
+hipError_t launch_factor_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *M,
+                              hipStream_t s) {
+    block_inverse_p<1, true>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->lambda, M, nullptr,
+                             h->d_ctrl, s);
     return hipGetLastError();
 }
 

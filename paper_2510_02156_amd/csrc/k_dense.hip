@@ -13,7 +13,8 @@ namespace rorbk {
 // [w*wu, (w+1)*wu), split into 128-column slabs; a slab is read by NV lanes
 // (16 bytes each) per row, and 16 row groups share the rows of a step:
 //   1. (ymode 0) r_S = b_S - sum_ch Pin[ch][.] (chunk order), y = H_t r_S with
-//      the stored inverse H_t of block t; (ymode 1) y given;
+//      the stored inverse H_t of block t, or y = X^T D^{-1} X r_S with the
+//      factored one of a gathered set; (ymode 1) y given;
 //   2. x[cols] += A_S[:, cols]^T y (row groups summed in group order);
 //   3. Pout[w][p] = A_{S'}[p, cols] . x[cols] for the next step's rows S'.
 // Every independent load (both row sets' first slab, the partials, the stored
@@ -33,7 +34,7 @@ struct StepP {
     const void *b;
     void *x;
     void *gb;
-    const double *Hsel;    // stored inverse of a gathered row set (NULL: the block's)
+    const double *Msel;    // factored inverse of a gathered row set, or NULL
     const double *ygiven;
     RowSel nxt;
     double *Pout;
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(STEP_T) void k_step_dense(StepP p) {
 
     __shared__ V s_x[1024];
     __shared__ V s_red[G][128];
-    __shared__ double s_r[MAXB], s_y[MAXB];
+    __shared__ double s_r[MAXB], s_w[MAXB], s_y[MAXB];
 
     int32_t crow[RPT], nrow[RPT];   // row ids (m < 2^31), -1 = none
 #pragma unroll
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(STEP_T) void k_step_dense(StepP p) {
     for (int c = tid; c < wcols; c += NT) s_x[c] = x[c0 + c];
 
     if (p.ymode == 0) {
-        const double *__restrict__ H = p.Hsel ? p.Hsel : p.H + blk_hoff(tc, p.q, p.rem);
+        const double *__restrict__ H = p.Msel ? p.Msel : p.H + blk_hoff(tc, p.q, p.rem);
         // prefetch the first HP stored-inverse terms of row tid / TPR
         constexpr int HP = (64 / TPR < 16) ? 64 / TPR : 16;
         double hpre[HP];
@@ -146,27 +147,50 @@ __global__ __launch_bounds__(STEP_T) void k_step_dense(StepP p) {
             if (i < cnt && qd == 0) s_r[i] = bi - s;
         }
         __syncthreads();
-        for (int base = 0; base < cnt; base += 128) {
-            const int i = base + tid / TPR, qd = tid % TPR;
-            double s = 0.0;
-            if (i < cnt) {
-                for (int jb = 0; jb < cnt; jb += HP * TPR) {
-                    double t[HP];
+        // out = (the entries of the matrix that `part` takes) vin
+        auto product = [&](const double *vin, double *out, auto part, auto scale) {
+            for (int base = 0; base < cnt; base += 128) {
+                const int i = base + tid / TPR, qd = tid % TPR;
+                double s = 0.0, dg = 0.0;
+                if (i < cnt) {
+                    for (int jb = 0; jb < cnt; jb += HP * TPR) {
+                        double t[HP];
 #pragma unroll
-                    for (int u = 0; u < HP; ++u) {
-                        const int j = jb + qd + TPR * u;
-                        t[u] = (base == 0 && jb == 0) ? hpre[u]
-                               : ((j < cnt) ? H[(int64_t)j * cnt + i] : 0.0);
-                    }
+                        for (int u = 0; u < HP; ++u) {
+                            const int j = jb + qd + TPR * u;
+                            t[u] = (base == 0 && jb == 0) ? hpre[u]
+                                   : ((j < cnt) ? H[(int64_t)j * cnt + i] : 0.0);
+                        }
 #pragma unroll
-                    for (int u = 0; u < HP; ++u) {
-                        const int j = jb + qd + TPR * u;
-                        if (j < cnt) s = __builtin_fma(t[u], s_r[j], s);
+                        for (int u = 0; u < HP; ++u) {
+                            const int j = jb + qd + TPR * u;
+                            if (j < cnt) s = __builtin_fma(part(t[u], i, j, dg), vin[j], s);
+                        }
                     }
                 }
+                s = group_sum(s, TPR);
+                scale(s, dg);
+                if (i < cnt && qd == 0) out[i] = s;
             }
-            s = group_sum(s, TPR);
-            if (i < cnt && qd == 0) s_y[i] = s;
+        };
+        if (p.Msel) {   // uniform: w = D^{-1} X r, y = X^T w
+            product(
+                s_r, s_w,
+                [](double t, int i, int j, double &dg) {
+                    if (j == i) dg = t;
+                    return j < i ? t : (j == i ? 1.0 : 0.0);
+                },
+                [](double &s, double dg) { s *= group_sum(dg, TPR); });
+            __syncthreads();
+            product(
+                s_w, s_y,
+                [](double t, int i, int j, double &) {
+                    return j > i ? t : (j == i ? 1.0 : 0.0);
+                },
+                [](double &, double) {});
+        } else {
+            product(
+                s_r, s_y, [](double t, int, int, double &) { return t; }, [](double &, double) {});
         }
         __syncthreads();
     } else {
@@ -372,7 +396,7 @@ static hipError_t step_typed(const rorbk_handle_s *h, const StepArgs &a, hipStre
     p.x = a.x;
     p.gb = a.gb;
     p.ygiven = a.ygiven;
-    p.Hsel = a.Hsel;
+    p.Msel = a.Msel;
     p.nxt = a.nxt;
     p.Pout = a.Pout;
     p.wu = L.wu;

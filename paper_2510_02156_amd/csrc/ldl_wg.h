@@ -231,9 +231,74 @@ __device__ __forceinline__ void wl_back(const double *T, const double *rd, doubl
     __syncthreads();
 }
 
-// H = (L D L^T)^{-1} after wl_factor, written row-major K x K: X = L^{-1} by
-// tile columns, a wave each (X_IJ = -E_I sum_k L_Ik X_kJ with the X_kJ of the
-// column in registers), the columns into the tiles' places, then
+// X = L^{-1} after wl_factor, wave J < P forming tile column J in registers,
+// X_IJ = -E_I sum_k L_Ik X_kJ with the X_kJ of the column at hand.
+template <int P>
+__device__ __forceinline__ void wl_lower_inverse(const double *T, const double *rd, dvec4 (&X)[P]) {
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    const int J = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (J >= P) return;
+    int at[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) at[q] = wl_at(4 * q + lk, li);
+#pragma unroll
+    for (int I = 0; I < P; ++I) {
+        if (I == J) {
+            const double *E = T + wl_tile(P, J, J);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) X[I][r] = E[wl_at(li, 4 * r + lk)];
+        } else if (I > J) {
+            dvec4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < I; ++k)
+                if (k >= J) {
+                    const double *w = T + wl_tile(P, k, I);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            -w[at[q]] * rd[16 * k + 4 * q + lk], X[k][q], acc, 0, 0, 0);
+                }
+            const double *E = T + wl_tile(P, I, I);
+            X[I] = dvec4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                X[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(E[at[q]], acc[q], X[I], 0, 0, 0);
+        }
+    }
+}
+
+// The factored form of (L D L^T)^{-1} after wl_factor, row-major K x K:
+// X = L^{-1} below the diagonal, its mirror image above, 1 / d_i on it.
+// y = X^T D^{-1} X r from it is as accurate as the two substitutions, which
+// the product with the inverse is not: of rows that nearly repeat, r almost
+// the same for both, each entry of H r rounds by itself, and A^T y passes the
+// rounding on magnified (160 rows, pairs 1e-4 apart: the adjoint's dL/dx0 59
+// times further from the exact one).
+template <int P, int NW>
+__device__ __forceinline__ void wl_put_factor(const double *T, const double *rd, int K,
+                                              double *__restrict__ M) {
+    static_assert(NW >= P, "a wave per tile column");
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    const int J = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    dvec4 X[P];
+    wl_lower_inverse<P>(T, rd, X);
+    if (J >= P) return;
+#pragma unroll
+    for (int I = 0; I < P; ++I)
+        if (I >= J)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 16 * I + lk + 4 * r, j = 16 * J + li;
+                if (i < K && j < i) {
+                    M[(int64_t)i * K + j] = X[I][r];
+                    M[(int64_t)j * K + i] = X[I][r];
+                }
+            }
+    for (int i = 16 * J + lane; i < 16 * J + 16 && i < K; i += 64) M[(int64_t)i * K + i] = rd[i];
+}
+
+// H = (L D L^T)^{-1} after wl_factor, written row-major K x K: X = L^{-1}, its
+// columns into the tiles' places, then
 // H_IJ = sum_{k >= I} X_kI^T D_k^{-1} X_kJ with the mirrored entries from the
 // lower ones, so that H is exactly symmetric.
 template <int P, int NW>
@@ -246,33 +311,7 @@ __device__ __forceinline__ void wl_inverse(double *T, const double *rd, int K,
 #pragma unroll
     for (int q = 0; q < 4; ++q) at[q] = wl_at(4 * q + lk, li);
     dvec4 X[P];
-    if (wv < P) {
-        const int J = wv;
-#pragma unroll
-        for (int I = 0; I < P; ++I) {
-            if (I == J) {
-                const double *E = T + wl_tile(P, J, J);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) X[I][r] = E[wl_at(li, 4 * r + lk)];
-            } else if (I > J) {
-                dvec4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int k = 0; k < I; ++k)
-                    if (k >= J) {
-                        const double *w = T + wl_tile(P, k, I);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                                -w[at[q]] * rd[16 * k + 4 * q + lk], X[k][q], acc, 0, 0, 0);
-                    }
-                const double *E = T + wl_tile(P, I, I);
-                X[I] = dvec4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    X[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(E[at[q]], acc[q], X[I], 0, 0, 0);
-            }
-        }
-    }
+    wl_lower_inverse<P>(T, rd, X);
     __syncthreads();
     if (wv < P) {
         const int J = wv;

@@ -342,7 +342,7 @@ void destroy_all(rorbk_handle_s *h) {
     dfree(h, h->d_rep_tau);
     dfree(h, h->d_rep_I);
     dfree(h, h->d_advG);
-    dfree(h, h->d_advH);
+    dfree(h, h->d_advM);
     free_solve_buffers(h);
     if (h->ev0) (void)hipEventDestroy(h->ev0);
     if (h->ev1) (void)hipEventDestroy(h->ev1);
@@ -1552,28 +1552,28 @@ int ror_bk_solve(rorbk_handle h, const void *b, void *x, uint64_t seed, double t
 namespace {
 
 // The recorded greedy sets are known before the adjoint starts, so their
-// regularised Grams are inverted many at a time (as many workgroups as sets
+// regularised Grams are factored many at a time (as many workgroups as sets
 // instead of one, 15 us for the solve and 4 for the Gram of every step) and a
-// greedy step then takes its y from a stored inverse as a sampled one does.
+// greedy step then takes its y from two products with the factored inverse.
 // Sets in one go: at most 64, in at most 64 MiB.
 int64_t adjoint_sets(const Layout &L, int64_t iters) {
     const int64_t per = 8 * (L.K * L.K + L.K * (L.K + 1) / 2);
     return std::max<int64_t>(1, std::min<int64_t>({64, iters, ((int64_t)64 << 20) / per}));
 }
 
-int adjoint_inverses(rorbk_handle_s *h, int64_t it0, int sets) {
+int adjoint_factors(rorbk_handle_s *h, int64_t it0, int sets) {
     const Layout &L = h->L;
     const int K = (int)L.K;
     if (h->adv_sets < sets) {
         // (the larger buffers replace the old ones once the work on those is done)
         HIPCHK(hipStreamSynchronize(h->stream));
         dfree(h, h->d_advG);
-        dfree(h, h->d_advH);
+        dfree(h, h->d_advM);
         h->adv_sets = 0;
         CHK(dalloc(h, &h->d_advG, (size_t)sets * K * (K + 1) / 2));
-        CHK(dalloc(h, &h->d_advH, (size_t)sets * K * K + RORBK_CSR_PAD));
-        // the CSR step reads past the last inverse
-        HIPCHK(launch_fill_zero(h->d_advH + (size_t)sets * K * K, 8 * RORBK_CSR_PAD, h->stream));
+        CHK(dalloc(h, &h->d_advM, (size_t)sets * K * K + RORBK_CSR_PAD));
+        // the CSR step reads past the last matrix
+        HIPCHK(launch_fill_zero(h->d_advM + (size_t)sets * K * K, 8 * RORBK_CSR_PAD, h->stream));
         h->adv_sets = sets;
     }
     const int32_t *idx = h->d_recI + it0 * K;
@@ -1581,7 +1581,7 @@ int adjoint_inverses(rorbk_handle_s *h, int64_t it0, int sets) {
         HIPCHK(launch_gram_csr(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
     else
         HIPCHK(launch_gram_sets_dense(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
-    HIPCHK(launch_inverse_sets(h, h->d_advG, K, sets, h->d_advH, h->stream));
+    HIPCHK(launch_factor_sets(h, h->d_advG, K, sets, h->d_advM, h->stream));
     return RORBK_OK;
 }
 
@@ -1636,11 +1636,11 @@ int backward_range(rorbk_handle_s *h, int64_t a, int64_t bnd, bool last_conv_in_
     ping ^= 1;
     const bool batched = !h->big && !h->col;
     const int64_t batch = adjoint_sets(L, bnd - a);
-    int64_t blo = bnd;   // inverses of the greedy sets of iterations blo .. are at hand
+    int64_t blo = bnd;   // factors of the greedy sets of iterations blo .. are at hand
     for (size_t i = 0; i < steps.size(); ++i) {
         const St &st = steps[i];
         sa.cur = st.r;
-        sa.Hsel = nullptr;
+        sa.Msel = nullptr;
         if (h->col) {
             // column form: y = -A_S (A_S^T A_S + lambda I)^{-1} g, gb[S] -= y
             HIPCHK(launch_col_adjoint(h, st.r, vec, g, gb, h->d_bigr, s));
@@ -1649,11 +1649,11 @@ int backward_range(rorbk_handle_s *h, int64_t a, int64_t bnd, bool last_conv_in_
         } else if (st.greedy && batched) {
             if (st.it < blo) {
                 blo = std::max(a, st.it - batch + 1);
-                CHK(adjoint_inverses(h, blo, (int)(st.it - blo + 1)));
+                CHK(adjoint_factors(h, blo, (int)(st.it - blo + 1)));
             }
             sa.ymode = 0;
             sa.Pin = h->d_P[ping];
-            sa.Hsel = h->d_advH + (st.it - blo) * L.K * L.K;
+            sa.Msel = h->d_advM + (st.it - blo) * L.K * L.K;
         } else if (st.greedy) {
             HIPCHK(gram(h, h->A, L.dtype, h->aligned, st.r.idx, (int)L.K, h->d_G));
             HIPCHK(launch_chol_solve(h, h->d_G, (int)L.K, nullptr, h->d_P[ping], h->d_y, s));

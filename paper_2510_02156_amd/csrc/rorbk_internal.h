@@ -116,7 +116,7 @@ struct rorbk_handle_s {
     size_t arena_bytes;       // device memory,
     size_t arena_used;        // the rest for buffers made later,
     int32_t arena_dev;        // its device
-    double *d_advG, *d_advH;  // adjoint: Grams and inverses of adv_sets greedy sets
+    double *d_advG, *d_advM;  // adjoint: Grams and factored inverses of adv_sets greedy sets
     int64_t adv_sets;
     uint32_t *d_selcnt;       // selection workgroups done (fused merge), 0 between launches
     double *d_ysum;           // sum of the rows of A (n), for the initial solution
@@ -246,7 +246,7 @@ struct StepArgs {
                           // x += A_S^T y in either form (column-form adjoint)
     const double *Pin;    // partials of the current step
     const double *ygiven;
-    const double *Hsel;   // ymode 0 on a gathered row set: its stored inverse
+    const double *Msel;   // ymode 0 on a gathered row set: its factored inverse
     RowSel nxt;           // rows whose partial products are produced
     double *Pout;
 };
@@ -373,8 +373,8 @@ hipError_t launch_fwd_chain(const rorbk_handle_s *h, const FwdArgs &a, const voi
                             double *ckst, hipStream_t s);
 hipError_t launch_gram_sets_dense(const rorbk_handle_s *h, const void *A, int dt,
                                   const int32_t *idx, int K, int sets, double *G, hipStream_t s);
-hipError_t launch_inverse_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *H,
-                               hipStream_t s);
+hipError_t launch_factor_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *M,
+                              hipStream_t s);
 hipError_t launch_gram_dense(const rorbk_handle_s *h, const void *A, int dt,
                              const int32_t *idx, int K, double *Gpart, hipStream_t s);
 hipError_t launch_step_csr(const rorbk_handle_s *h, const StepArgs &a, hipStream_t s);
