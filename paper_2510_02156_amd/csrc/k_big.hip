@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256) void k_big_xtx(const double *__restrict__ X, i
     }
     const int64_t t = t0 + bt;
     const int K = fixedK > 0 ? fixedK : blk_rows(t, q, rem);
-    double *Hb = H + (fixedK > 0 ? t * (int64_t)fixedK * fixedK : blk_hoff(t, q, rem));
+    double *Hb = H + (fixedK > 0 ? t * (int64_t)fixedK * fixedK : blk_hoff(t, q, rem, 0));
     const int r = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * 4;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256) void k_big_y(const double *__restrict__ H,
     const int64_t cst = blk_start(t, q, rem);
     for (int j = threadIdx.x; j < cnt; j += blockDim.x) sr[j] = r[j];
     __syncthreads();
-    const double *Hb = H + blk_hoff(t, q, rem);
+    const double *Hb = H + blk_hoff(t, q, rem, 0);
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
     double s = 0.0;
     if (i < cnt) {

@@ -9,21 +9,20 @@ namespace rorbk {
 
 // ------------------------------------------------------------- partition --
 // Algorithm 1, first step: k contiguous blocks of floor(m/k) rows, the first
-// (m mod k) of them one row longer.  hoff[t] = sum_{s<t} b_s^2 locates the
-// stored inverse of block t.
-__global__ void k_partition(int64_t m, int64_t k, int64_t *off, int64_t *hoff) {
+// (m mod k) of them one row longer.  hoff[t] locates the stored inverse of
+// block t.
+__global__ void k_partition(int64_t m, int64_t k, int64_t zc, int64_t *off, int64_t *hoff) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t > k) return;
     const int64_t q = m / k, rem = m - k * q;
     off[t] = t * q + (t < rem ? t : rem);
-    const int64_t big = (t < rem ? t : rem);
-    hoff[t] = big * (q + 1) * (q + 1) + (t - big) * q * q;
+    hoff[t] = blk_hoff(t, q, rem, zc);
 }
 
-hipError_t launch_partition(int64_t m, int64_t k, int64_t *off, int64_t *hoff,
+hipError_t launch_partition(int64_t m, int64_t k, int64_t zc, int64_t *off, int64_t *hoff,
                             hipStream_t s) {
     const int64_t nb = (k + 1 + 255) / 256;
-    hipLaunchKernelGGL(k_partition, dim3((unsigned)nb), dim3(256), 0, s, m, k, off, hoff);
+    hipLaunchKernelGGL(k_partition, dim3((unsigned)nb), dim3(256), 0, s, m, k, zc, off, hoff);
     return hipGetLastError();
 }
 
@@ -973,7 +972,7 @@ template <int P>
 constexpr int bi_waves() { return P < 4 ? 4 : P; }
 template <int P, bool FAC>
 __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
-    const double *__restrict__ Gs, int64_t kpmax, int64_t q, int64_t rem, double lambda,
+    const double *__restrict__ Gs, int64_t kpmax, int64_t q, int64_t rem, int64_t zc, double lambda,
     double *__restrict__ H, int32_t *__restrict__ fail, Ctrl *__restrict__ ctrl) {
     constexpr int NW = bi_waves<P>();
     __shared__ __align__(16) double T[wl_tiles(P) * WT];
@@ -991,7 +990,8 @@ __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
         }
         return;
     }
-    double *Ht = H + blk_hoff(t, q, rem);
+    double *Ht = H + blk_hoff(t, q, rem, zc);
+    for (int e = threadIdx.x; e < K * (int)zc; e += 64 * NW) Ht[K * K + e] = 0.0;
     if constexpr (FAC) wl_put_factor<P, NW>(T, rd, K, Ht);
     else wl_inverse<P, NW>(T, rd, K, Ht);
 }
@@ -999,29 +999,30 @@ __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
 // k matrices of q or q + 1 (the first rem) rows, bmax at most.
 template <int P, bool FAC>
 static void block_inverse_p(const double *Gs, int64_t kp, int64_t k, int64_t bmax, int64_t q,
-                            int64_t rem, double lambda, double *H, int32_t *d_fail, Ctrl *ctrl,
+                            int64_t rem, int64_t zc, double lambda, double *H, int32_t *d_fail, Ctrl *ctrl,
                             hipStream_t s) {
     if ((bmax + 15) / 16 == P)
         hipLaunchKernelGGL((k_block_inverse<P, FAC>), dim3((unsigned)k), dim3(64 * bi_waves<P>()), 0, s,
-                           Gs, kp, q, rem, lambda, H, d_fail, ctrl);
+                           Gs, kp, q, rem, zc, lambda, H, d_fail, ctrl);
     else if constexpr (P < WL_MAXP)
-        block_inverse_p<P + 1, FAC>(Gs, kp, k, bmax, q, rem, lambda, H, d_fail, ctrl, s);
+        block_inverse_p<P + 1, FAC>(Gs, kp, k, bmax, q, rem, zc, lambda, H, d_fail, ctrl, s);
 }
 
 hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const double *Gs, int64_t kp,
                                             int32_t *d_fail, hipStream_t s) {
     const Layout &L = h->L;
     if (L.bmax > MAXB) return launch_big_block_inverses(h, Gs, kp, d_fail, s);
-    block_inverse_p<1, false>(Gs, kp, L.k, L.bmax, L.q, L.rem, h->lambda, h->d_H, d_fail, nullptr, s);
+    block_inverse_p<1, false>(Gs, kp, L.k, L.bmax, L.q, L.rem, L.zc, h->lambda, h->d_H, d_fail,
+                              nullptr, s);
     return hipGetLastError();
 }
 
 // (G_t + lambda I)^{-1} of `sets` packed K x K Grams, K <= MAXB, in the factored
-// form (wl_put_factor) at M + t K^2.
+// form (wl_put_factor) at M + t K (K + zc).
 // One that is not positive definite ends the adjoint (status and done).
 hipError_t launch_factor_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *M,
                               hipStream_t s) {
-    block_inverse_p<1, true>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->lambda, M, nullptr,
+    block_inverse_p<1, true>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->L.zc, h->lambda, M, nullptr,
                              h->d_ctrl, s);
     return hipGetLastError();
 }

@@ -258,8 +258,8 @@ constexpr int CSR_HU = ((MAXB + CSR_TPR - 1) / CSR_TPR + CSR_HG - 1) / CSR_HG * 
 constexpr int CSR_HT = CSR_STEP_T / 2;  // threads of the product; the others take the entries
 constexpr int CSR_ET = CSR_STEP_T - CSR_HT;
 static_assert(MAXB <= 2 * CSR_HT / CSR_TPR, "two rows per thread group");
-static_assert(CSR_HU * CSR_TPR * MAXB - MAXB * MAXB + MAXB <= RORBK_CSR_PAD,
-              "columns read past a stored inverse stay inside the allocation");
+static_assert(CSR_HG * CSR_TPR - 1 <= RORBK_CSR_ZCOLS,
+              "columns read past a stored inverse are its own zeros");
 
 struct CsrStepP {
     const int64_t *rowptr;
@@ -480,13 +480,13 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     bool multi;
     if (!entries) {
         // B. y = H_t r_S: row tid / 4 (and that + 128 of larger blocks),
-        // columns tid % 4 + 4 u (columns past it, finite, meet zeros of s_r);
+        // columns tid % 4 + 4 u (columns past it hold zeros);
         // the loads travel through the other half's barriers
         const int qd = tid % CSR_TPR;
         int hi = tid / CSR_TPR;
         double hv[CSR_HU];
         auto load_row = [&]() {
-            const double *ph = (p.Msel ? p.Msel : p.H + blk_hoff(tc, p.q, p.rem)) +
+            const double *ph = (p.Msel ? p.Msel : p.H + blk_hoff(tc, p.q, p.rem, RORBK_CSR_ZCOLS)) +
                                (int64_t)qd * cnt + (hi < cnt ? hi : 0);
             const int64_t st = (int64_t)CSR_TPR * cnt;
 #pragma unroll

@@ -24,6 +24,7 @@ namespace rorbk {
 struct StepP {
     const void *A;
     int64_t ld, m, n, q, rem;
+    int64_t zc;            // columns of zeros behind each stored inverse
     const int32_t *tau;
     RowSel cur;
     int ymode;
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(STEP_T) void k_step_dense(StepP p) {
     for (int c = tid; c < wcols; c += NT) s_x[c] = x[c0 + c];
 
     if (p.ymode == 0) {
-        const double *__restrict__ H = p.Msel ? p.Msel : p.H + blk_hoff(tc, p.q, p.rem);
+        const double *__restrict__ H = p.Msel ? p.Msel : p.H + blk_hoff(tc, p.q, p.rem, p.zc);
         // prefetch the first HP stored-inverse terms of row tid / TPR
         constexpr int HP = (64 / TPR < 16) ? 64 / TPR : 16;
         double hpre[HP];
@@ -396,6 +397,7 @@ static hipError_t step_typed(const rorbk_handle_s *h, const StepArgs &a, hipStre
     p.x = a.x;
     p.gb = a.gb;
     p.ygiven = a.ygiven;
+    p.zc = L.zc;
     p.Msel = a.Msel;
     p.nxt = a.nxt;
     p.Pout = a.Pout;

@@ -440,6 +440,8 @@ struct FwdSamp3P {
 // and no group of MG entries needs a bound of its own.
 constexpr int MG = 4;
 constexpr int MC = ((FWD_B + 1) / 2 + MG - 1) / MG * MG;   // most entries per thread
+// (hb of blocks of bmax rows serves those of bmax - 1 too: 2 hb - (bmax - 1) at most)
+static_assert(2 * MG <= RORBK_FWD_ZCOLS, "columns read past a stored inverse are its own zeros");
 __device__ __forceinline__ int mv_half(int cols) { return ((cols + 1) / 2 + MG - 1) / MG * MG; }
 // LDS slots per block of the vectors mv_dot reads; the slots past the block
 // hold zeros, which meet whatever finite entries mv_load read past the matrix
@@ -456,10 +458,10 @@ __device__ __forceinline__ double pair_other(double v) {
 
 // Entry (i, hb h + t) of a rows x cols matrix stored at M[i + j * sj] into
 // m[t] (rows past it get some other row's entries, whose product is not used).
-// Up to nine columns past the matrix are read, finite numbers that meet
-// zeros: the stored inverses and the cross-Grams are allocated with
-// RORBK_FWD_PAD doubles behind them and cleared at setup where nothing else
-// writes.  So a load is an address addition and no select; clamping
+// Up to eight columns past the matrix are read and multiplied by zero: the
+// zeros behind each stored inverse, or finite numbers (the next cross-Grams,
+// which are cleared at setup where nothing else writes, and RORBK_FWD_PAD
+// doubles behind the last).  So a load is an address addition and no select; clamping
 // every address cost 6 us for a thread's two matrices, and a select on the
 // loaded value made the compiler wait for every load by itself (12 us).
 __device__ __forceinline__ void mv_load(const double *__restrict__ M, uint32_t sj, int i, int h,
@@ -558,9 +560,9 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
     const int tid = threadIdx.x, g = tid / NV, v = tid % NV;
     Blk3 B;
     blocks3(p.tau, p.tau_index, p.q, p.rem, B);
-    const int64_t hoff0 = blk_hoff(p.tau[p.tau_index], p.q, p.rem);
-    const int64_t hoff1 = blk_hoff(p.tau[p.tau_index + 1], p.q, p.rem);
-    const int64_t hoff2 = blk_hoff(p.tau[p.tau_index + 2], p.q, p.rem);
+    const int64_t hoff0 = blk_hoff(p.tau[p.tau_index], p.q, p.rem, RORBK_FWD_ZCOLS);
+    const int64_t hoff1 = blk_hoff(p.tau[p.tau_index + 1], p.q, p.rem, RORBK_FWD_ZCOLS);
+    const int64_t hoff2 = blk_hoff(p.tau[p.tau_index + 2], p.q, p.rem, RORBK_FWD_ZCOLS);
     const int ncnt = B.c0 + B.c1 + B.c2;
     const int bm = p.bmax;
     const int n0 = B.c0, n1 = B.c1, n2 = B.c2;
@@ -952,9 +954,9 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
         // the sampled steps' matrices (two per thread range, as k_fwd_samp3)
         double m2[MC];
         {
-            const int64_t hoff0 = blk_hoff(p.tau[p.tau_index], p.q, p.rem);
-            const int64_t hoff1 = blk_hoff(p.tau[p.tau_index + 1], p.q, p.rem);
-            const int64_t hoff2 = blk_hoff(p.tau[p.tau_index + 2], p.q, p.rem);
+            const int64_t hoff0 = blk_hoff(p.tau[p.tau_index], p.q, p.rem, RORBK_FWD_ZCOLS);
+            const int64_t hoff1 = blk_hoff(p.tau[p.tau_index + 1], p.q, p.rem, RORBK_FWD_ZCOLS);
+            const int64_t hoff2 = blk_hoff(p.tau[p.tau_index + 2], p.q, p.rem, RORBK_FWD_ZCOLS);
             chain_mats_wave(p.H, p.xg, hoff0, hoff1, hoff2, n0, n1, n2, bm, wv - 1, rg, ir, h, hb,
                             m, m2);
         }

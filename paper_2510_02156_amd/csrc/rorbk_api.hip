@@ -811,7 +811,10 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
 
     const int64_t k = L.k, K = L.K, bmax = L.bmax;
     const int64_t q = L.q, rem = L.rem;
-    const int64_t htotal = h->col ? k * L.n * L.n : rem * (q + 1) * (q + 1) + (k - rem) * q * q;
+    L.zc = L.format == RORBK_CSR ? RORBK_CSR_ZCOLS
+                                 : (bmax <= RORBK_FWD_MAX_BLOCK ? RORBK_FWD_ZCOLS : 0);
+    const int64_t htotal = h->col ? k * L.n * L.n
+                                  : rem * (q + 1) * (q + 1 + L.zc) + (k - rem) * q * (q + L.zc);
     const int64_t gdim = h->col ? L.n : K;   // size of the greedy system
     int rc = RORBK_OK;
     Arena ar;
@@ -821,8 +824,7 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     ALLOC(h->d_S, k);
     ALLOC(h->d_pbar, k);
     ALLOC(h->d_W, k);
-    const int64_t hpad = L.format == RORBK_CSR ? RORBK_CSR_PAD : RORBK_FWD_PAD;
-    ALLOC(h->d_H, htotal + hpad);
+    ALLOC(h->d_H, htotal);
     ALLOC(h->d_ctrl, 1);
     ALLOC(h->d_P[0], (int64_t)L.nch_u * bmax);
     ALLOC(h->d_P[1], (int64_t)L.nch_u * bmax);
@@ -910,9 +912,8 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     if (hipMemsetAsync(h->d_selcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess ||
         (h->d_fwdcnt &&
          hipMemsetAsync(h->d_fwdcnt, 0, sizeof(uint32_t), (hipStream_t)stream) != hipSuccess) ||
-        // the chain step and the CSR step read, and multiply by zero, entries
-        // past the matrices in these: they have to be finite
-        launch_fill_zero(h->d_H + htotal, 8 * hpad, (hipStream_t)stream) != hipSuccess ||
+        // the chain step reads, and multiplies by zero, entries past the
+        // matrices in these: they have to be finite
         (h->d_XG && launch_fill_zero(h->d_XG, 8 * (6 * bmax * bmax + RORBK_FWD_PAD),
                                      (hipStream_t)stream) != hipSuccess) ||
         (h->d_C && launch_fill_zero(h->d_C, 8 * (int64_t)L.nch_c * 3 * RORBK_FWD_MAX_BLOCK * 64,
@@ -950,7 +951,7 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
                              "CSR arrays invalid (rowptr not monotone from 0 to nnz, or column "
                              "indices not strictly ascending in [0, n) within a row)"));
     }
-    if (launch_partition(L.m, k, h->d_off, h->d_hoff, s) != hipSuccess)
+    if (launch_partition(L.m, k, L.zc, h->d_off, h->d_hoff, s) != hipSuccess)
         return bail(fail(RORBK_ERR_HIP, "partition launch failed"));
     // centroid cosines and the proposal, then the stored block inverses, both on
     // one scratch array (the second starts when the first is done with it)
@@ -1035,7 +1036,7 @@ int ror_bk_get_block_inverse(rorbk_handle h, int64_t t, double *Hinv_host) {
     const Layout &L = h->L;
     if (t < 0 || t >= L.k) return fail(RORBK_ERR_INVALID_ARG, "block %lld out of range", (long long)t);
     const int64_t big = std::min(t, L.rem);
-    int64_t off = big * (L.q + 1) * (L.q + 1) + (t - big) * L.q * L.q;
+    int64_t off = big * (L.q + 1) * (L.q + 1 + L.zc) + (t - big) * L.q * (L.q + L.zc);
     int64_t bt = L.q + (t < L.rem ? 1 : 0);
     if (h->col) {   // column form: (A_t^T A_t + lambda I)^{-1}, n x n
         off = t * L.n * L.n;
@@ -1557,7 +1558,7 @@ namespace {
 // greedy step then takes its y from two products with the factored inverse.
 // Sets in one go: at most 64, in at most 64 MiB.
 int64_t adjoint_sets(const Layout &L, int64_t iters) {
-    const int64_t per = 8 * (L.K * L.K + L.K * (L.K + 1) / 2);
+    const int64_t per = 8 * (L.K * (L.K + L.zc) + L.K * (L.K + 1) / 2);
     return std::max<int64_t>(1, std::min<int64_t>({64, iters, ((int64_t)64 << 20) / per}));
 }
 
@@ -1571,9 +1572,7 @@ int adjoint_factors(rorbk_handle_s *h, int64_t it0, int sets) {
         dfree(h, h->d_advM);
         h->adv_sets = 0;
         CHK(dalloc(h, &h->d_advG, (size_t)sets * K * (K + 1) / 2));
-        CHK(dalloc(h, &h->d_advM, (size_t)sets * K * K + RORBK_CSR_PAD));
-        // the CSR step reads past the last matrix
-        HIPCHK(launch_fill_zero(h->d_advM + (size_t)sets * K * K, 8 * RORBK_CSR_PAD, h->stream));
+        CHK(dalloc(h, &h->d_advM, (size_t)sets * K * (K + L.zc)));
         h->adv_sets = sets;
     }
     const int32_t *idx = h->d_recI + it0 * K;
@@ -1653,7 +1652,7 @@ int backward_range(rorbk_handle_s *h, int64_t a, int64_t bnd, bool last_conv_in_
             }
             sa.ymode = 0;
             sa.Pin = h->d_P[ping];
-            sa.Msel = h->d_advM + (st.it - blo) * L.K * L.K;
+            sa.Msel = h->d_advM + (st.it - blo) * L.K * (L.K + L.zc);
         } else if (st.greedy) {
             HIPCHK(gram(h, h->A, L.dtype, h->aligned, st.r.idx, (int)L.K, h->d_G));
             HIPCHK(launch_chol_solve(h, h->d_G, (int)L.K, nullptr, h->d_P[ping], h->d_y, s));

@@ -25,16 +25,16 @@ typedef double dvec4 __attribute__((ext_vector_type(4)));
 
 // Closed-form partition (Algorithm 1, first step): block t starts at
 // t*q + min(t, rem) and has q or q+1 rows; its stored inverse starts at
-// sum_{s<t} b_s^2.
+// sum_{s<t} b_s (b_s + zc), zc columns of zeros standing behind each.
 __device__ __forceinline__ int64_t blk_start(int64_t t, int64_t q, int64_t rem) {
     return t * q + (t < rem ? t : rem);
 }
 __device__ __forceinline__ int blk_rows(int64_t t, int64_t q, int64_t rem) {
     return (int)(q + (t < rem ? 1 : 0));
 }
-__device__ __forceinline__ int64_t blk_hoff(int64_t t, int64_t q, int64_t rem) {
+__device__ __forceinline__ int64_t blk_hoff(int64_t t, int64_t q, int64_t rem, int64_t zc) {
     const int64_t big = t < rem ? t : rem;
-    return big * (q + 1) * (q + 1) + (t - big) * q * q;
+    return big * (q + 1) * (q + 1 + zc) + (t - big) * q * (q + zc);
 }
 
 // Storage traits: elements per 16-byte load.

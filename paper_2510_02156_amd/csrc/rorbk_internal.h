@@ -37,13 +37,16 @@ struct Ctrl {
 // Blocks of at most this many rows (dense, row form) run the fused forward
 // steps of k_fwd.hip: the three sampled updates in one launch.
 constexpr int RORBK_FWD_MAX_BLOCK = 65;
-// Doubles allocated behind the stored inverses and the cross-Grams for those
-// steps' loads: they read, and multiply by zero, up to nine columns of at most
-// RORBK_FWD_MAX_BLOCK entries past a matrix's last and one more.
+// Columns of zeros behind each stored inverse for the steps that read whole
+// groups of columns and multiply those past the matrix by zero: a neighbour's
+// inverse there need not be finite (pivots near the smallest normal number are
+// accepted, and sums of their reciprocals overflow).  The fused forward steps
+// read up to eight columns past, the CSR step up to fifteen.
+constexpr int RORBK_FWD_ZCOLS = 8;
+constexpr int RORBK_CSR_ZCOLS = 15;
+// Doubles behind the cross-Grams, for the same loads (the neighbours there are
+// products of finite rows with finite norms, so finite).
 constexpr int RORBK_FWD_PAD = 12 * RORBK_FWD_MAX_BLOCK;
-// The same behind the stored inverses of CSR blocks, whose step reads whole
-// groups of 16 columns.
-constexpr int RORBK_CSR_PAD = 17 * (RORBK_MAX_BLOCK_ROWS + 1);
 
 // The cross-Gram tile jobs a residual launch carries (jobs == 0: none).
 struct XgSide {
@@ -71,6 +74,7 @@ struct Layout {
     int64_t m, n, ld, nnz;
     int32_t format, dtype;
     int64_t k, q, rem, K, bmax;
+    int64_t zc;           // columns of zeros behind each stored inverse
     // update kernel column chunks
     int64_t wu;           // columns per update workgroup (multiple of 128)
     int32_t nch_u;        // update chunks
@@ -198,7 +202,7 @@ namespace rorbk {
 // Each returns hipSuccess or the launch error.  `vec` is VecType; `dt` is the
 // storage dtype of the matrix pointer passed.
 
-hipError_t launch_partition(int64_t m, int64_t k, int64_t *off, int64_t *hoff,
+hipError_t launch_partition(int64_t m, int64_t k, int64_t zc, int64_t *off, int64_t *hoff,
                             hipStream_t s);
 
 hipError_t launch_sample(uint64_t seed, int64_t j0, int64_t count,
