@@ -979,6 +979,17 @@ __global__ __launch_bounds__(64 * bi_waves<P>()) void k_block_inverse(
     __shared__ double rd[16 * P];
     const int64_t t = blockIdx.x;
     const int K = blk_rows(t, q, rem);
+    if constexpr (!FAC) {
+        // one row: the division itself, as every positive norm is accepted, also
+        // one whose reciprocal the elimination cannot form (below 2^-1024, Inf)
+        if (K == 1) {   // uniform
+            double *Ht = H + blk_hoff(t, q, rem, zc);
+            const double d = Gs[t * kpmax] + lambda;
+            if (threadIdx.x == 0 && !(d > 0.0)) *fail = RORBK_ERR_NOT_SPD;
+            for (int e = threadIdx.x; e <= (int)zc; e += 64 * NW) Ht[e] = (e == 0) ? 1.0 / d : 0.0;
+            return;
+        }
+    }
     wl_load<P, NW>(T, Gs + t * kpmax, 1, K, lambda);
     if (!wl_factor<P, NW, false>(T, rd, nullptr)) {
         if (threadIdx.x == 0) {

@@ -51,3 +51,32 @@ def test_overflowing_inverse_stays_in_its_block(kind, n):
         g = g - A[S].T @ np.linalg.solve(A[S] @ A[S].T, A[S] @ g)
     assert np.isfinite(host(gb)).all()
     assert np.linalg.norm(host(gx0) - g) < 1e-10 * np.sqrt(n)
+
+
+@pytest.mark.parametrize("br", [1, 2])
+@pytest.mark.parametrize("csr", [False, True])
+def test_one_row_blocks_of_any_norm(br, csr):
+    """Blocks of one row: every positive squared norm is accepted, also one
+    whose reciprocal overflows (a last row of 2^-520 here)."""
+    m, n = 2 * br + 1, 40                       # the last block has one row for br = 1
+    A = np.random.default_rng(br).standard_normal((m, n))
+    if br == 1:
+        A[-1] = 0.0
+        A[-1, 3] = 2.0 ** -520
+    if csr:
+        rows, cols = np.nonzero(A)
+        sol = P.Solver(None, br, 0.0, rowptr=dev(np.searchsorted(rows, np.arange(m + 1)), torch.int64),
+                       colidx=dev(cols, torch.int32), values=dev(A[rows, cols]), shape=(m, n))
+    else:
+        sol = P.Solver(dev(A), br, 0.0)
+    off = sol.setup_arrays()["offsets"]
+    for t in range(sol.k):
+        G = A[off[t]:off[t + 1]] @ A[off[t]:off[t + 1]].T
+        with np.errstate(divide="ignore", over="ignore"):
+            want = 1.0 / G if len(G) == 1 else np.linalg.inv(G)
+        np.testing.assert_allclose(sol.block_inverse(t), want, rtol=1e-13)
+    zero = A.copy()
+    zero[-1] = 0.0
+    with pytest.raises(P.RorBkError) as e:
+        P.Solver(dev(zero), br, 0.0)
+    assert e.value.code == P.RORBK_ERR_NOT_SPD
