@@ -1028,12 +1028,43 @@ hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const doubl
     return hipGetLastError();
 }
 
-// (G_t + lambda I)^{-1} of `sets` packed K x K Grams, K <= MAXB, in the factored
+// The nch chunks of `sets` packed Grams (KP entries each) summed in chunk order
+// into the first: an entry a thread, eight loads in flight, so that the factor
+// kernel's few waves have one chunk to load (64 chunks one after another there
+// would be a memory round trip each).
+__global__ __launch_bounds__(64) void k_sum_chunks(double *__restrict__ G, int nch, int64_t KP,
+                                                   const Ctrl *__restrict__ ctrl) {
+    if (ctrl->done) return;
+    const int64_t f = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (f >= KP) return;
+    double *g = G + (int64_t)blockIdx.y * nch * KP + f;
+    double v = g[0];
+    int c = 1;
+    for (; c + 8 <= nch; c += 8) {
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = g[(c + u) * KP];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += t[u];
+    }
+    for (; c < nch; ++c) v += g[c * KP];
+    g[0] = v;
+}
+
+// (G_t + lambda I)^{-1} of `sets` K x K Grams of nch packed chunks each, K <=
+// MAXB (the chunks are summed in place), in the factored
 // form (wl_put_factor) at M + t K (K + zc).
 // One that is not positive definite ends the adjoint (status and done).
-hipError_t launch_factor_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *M,
+hipError_t launch_factor_sets(const rorbk_handle_s *h, double *G, int K, int nch, int sets, double *M,
                               hipStream_t s) {
-    block_inverse_p<1, true>(G, (int64_t)K * (K + 1) / 2, sets, K, K, 0, h->L.zc, h->lambda, M, nullptr,
+    const int64_t KP = (int64_t)K * (K + 1) / 2;
+    if (nch > 1) {
+        hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((KP + 63) / 64), (unsigned)sets), dim3(64),
+                           0, s, G, nch, KP, (const Ctrl *)h->d_ctrl);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    block_inverse_p<1, true>(G, nch * KP, sets, K, K, 0, h->L.zc, h->lambda, M, nullptr,
                              h->d_ctrl, s);
     return hipGetLastError();
 }

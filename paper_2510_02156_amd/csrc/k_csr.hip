@@ -407,7 +407,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     if (p.ctrl->done) return;
     const bool upd = p.ymode != 2 && cnt > 0;
 
-    __shared__ double s_r[CSR_HU * CSR_TPR], s_w[CSR_HU * CSR_TPR], s_y[MAXB];
+    __shared__ double s_r[CSR_HU * CSR_TPR], s_w[MAXB], s_y[MAXB];
     __shared__ int64_t s_len[MAXB], s_off[MAXB + 1], s_p0[MAXB];
     __shared__ int64_t n_len[MAXB], n_off[MAXB + 1], n_p0[MAXB];
     __shared__ int32_t e_col[CSR_CHUNK], e_slot[CSR_CHUNK], s_dup[CSR_CHUNK];
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     int16_t *l_any = (int16_t *)s_dup, *l_ord = l_any + CSR_CHUNK;
 
     // A. row offsets of both row sets; b - Pin or the given y
-    if (tid < CSR_HU * CSR_TPR) s_r[tid] = s_w[tid] = 0.0;
+    if (tid < CSR_HU * CSR_TPR) s_r[tid] = 0.0;
     if (upd) {
         for (int i = tid; i < cnt; i += CSR_STEP_T) {
             const int64_t row = (p.cur.kind == 1) ? (int64_t)p.cur.idx[i] : cst + i;
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
         int hi = tid / CSR_TPR;
         double hv[CSR_HU];
         auto load_row = [&]() {
-            const double *ph = (p.Msel ? p.Msel : p.H + blk_hoff(tc, p.q, p.rem, RORBK_CSR_ZCOLS)) +
+            const double *ph = p.H + blk_hoff(tc, p.q, p.rem, RORBK_CSR_ZCOLS) +
                                (int64_t)qd * cnt + (hi < cnt ? hi : 0);
             const int64_t st = (int64_t)CSR_TPR * cnt;
 #pragma unroll
@@ -511,50 +511,49 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
             s0 = group_sum(s0, CSR_TPR);
             if (qd == 0 && hi < cnt) s_y[hi] = s0;
         };
-        // factored inverse: w = D^{-1} X r (lower entries, the unit and the
-        // reciprocal pivot on the diagonal), then y = X^T w (upper ones)
-        auto dot_factor = [&](bool lower, const double *vin, double *out) {
-            double s0 = 0.0, dg = 0.0;
+        // factored inverse: w = D^{-1} X r (the entries below the diagonal, with
+        // the reciprocal pivots on it), then y = X^T w (those above); read as
+        // they are needed, since a row kept for both products spills the
+        // registers of the other half
+        auto dot_factor = [&](auto lower, const double *vin, double *out) {
+#pragma unroll 1
+            for (int i = tid / CSR_TPR; i < MAXB; i += CSR_HT / CSR_TPR) {
+                const double *row = p.Msel + (i < cnt ? i : 0);
+                const double dg = lower.value ? row[(i < cnt ? i : 0) * cnt] : 1.0;
+                double s0 = 0.0;
+#pragma unroll 1
+                for (int j0 = qd; j0 < cnt; j0 += 16 * CSR_TPR) {
+                    double t[16];
 #pragma unroll
-            for (int u0 = 0; u0 < CSR_HU; u0 += CSR_HG)
-                if (CSR_TPR * u0 < cnt) {
+                    for (int u = 0; u < 16; ++u) {
+                        const int j = j0 + CSR_TPR * u;
+                        t[u] = row[(j < cnt ? j : cnt - 1) * cnt];
+                    }
 #pragma unroll
-                    for (int u = u0; u < u0 + CSR_HG; ++u) {
-                        const int j = qd + CSR_TPR * u;
-                        const bool in = lower ? j < hi : (j > hi && j < cnt);
-                        s0 = __builtin_fma(in ? hv[u] : (j == hi ? 1.0 : 0.0), vin[j], s0);
-                        dg = (j == hi) ? hv[u] : dg;
+                    for (int u = 0; u < 16; ++u) {
+                        const int j = j0 + CSR_TPR * u;
+                        const bool in = lower.value ? j < i : (j > i && j < cnt);
+                        s0 = __builtin_fma(in ? t[u] : 0.0, vin[j < cnt ? j : cnt - 1], s0);
                     }
                 }
-            s0 = group_sum(s0, CSR_TPR);
-            dg = group_sum(dg, CSR_TPR);
-            if (qd == 0 && hi < cnt) out[hi] = lower ? s0 * dg : s0;
+                s0 = group_sum(s0, CSR_TPR);
+                if (qd == 0 && i < cnt) out[i] = (s0 + vin[i]) * dg;
+            }
         };
-        if (own_y) load_row();
+        if (own_y && !fac) load_row();
         __syncthreads();
         __syncthreads();
         __syncthreads();
         multi = s_ndup > 0;
         if (multi) __syncthreads();
-        constexpr int HR = CSR_HT / CSR_TPR;   // rows at a time
         if (fac) {
-            dot_factor(true, s_r, s_w);
-            if (cnt > HR) {   // uniform
-                hi += HR;
-                load_row();
-                dot_factor(true, s_r, s_w);
-            }
+            dot_factor(std::true_type{}, s_r, s_w);
             __syncthreads();
-            dot_factor(false, s_w, s_y);
-            if (cnt > HR) {
-                hi -= HR;
-                load_row();
-                dot_factor(false, s_w, s_y);
-            }
+            dot_factor(std::false_type{}, s_w, s_y);
         } else if (own_y) {
             dot_row();
-            if (cnt > HR) {   // uniform
-                hi += HR;
+            if (cnt > CSR_HT / CSR_TPR) {   // uniform
+                hi += CSR_HT / CSR_TPR;
                 load_row();
                 dot_row();
             }

@@ -147,12 +147,46 @@ __global__ __launch_bounds__(STEP_T) void k_step_dense(StepP p) {
             s = group_sum(s, TPR);
             if (i < cnt && qd == 0) s_r[i] = bi - s;
         }
+        if (tid >= cnt && tid < MAXB) s_r[tid] = s_w[tid] = 0.0;
         __syncthreads();
-        // out = (the entries of the matrix that `part` takes) vin
-        auto product = [&](const double *vin, double *out, auto part, auto scale) {
+        if (p.Msel) {   // uniform: w = D^{-1} X r, y = X^T w
+            // the 64 columns at hand serve both products; the others are read
+            // four at a time, so that the registers hold both
+            auto product = [&](auto lower, const double *vin, double *out) {
+                for (int base = 0; base < cnt; base += 128) {
+                    const int i = base + tid / TPR, qd = tid % TPR;
+                    const double dg = (lower.value && i < cnt) ? H[(int64_t)i * cnt + i] : 1.0;
+                    double s = 0.0;
+                    auto term = [&](int j, double t) {   // (past the set t and vin are zero)
+                        s = __builtin_fma((lower.value ? j < i : j > i) ? t : 0.0, vin[j], s);
+                    };
+                    if (base == 0) {
+#pragma unroll
+                        for (int u = 0; u < HP; ++u) term(qd + TPR * u, hpre[u]);
+                    }
+#pragma unroll 1
+                    for (int jb = (base == 0) ? HP * TPR : 0; jb < cnt; jb += 4 * TPR) {
+                        double t[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int j = jb + qd + TPR * u;
+                            t[u] = (i < cnt && j < cnt) ? H[(int64_t)j * cnt + i] : 0.0;
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (jb + qd + TPR * u < cnt) term(jb + qd + TPR * u, t[u]);
+                    }
+                    s = group_sum(s, TPR);
+                    if (i < cnt && qd == 0) out[i] = lower.value ? (s + vin[i]) * dg : s + vin[i];
+                }
+            };
+            product(std::true_type{}, s_r, s_w);
+            __syncthreads();
+            product(std::false_type{}, s_w, s_y);
+        } else {
             for (int base = 0; base < cnt; base += 128) {
                 const int i = base + tid / TPR, qd = tid % TPR;
-                double s = 0.0, dg = 0.0;
+                double s = 0.0;
                 if (i < cnt) {
                     for (int jb = 0; jb < cnt; jb += HP * TPR) {
                         double t[HP];
@@ -165,33 +199,13 @@ __global__ __launch_bounds__(STEP_T) void k_step_dense(StepP p) {
 #pragma unroll
                         for (int u = 0; u < HP; ++u) {
                             const int j = jb + qd + TPR * u;
-                            if (j < cnt) s = __builtin_fma(part(t[u], i, j, dg), vin[j], s);
+                            if (j < cnt) s = __builtin_fma(t[u], s_r[j], s);
                         }
                     }
                 }
                 s = group_sum(s, TPR);
-                scale(s, dg);
-                if (i < cnt && qd == 0) out[i] = s;
+                if (i < cnt && qd == 0) s_y[i] = s;
             }
-        };
-        if (p.Msel) {   // uniform: w = D^{-1} X r, y = X^T w
-            product(
-                s_r, s_w,
-                [](double t, int i, int j, double &dg) {
-                    if (j == i) dg = t;
-                    return j < i ? t : (j == i ? 1.0 : 0.0);
-                },
-                [](double &s, double dg) { s *= group_sum(dg, TPR); });
-            __syncthreads();
-            product(
-                s_w, s_y,
-                [](double t, int i, int j, double &) {
-                    return j > i ? t : (j == i ? 1.0 : 0.0);
-                },
-                [](double &, double) {});
-        } else {
-            product(
-                s_r, s_y, [](double t, int, int, double &) { return t; }, [](double &, double) {});
         }
         __syncthreads();
     } else {
@@ -415,38 +429,34 @@ hipError_t launch_step_dense(const rorbk_handle_s *h, const StepArgs &a, hipStre
 
 template <typename T>
 static hipError_t gram_typed(const rorbk_handle_s *h, const void *A, int aligned,
-                             const int32_t *idx, int K, int sets, int nch, int64_t wg,
-                             double *Gpart, hipStream_t s) {
+                             const int32_t *idx, int K, int sets, double *Gpart, hipStream_t s) {
     const Layout &L = h->L;
     const int nt = (K + 15) / 16;
-    dim3 grid((unsigned)(nt * (nt + 1) / 2), (unsigned)nch, (unsigned)sets);
+    dim3 grid((unsigned)(nt * (nt + 1) / 2), (unsigned)L.nch_g, (unsigned)sets);
     if (aligned)
         hipLaunchKernelGGL((k_gram_mfma<T, true>), grid, dim3(256), 0, s, (const T *)A, L.ld, L.n,
-                           idx, K, wg, Gpart, (const Ctrl *)h->d_ctrl);
+                           idx, K, L.wg, Gpart, (const Ctrl *)h->d_ctrl);
     else
         hipLaunchKernelGGL((k_gram_mfma<T, false>), grid, dim3(256), 0, s, (const T *)A, L.ld,
-                           L.n, idx, K, wg, Gpart, (const Ctrl *)h->d_ctrl);
+                           L.n, idx, K, L.wg, Gpart, (const Ctrl *)h->d_ctrl);
     return hipGetLastError();
 }
 
-// The Grams of `sets` row sets of K rows each, one packed chunk per set (the
-// sets fill the chip, so their columns are not split further).
+// The Grams of `sets` row sets of K rows each, nch_g packed chunks per set: the
+// column chunks of a single set's Gram, so that a few sets of a wide matrix
+// fill the chip too (one set of 32 rows and 50000 columns: 360 us in one
+// chunk, 15 in 64) and a set gets the same sums in any batch.
 hipError_t launch_gram_sets_dense(const rorbk_handle_s *h, const void *A, int dt,
                                   const int32_t *idx, int K, int sets, double *G, hipStream_t s) {
     const int al = h->aligned;
-    const int64_t n = h->L.n;
-    if (dt == RORBK_F64) return gram_typed<double>(h, A, al, idx, K, sets, 1, n, G, s);
-    if (dt == RORBK_F32) return gram_typed<float>(h, A, al, idx, K, sets, 1, n, G, s);
-    return gram_typed<bf16_t>(h, A, al, idx, K, sets, 1, n, G, s);
+    if (dt == RORBK_F64) return gram_typed<double>(h, A, al, idx, K, sets, G, s);
+    if (dt == RORBK_F32) return gram_typed<float>(h, A, al, idx, K, sets, G, s);
+    return gram_typed<bf16_t>(h, A, al, idx, K, sets, G, s);
 }
 
 hipError_t launch_gram_dense(const rorbk_handle_s *h, const void *A, int dt, const int32_t *idx,
                              int K, double *Gpart, hipStream_t s) {
-    const int al = h->aligned;
-    const Layout &L = h->L;
-    if (dt == RORBK_F64) return gram_typed<double>(h, A, al, idx, K, 1, L.nch_g, L.wg, Gpart, s);
-    if (dt == RORBK_F32) return gram_typed<float>(h, A, al, idx, K, 1, L.nch_g, L.wg, Gpart, s);
-    return gram_typed<bf16_t>(h, A, al, idx, K, 1, L.nch_g, L.wg, Gpart, s);
+    return launch_gram_sets_dense(h, A, dt, idx, K, 1, Gpart, s);
 }
 
 // ------------------------------------------------------------------ setup --

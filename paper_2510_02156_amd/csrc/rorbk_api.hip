@@ -1558,7 +1558,7 @@ namespace {
 // greedy step then takes its y from two products with the factored inverse.
 // Sets in one go: at most 64, in at most 64 MiB.
 int64_t adjoint_sets(const Layout &L, int64_t iters) {
-    const int64_t per = 8 * (L.K * (L.K + L.zc) + L.K * (L.K + 1) / 2);
+    const int64_t per = 8 * (L.K * (L.K + L.zc) + L.nch_g * (L.K * (L.K + 1) / 2));
     return std::max<int64_t>(1, std::min<int64_t>({64, iters, ((int64_t)64 << 20) / per}));
 }
 
@@ -1571,7 +1571,7 @@ int adjoint_factors(rorbk_handle_s *h, int64_t it0, int sets) {
         dfree(h, h->d_advG);
         dfree(h, h->d_advM);
         h->adv_sets = 0;
-        CHK(dalloc(h, &h->d_advG, (size_t)sets * K * (K + 1) / 2));
+        CHK(dalloc(h, &h->d_advG, (size_t)sets * L.nch_g * (K * (K + 1) / 2)));
         CHK(dalloc(h, &h->d_advM, (size_t)sets * K * (K + L.zc)));
         h->adv_sets = sets;
     }
@@ -1580,7 +1580,7 @@ int adjoint_factors(rorbk_handle_s *h, int64_t it0, int sets) {
         HIPCHK(launch_gram_csr(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
     else
         HIPCHK(launch_gram_sets_dense(h, h->A, L.dtype, idx, K, sets, h->d_advG, h->stream));
-    HIPCHK(launch_factor_sets(h, h->d_advG, K, sets, h->d_advM, h->stream));
+    HIPCHK(launch_factor_sets(h, h->d_advG, K, L.nch_g, sets, h->d_advM, h->stream));
     return RORBK_OK;
 }
 

@@ -377,7 +377,7 @@ hipError_t launch_fwd_chain(const rorbk_handle_s *h, const FwdArgs &a, const voi
                             double *ckst, hipStream_t s);
 hipError_t launch_gram_sets_dense(const rorbk_handle_s *h, const void *A, int dt,
                                   const int32_t *idx, int K, int sets, double *G, hipStream_t s);
-hipError_t launch_factor_sets(const rorbk_handle_s *h, const double *G, int K, int sets, double *M,
+hipError_t launch_factor_sets(const rorbk_handle_s *h, double *G, int K, int nch, int sets, double *M,
                               hipStream_t s);
 hipError_t launch_gram_dense(const rorbk_handle_s *h, const void *A, int dt,
                              const int32_t *idx, int K, double *Gpart, hipStream_t s);

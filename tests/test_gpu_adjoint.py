@@ -1,9 +1,10 @@
 """The adjoint's greedy steps: a set whose Gram is not positive definite is
 reported from whichever checkpoint segment it lies in; sets of rows that nearly
-repeat lose no more accuracy than factor solves do.
+repeat lose no more accuracy than factor solves do; Grams in many column chunks
+(wide matrices) give the same bits however many sets go together.
 
-Bar of the latter: the distance from the adjoint in 80-bit arithmetic may be at
-most 8 times the FP64 oracle's, which solves with the factor at every step (the
+Bars: FP64 1e-10 relative to the oracle's adjoint; for rows that nearly repeat the
+distance from the adjoint in 80-bit arithmetic may be at most 8 times the FP64 oracle's, which solves with the factor at every step (the
 two differ in summation order only, so their distances are of one size)."""
 import numpy as np
 import pytest
@@ -149,3 +150,23 @@ def test_accuracy_on_rows_that_nearly_repeat(br, m, csr):
         e, eo = (float(np.linalg.norm(v - w) / np.linalg.norm(w)) for v in (x, o))
         print(f"near repeats br={br} csr={csr} {what}: {e:.1e}, oracle {eo:.1e}", flush=True)
         assert e <= 8 * eo
+
+
+@pytest.mark.parametrize("br,n,iters", [(1, 5001, 65), (10, 5001, 65), (33, 17000, 9),
+                                        (64, 5002, 9), (100, 20000, 5), (161, 5001, 3)])
+def test_wide_matrices_in_batches_of_any_size(br, n, iters):
+    m, lam = 3 * br + 5, 1e-2
+    rng = np.random.default_rng(br)
+    A, g = rng.standard_normal((m, n)), rng.standard_normal(n)
+    b = A @ rng.standard_normal(n)
+    sol = P.Solver(dev(A), br, lam)
+    sol.solve(dev(b), seed=4, tol=0.0, max_iters=iters, record=True)
+    rec = sol.record()
+    got = sol.backward(dev(g))
+    want = O.backward(A, br, lam, rec["tau"], rec["I"], iters, False, g)
+    print(f"wide adjoint br={br} n={n}", flush=True)
+    for x, w in zip(got, want):
+        assert np.linalg.norm(host(x) - w) < 1e-10 * np.linalg.norm(w)
+    for every in (1, 2, 4):
+        sol.solve(dev(b), seed=4, tol=0.0, max_iters=iters, checkpoint_every=every)
+        assert all(torch.equal(x, y) for x, y in zip(sol.backward(dev(g)), got)), every
