@@ -382,7 +382,8 @@ __device__ __forceinline__ void csr_entry_rows(const int64_t *off, const int64_t
     }
 }
 
-template <typename T, typename V>
+// FAC: the current rows are a gathered set with its factored inverse Msel.
+template <typename T, typename V, bool FAC>
 __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     const int tid = threadIdx.x;
     const T *__restrict__ val = (const T *)p.val;
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     if (p.ctrl->done) return;
     const bool upd = p.ymode != 2 && cnt > 0;
 
-    __shared__ double s_r[CSR_HU * CSR_TPR], s_w[MAXB], s_y[MAXB];
+    __shared__ double s_r[CSR_HU * CSR_TPR], s_w[FAC ? CSR_HU * CSR_TPR : 1], s_y[MAXB];
     __shared__ int64_t s_len[MAXB], s_off[MAXB + 1], s_p0[MAXB];
     __shared__ int64_t n_len[MAXB], n_off[MAXB + 1], n_p0[MAXB];
     __shared__ int32_t e_col[CSR_CHUNK], e_slot[CSR_CHUNK], s_dup[CSR_CHUNK];
@@ -422,7 +423,10 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     int16_t *l_any = (int16_t *)s_dup, *l_ord = l_any + CSR_CHUNK;
 
     // A. row offsets of both row sets; b - Pin or the given y
-    if (tid < CSR_HU * CSR_TPR) s_r[tid] = 0.0;
+    if (tid < CSR_HU * CSR_TPR) {
+        s_r[tid] = 0.0;
+        if (FAC) s_w[tid] = 0.0;
+    }
     if (upd) {
         for (int i = tid; i < cnt; i += CSR_STEP_T) {
             const int64_t row = (p.cur.kind == 1) ? (int64_t)p.cur.idx[i] : cst + i;
@@ -474,7 +478,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
     int er[EU], es[EU], eb[EU], ns[NU];
     uint32_t ek[EU], em[EU];   // arrival number, then rank, in the column; its terms
     V ex[EU], nx[NU];
-    const bool own_y = upd && p.ymode == 0, fac = own_y && p.Msel;
+    const bool own_y = upd && p.ymode == 0;
     const bool entries = __builtin_amdgcn_readfirstlane(tid) >= CSR_HT;   // scalar
     const int t1 = tid - CSR_HT;
     bool multi;
@@ -486,7 +490,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
         int hi = tid / CSR_TPR;
         double hv[CSR_HU];
         auto load_row = [&]() {
-            const double *ph = p.H + blk_hoff(tc, p.q, p.rem, RORBK_CSR_ZCOLS) +
+            const double *ph = (FAC ? p.Msel : p.H + blk_hoff(tc, p.q, p.rem, RORBK_CSR_ZCOLS)) +
                                (int64_t)qd * cnt + (hi < cnt ? hi : 0);
             const int64_t st = (int64_t)CSR_TPR * cnt;
 #pragma unroll
@@ -499,63 +503,63 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
                     }
                 }
         };
-        auto dot_row = [&]() {
+        // row hi of the matrix (PART 0), of what is below its diagonal (1) or
+        // above it (2), times vin
+        auto dot_row = [&](auto part, const double *vin) -> double {
+            constexpr int PART = decltype(part)::value;
             double s0 = 0.0;
 #pragma unroll
             for (int u0 = 0; u0 < CSR_HU; u0 += CSR_HG)
                 if (CSR_TPR * u0 < cnt) {
 #pragma unroll
-                    for (int u = u0; u < u0 + CSR_HG; ++u)
-                        s0 = __builtin_fma(hv[u], s_r[qd + CSR_TPR * u], s0);
-                }
-            s0 = group_sum(s0, CSR_TPR);
-            if (qd == 0 && hi < cnt) s_y[hi] = s0;
-        };
-        // factored inverse: w = D^{-1} X r (the entries below the diagonal, with
-        // the reciprocal pivots on it), then y = X^T w (those above); read as
-        // they are needed, since a row kept for both products spills the
-        // registers of the other half
-        auto dot_factor = [&](auto lower, const double *vin, double *out) {
-#pragma unroll 1
-            for (int i = tid / CSR_TPR; i < MAXB; i += CSR_HT / CSR_TPR) {
-                const double *row = p.Msel + (i < cnt ? i : 0);
-                const double dg = lower.value ? row[(i < cnt ? i : 0) * cnt] : 1.0;
-                double s0 = 0.0;
-#pragma unroll 1
-                for (int j0 = qd; j0 < cnt; j0 += 16 * CSR_TPR) {
-                    double t[16];
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) {
-                        const int j = j0 + CSR_TPR * u;
-                        t[u] = row[(j < cnt ? j : cnt - 1) * cnt];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) {
-                        const int j = j0 + CSR_TPR * u;
-                        const bool in = lower.value ? j < i : (j > i && j < cnt);
-                        s0 = __builtin_fma(in ? t[u] : 0.0, vin[j < cnt ? j : cnt - 1], s0);
+                    for (int u = u0; u < u0 + CSR_HG; ++u) {
+                        const int j = qd + CSR_TPR * u;
+                        const bool in = PART == 0 || (PART == 1 ? j < hi : j > hi);
+                        s0 = __builtin_fma(in ? hv[u] : 0.0, vin[j], s0);
                     }
                 }
-                s0 = group_sum(s0, CSR_TPR);
-                if (qd == 0 && i < cnt) out[i] = (s0 + vin[i]) * dg;
-            }
+            return group_sum(s0, CSR_TPR);
         };
-        if (own_y && !fac) load_row();
+        if (own_y) load_row();
         __syncthreads();
         __syncthreads();
         __syncthreads();
         multi = s_ndup > 0;
         if (multi) __syncthreads();
-        if (fac) {
-            dot_factor(std::true_type{}, s_r, s_w);
-            __syncthreads();
-            dot_factor(std::false_type{}, s_w, s_y);
-        } else if (own_y) {
-            dot_row();
-            if (cnt > CSR_HT / CSR_TPR) {   // uniform
-                hi += CSR_HT / CSR_TPR;
+        constexpr int HR = CSR_HT / CSR_TPR;   // rows at a time
+        if constexpr (FAC) {
+            // w = D^{-1} X r with the reciprocal pivots of the diagonal, then
+            // y = X^T w
+            auto lower = [&]() {
+                const double dg = p.Msel[(int64_t)(hi < cnt ? hi : 0) * (cnt + 1)];
+                const double s0 = dot_row(std::integral_constant<int, 1>{}, s_r);
+                if (qd == 0 && hi < cnt) s_w[hi] = (s0 + s_r[hi]) * dg;
+            };
+            auto upper = [&]() {
+                const double s0 = dot_row(std::integral_constant<int, 2>{}, s_w);
+                if (qd == 0 && hi < cnt) s_y[hi] = s0 + s_w[hi];
+            };
+            lower();
+            if (cnt > HR) {   // uniform
+                hi += HR;
                 load_row();
-                dot_row();
+                lower();
+            }
+            __syncthreads();
+            upper();
+            if (cnt > HR) {
+                hi -= HR;
+                load_row();
+                upper();
+            }
+        } else if (own_y) {
+            const double s0 = dot_row(std::integral_constant<int, 0>{}, s_r);
+            if (qd == 0 && hi < cnt) s_y[hi] = s0;
+            if (cnt > HR) {
+                hi += HR;
+                load_row();
+                const double s1 = dot_row(std::integral_constant<int, 0>{}, s_r);
+                if (qd == 0 && hi < cnt) s_y[hi] = s1;
             }
         }
     } else {
@@ -657,7 +661,7 @@ __global__ __launch_bounds__(CSR_STEP_T) void k_csr_step(CsrStepP p) {
                     ek[u] = (uint32_t)rank;
                 }
         }
-        if (fac) __syncthreads();
+        if (FAC) __syncthreads();
     }
     __syncthreads();
     if (upd && p.gb && !entries) {
@@ -796,13 +800,16 @@ hipError_t launch_step_csr(const rorbk_handle_s *h, const StepArgs &a, hipStream
     p.nxt = a.nxt;
     p.Pout = a.Pout;
     p.ctrl = h->d_ctrl;
-    if (a.vec == VEC_F64) {
-        if (a.dt != RORBK_F64) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_csr_step<double, double>), dim3(1), dim3(CSR_STEP_T), 0, s, p);
-    } else {
-        if (a.dt != RORBK_F32) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_csr_step<float, float>), dim3(1), dim3(CSR_STEP_T), 0, s, p);
-    }
+    const bool f64 = a.vec == VEC_F64, fac = a.ymode == 0 && a.Msel;
+    if (a.dt != (f64 ? RORBK_F64 : RORBK_F32)) return hipErrorInvalidValue;
+    if (f64 && fac)
+        hipLaunchKernelGGL((k_csr_step<double, double, true>), dim3(1), dim3(CSR_STEP_T), 0, s, p);
+    else if (f64)
+        hipLaunchKernelGGL((k_csr_step<double, double, false>), dim3(1), dim3(CSR_STEP_T), 0, s, p);
+    else if (fac)
+        hipLaunchKernelGGL((k_csr_step<float, float, true>), dim3(1), dim3(CSR_STEP_T), 0, s, p);
+    else
+        hipLaunchKernelGGL((k_csr_step<float, float, false>), dim3(1), dim3(CSR_STEP_T), 0, s, p);
     return hipGetLastError();
 }
 
