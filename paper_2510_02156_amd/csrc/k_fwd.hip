@@ -824,12 +824,16 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
     __shared__ double s_m2[MC][6 * 64 + 8];
     __shared__ V s_x[SWC];
     __shared__ int32_t s_row[64 + 3 * FWD_B], s_slot[64 + 3 * FWD_B];
-    __shared__ int s_ok;
+    __shared__ int s_ok, s_stop;
     double *Lc = lds_a;
     double *s_z = lds_a, *s_y = lds_a + 256;
     V (*s_red)[SWC] = reinterpret_cast<V (*)[SWC]>(lds_a + 1024);
 
-    // the draws (scalar loads) travel with the first vector loads
+    // the draws (scalar loads) travel with the first vector loads.  The stop
+    // flag takes effect behind the first barrier, as wave 0 read it: another
+    // workgroup whose factorisation failed may set it meanwhile, and waves that
+    // disagreed would leave the row tables below unwritten for the others.
+    // (What is loaded before does not depend on it.)
     const int stop = __hip_atomic_load(&p.ctrl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     Blk3 B;
     blocks3(p.tau, p.tau_index, p.q, p.rem, B);
@@ -913,9 +917,10 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
     bool rok = false;
     if (wv == 0) {
         load_gram();
-        if (stop) return;
         put_gram();
+        if (tid == 0) s_stop = stop;
         __syncthreads();
+        if (s_stop) return;
         // (this wave's chain comes first on its SIMD)
         __builtin_amdgcn_s_setprio(3);
         const bool ok = ldl_blk64(Lc, s_yk, K);
@@ -941,7 +946,6 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
         }
         const int32_t iv = p.I[t < K ? t : 0];
         const V xv = x[c0 + (t < wcols ? t : 0)];
-        if (stop) return;
         put_gram();
         if (t < nrows) {   // the update's row tables, greedy rows first
             int l, i;
@@ -951,6 +955,7 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_chain(FwdChainP p) {
             s_slot[t] = (t < K) ? 3 * ZS + t : l * ZS + i;
         }
         __syncthreads();
+        if (s_stop) return;
         // the sampled steps' matrices (two per thread range, as k_fwd_samp3)
         double m2[MC];
         {
