@@ -1190,10 +1190,10 @@ hipError_t launch_big_block_inverses(const rorbk_handle_s *h, const double *Gs, 
     if (bmaxb < 1) bmaxb = 1;
     if (bmaxb > L.k) bmaxb = L.k;
     double *G = nullptr, *Lf = nullptr, *W = nullptr;
-    hipError_t e = hipMallocAsync((void **)&G, sizeof(double) * (size_t)(bmaxb * ms), s);
-    if (e == hipSuccess) e = hipMallocAsync((void **)&Lf, sizeof(double) * (size_t)(bmaxb * ms), s);
+    hipError_t e = malloc_async((void **)&G, sizeof(double) * (size_t)(bmaxb * ms), s);
+    if (e == hipSuccess) e = malloc_async((void **)&Lf, sizeof(double) * (size_t)(bmaxb * ms), s);
     if (e == hipSuccess)
-        e = hipMallocAsync((void **)&W, sizeof(double) * (size_t)(bmaxb * P * TB * TB), s);
+        e = malloc_async((void **)&W, sizeof(double) * (size_t)(bmaxb * P * TB * TB), s);
     for (int64_t t0 = 0; t0 < L.k && e == hipSuccess; t0 += bmaxb) {
         const int batch = (int)((L.k - t0 < bmaxb) ? L.k - t0 : bmaxb);
         hipLaunchKernelGGL(k_big_unpack, dim3((unsigned)((ms + 255) / 256), (unsigned)batch),
@@ -1252,12 +1252,12 @@ static hipError_t col_inverses_typed(const rorbk_handle_s *h, const void *A, int
     if (bmaxb < 1) bmaxb = 1;
     if (bmaxb > L.k) bmaxb = L.k;
     double *G = nullptr, *Lf = nullptr, *W = nullptr, *Gs = nullptr;
-    hipError_t e = hipMallocAsync((void **)&G, sizeof(double) * (size_t)(bmaxb * ms), s);
-    if (e == hipSuccess) e = hipMallocAsync((void **)&Lf, sizeof(double) * (size_t)(bmaxb * ms), s);
+    hipError_t e = malloc_async((void **)&G, sizeof(double) * (size_t)(bmaxb * ms), s);
+    if (e == hipSuccess) e = malloc_async((void **)&Lf, sizeof(double) * (size_t)(bmaxb * ms), s);
     if (e == hipSuccess)
-        e = hipMallocAsync((void **)&W, sizeof(double) * (size_t)(bmaxb * P * TB * TB), s);
+        e = malloc_async((void **)&W, sizeof(double) * (size_t)(bmaxb * P * TB * TB), s);
     if (e == hipSuccess)
-        e = hipMallocAsync((void **)&Gs, sizeof(double) * (size_t)(bmaxb * nchunk * KP), s);
+        e = malloc_async((void **)&Gs, sizeof(double) * (size_t)(bmaxb * nchunk * KP), s);
     const unsigned tiles = (unsigned)(P * (P + 1) / 2);
     for (int64_t t0 = 0; t0 < L.k && e == hipSuccess; t0 += bmaxb) {
         const int batch = (int)((L.k - t0 < bmaxb) ? L.k - t0 : bmaxb);

@@ -13,6 +13,7 @@
 #include <new>
 #include <vector>
 
+#include "block_pool.h"
 #include "rorbk_internal.h"
 
 using namespace rorbk;
@@ -47,16 +48,27 @@ int fail(int code, const char *fmt, ...) {
 size_t dtype_size(int dt) { return dt == RORBK_F64 ? 8 : (dt == RORBK_F32 ? 4 : 2); }
 size_t vec_size(int vec) { return vec == VEC_F64 ? 8 : 4; }
 
+// Device memory of the library: idle blocks of closed handles (block_pool.h)
+// go back to the driver when any of its allocations finds none left.
+int pool_malloc(void **p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return (int)e;
+}
+void pool_free(void *p) { (void)hipFree(p); }
+BlockPool g_pool(pool_malloc, pool_free);   // (constant-initialised, no destructor)
+
 template <typename P>
 int dalloc(P **p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
-    hipError_t e = hipMalloc((void **)p, count * sizeof(P));
-    if (e != hipSuccess) {
-        *p = nullptr;
+    const int e = g_pool.alloc((void **)p, count * sizeof(P));
+    if (e)
         return fail(RORBK_ERR_OOM, "hipMalloc of %zu bytes failed: %s", count * sizeof(P),
-                    hipGetErrorString(e));
-    }
+                    hipGetErrorString((hipError_t)e));
     return RORBK_OK;
 }
 
@@ -66,92 +78,13 @@ void dfree(P *&p) {
     p = nullptr;
 }
 
-// Blocks of device memory kept when a handle is destroyed or a setup is done
-// with its scratch, for the next handle: the driver clears freed device memory
-// before it gives it out again and does not keep up with programs that set up
-// handles one after another (640 MB taken and freed every 4 ms: 0.2 ms a call
-// at first, 28 ms after two seconds; 100000-row CSR handles of 128-row blocks
-// made, used for 4 iterations and closed: 8 to 41 ms each, 3.75 with this).  A block is idle when it is kept and taken out while in use, so
-// threads and streams never share one.  At most KEPT_BYTES in KEPT_BLOCKS
-// blocks; one that KEPT_MISSES requests have passed over, and all of them when
-// the device is out of memory, go back to the driver.
-constexpr size_t KEPT_BYTES = (size_t)2 << 30;
-constexpr size_t KEPT_BLOCKS = 8;
-constexpr int KEPT_MISSES = 16;
-struct Block {
-    char *p;
-    size_t bytes;
-    int dev, misses;
-};
-std::mutex g_kept_mutex;
-std::vector<Block> &kept() {   // never destroyed: the runtime may be gone at exit
-    static std::vector<Block> *v = new std::vector<Block>();
-    return *v;
-}
-
-// Idle block back: kept, or freed where it would pass the bounds.
-void block_put(Block &b) {
-    if (!b.p) return;
-    bool keep = false;
-    try {
-        std::lock_guard<std::mutex> g(g_kept_mutex);
-        size_t sum = b.bytes;
-        for (const Block &k : kept()) sum += k.bytes;
-        if (sum <= KEPT_BYTES && kept().size() < KEPT_BLOCKS) {
-            b.misses = 0;
-            kept().push_back(b);
-            keep = true;
-        }
-    } catch (...) {
-    }
-    if (!keep) (void)hipFree(b.p);
-    b = Block{nullptr, 0, 0, 0};
-}
-
-// A block of at least `bytes` (contents undefined): the smallest kept one that
-// is not more than twice that, else a new one.
 int block_get(Block *out, size_t bytes) {
     int dev = 0;
     HIPCHK(hipGetDevice(&dev));
-    if (bytes == 0) bytes = 1;
-    Block drop[KEPT_BLOCKS];
-    size_t ndrop = 0;
-    *out = Block{nullptr, 0, 0, 0};
-    {
-        std::lock_guard<std::mutex> g(g_kept_mutex);
-        std::vector<Block> &v = kept();
-        size_t best = v.size();
-        for (size_t i = 0; i < v.size(); ++i)
-            if (v[i].dev == dev && v[i].bytes >= bytes && v[i].bytes / 2 <= bytes &&
-                (best == v.size() || v[i].bytes < v[best].bytes))
-                best = i;
-        if (best < v.size()) {
-            *out = v[best];
-            v.erase(v.begin() + (std::ptrdiff_t)best);
-        }
-        for (size_t i = v.size(); i-- > 0;)
-            if (++v[i].misses >= KEPT_MISSES) {
-                drop[ndrop++] = v[i];
-                v.erase(v.begin() + (std::ptrdiff_t)i);
-            }
-    }
-    for (size_t i = 0; i < ndrop; ++i) (void)hipFree(drop[i].p);
-    if (out->p) return RORBK_OK;
-    char *p = nullptr;
-    hipError_t e = hipMalloc((void **)&p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> g(g_kept_mutex);
-            for (ndrop = 0; ndrop < kept().size(); ++ndrop) drop[ndrop] = kept()[ndrop];
-            kept().clear();
-        }
-        for (size_t i = 0; i < ndrop; ++i) (void)hipFree(drop[i].p);
-        e = hipMalloc((void **)&p, bytes);
-    }
-    if (e != hipSuccess)
-        return fail(RORBK_ERR_OOM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-    *out = Block{p, bytes, dev, 0};
+    const int e = g_pool.get(out, bytes, dev);
+    if (e)
+        return fail(RORBK_ERR_OOM, "hipMalloc of %zu bytes failed: %s", bytes,
+                    hipGetErrorString((hipError_t)e));
     return RORBK_OK;
 }
 
@@ -354,7 +287,7 @@ void destroy_all(rorbk_handle_s *h) {
         int dev = -1;
         Block b = {h->d_arena, h->arena_bytes, h->arena_dev, 0};
         if (hipGetDevice(&dev) == hipSuccess && dev == b.dev && hipDeviceSynchronize() == hipSuccess)
-            block_put(b);
+            g_pool.put(&b);
         else
             (void)hipFree(b.p);
         h->d_arena = nullptr;
@@ -682,6 +615,15 @@ int prepare_tau(rorbk_handle_s *h, uint64_t seed, int64_t start_iter, int64_t it
 
 }  // namespace
 
+hipError_t rorbk::malloc_async(void **p, size_t bytes, hipStream_t s) {
+    hipError_t e = hipMallocAsync(p, bytes, s);
+    if (e != hipSuccess && g_pool.trim() > 0) {
+        (void)hipGetLastError();
+        e = hipMallocAsync(p, bytes, s);
+    }
+    return e;
+}
+
 // ======================================================================= ABI
 
 extern "C" {
@@ -975,7 +917,7 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
                                                                     scratch, d_fail, s));
         hipError_t e3 = hipMemcpyAsync(&hfail, d_fail, 4, hipMemcpyDeviceToHost, s);
         hipError_t e4 = hipStreamSynchronize(s);
-        if (e4 == hipSuccess) block_put(sb);   // idle: the stream has been waited for
+        if (e4 == hipSuccess) g_pool.put(&sb);   // idle: the stream has been waited for
         else (void)hipFree(sb.p);
         if (le != hipSuccess)
             return bail(fail(RORBK_ERR_HIP, "proposal setup failed: %s", hipGetErrorString(le)));

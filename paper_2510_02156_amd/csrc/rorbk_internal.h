@@ -198,6 +198,10 @@ struct rorbk_handle_s {
 
 namespace rorbk {
 
+// hipMallocAsync; where it fails the idle blocks of closed handles are given
+// back and it is tried once more.
+hipError_t malloc_async(void **p, size_t bytes, hipStream_t s);
+
 // ---------------------------------------------------------------- launchers
 // Each returns hipSuccess or the launch error.  `vec` is VecType; `dt` is the
 // storage dtype of the matrix pointer passed.
