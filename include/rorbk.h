@@ -158,10 +158,20 @@ int ror_bk_solve(rorbk_handle h, const void *b, void *x, uint64_t seed,
 int ror_bk_backward(rorbk_handle h, const void *grad_x, void *grad_b,
                     void *grad_x0);
 
-/* Release every device buffer the handle owns (the stored block inverses of
- * Section 3.1, the proposal, workspaces and records); h may be NULL.  The
- * caller's matrix and vectors are not touched. */
+/* End the handle: waits for its stream and takes back every device buffer the
+ * handle owns (the stored block inverses of Section 3.1, the proposal,
+ * workspaces and records); h may be NULL.  The caller's matrix and vectors are
+ * not touched.  The handle's main block of memory, and a setup's scratch, are
+ * kept idle for the next setup while all idle blocks stay within 2 GiB and 8
+ * blocks; beyond that they are freed.  An idle block goes back to the driver
+ * when 16 setups' requests have passed it over, all of them when an allocation
+ * of the library finds no memory, and by ror_bk_trim. */
 int ror_bk_destroy(rorbk_handle h);
+
+/* Give the idle device memory that closed handles left with the library back
+ * to the driver, on every device (library memory, not a step of the method).
+ * Handles that are open keep theirs.  May be called from any thread. */
+int ror_bk_trim(void);
 
 /* ------------------------------------------------- inspection and replay -- */
 

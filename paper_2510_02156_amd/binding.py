@@ -34,6 +34,7 @@ RORBK_NOALLOC_SCRATCH_BYTES = 16777216
 
 EXPORTS = [
     "ror_bk_partition", "ror_bk_setup", "ror_bk_solve", "ror_bk_backward", "ror_bk_destroy",
+    "ror_bk_trim",
     "ror_bk_get_sizes", "ror_bk_get_setup", "ror_bk_set_proposal",
     "ror_bk_get_block_inverse", "ror_bk_get_form", "ror_bk_sample", "ror_bk_topk", "ror_bk_residual",
     "ror_bk_residual_noalloc", "ror_bk_get_record", "ror_bk_set_replay", "ror_bk_set_refine",
@@ -89,6 +90,7 @@ def lib():
                                        C.POINTER(rorbk_info)]),
             "ror_bk_backward": (C.c_int, [P, P, P, P]),
             "ror_bk_destroy": (C.c_int, [P]),
+            "ror_bk_trim": (C.c_int, []),
             "ror_bk_get_sizes": (C.c_int, [P, P, P, P]),
             "ror_bk_get_setup": (C.c_int, [P, P, P, P, P]),
             "ror_bk_set_proposal": (C.c_int, [P, P]),
@@ -223,6 +225,11 @@ def ror_bk_backward(h, grad_x, grad_b, grad_x0):
 def ror_bk_destroy(h):
     if h:
         _check(lib().ror_bk_destroy(h), "ror_bk_destroy")
+
+
+def ror_bk_trim():
+    """Give the idle device memory of closed handles back to the driver."""
+    _check(lib().ror_bk_trim(), "ror_bk_trim")
 
 
 def ror_bk_get_sizes(h):

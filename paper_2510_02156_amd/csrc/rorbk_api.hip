@@ -653,6 +653,12 @@ int ror_bk_destroy(rorbk_handle h) {
     return RORBK_OK;
 }
 
+int ror_bk_trim(void) {
+    g_msg[0] = 0;
+    (void)g_pool.trim();
+    return RORBK_OK;
+}
+
 int ror_bk_partition(int64_t m, int64_t block_rows, int64_t *offsets_host, int64_t *k) {
     g_msg[0] = 0;
     if (!k) return fail(RORBK_ERR_INVALID_ARG, "k pointer is NULL");
