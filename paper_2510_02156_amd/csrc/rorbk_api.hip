@@ -65,6 +65,8 @@ template <typename P>
 int dalloc(P **p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
+    if (count > SIZE_MAX / sizeof(P))
+        return fail(RORBK_ERR_OOM, "a buffer of %zu entries of %zu bytes", count, sizeof(P));
     const int e = g_pool.alloc((void **)p, count * sizeof(P));
     if (e)
         return fail(RORBK_ERR_OOM, "hipMalloc of %zu bytes failed: %s", count * sizeof(P),
@@ -206,6 +208,10 @@ void plan_layout(Layout &L, bool col) {
     L.nch_s = (int32_t)((L.k + L.bpc - 1) / L.bpc);
 }
 
+// Most iterations, draws or outer steps a call takes: more would not fit any
+// device's memory, and sizes formed from these fit 64 bits.
+constexpr int64_t MAX_COUNT = (int64_t)1 << 40;
+
 // Buffers made at a handle's first solve or adjoint: from the spare end of its
 // block while that lasts (a first driver call of a process or after a pause
 // takes 0.3 to 0.5 ms: 40009 x 1501 BF16, first solve of a handle 2.0 ms
@@ -214,11 +220,14 @@ void plan_layout(Layout &L, bool col) {
 constexpr size_t SPARE_BYTES = (size_t)4 << 20;
 template <typename P>
 int dalloc(rorbk_handle_s *h, P **p, size_t count) {
-    const size_t bytes = (count * sizeof(P) + 255) / 256 * 256;
-    if (count > 0 && h->d_arena && bytes <= h->arena_bytes - h->arena_used) {
-        *p = (P *)(h->d_arena + h->arena_used);
-        h->arena_used += bytes;
-        return RORBK_OK;
+    // (the division keeps sizes that do not fit 64 bits out)
+    if (count > 0 && h->d_arena && count <= (h->arena_bytes - h->arena_used) / sizeof(P)) {
+        const size_t bytes = (count * sizeof(P) + 255) / 256 * 256;
+        if (bytes <= h->arena_bytes - h->arena_used) {
+            *p = (P *)(h->d_arena + h->arena_used);
+            h->arena_used += bytes;
+            return RORBK_OK;
+        }
     }
     return dalloc(p, count);
 }
@@ -320,14 +329,20 @@ hipError_t gram(const rorbk_handle_s *h, const void *A, int dt, int aligned, con
 int ensure_solve_buffers(rorbk_handle_s *h, int64_t iters, bool record_I, int64_t ckpt_slots,
                          int vec) {
     const Layout &L = h->L;
+    if (iters > MAX_COUNT || (ckpt_slots > 0 && ckpt_slots > INT64_MAX / 8 / L.n))
+        return fail(RORBK_ERR_OOM, "records of %lld iterations", (long long)iters);
+    // (a capacity is zero while its buffer is being replaced: the allocation
+    // may fail, and a later, smaller solve must not take it for there)
     if (h->tau_cap < iters) {
         dfree(h, h->d_tau);
+        h->tau_cap = 0;
         CHK(dalloc(h, &h->d_tau, (size_t)(3 * iters)));
         h->tau_cap = iters;
     }
     if (h->rec_cap < iters || (record_I && !h->d_recI)) {
         dfree(h, h->d_recI);
         dfree(h, h->d_recR);
+        h->rec_cap = 0;
         CHK(dalloc(h, &h->d_recR, (size_t)iters));
         if (record_I) CHK(dalloc(h, &h->d_recI, (size_t)(iters * L.K)));
         h->rec_cap = iters;
@@ -336,11 +351,13 @@ int ensure_solve_buffers(rorbk_handle_s *h, int64_t iters, bool record_I, int64_
         const int64_t need = ckpt_slots * L.n * (int64_t)vec_size(vec);
         if (h->ckpt_cap < need) {
             dfree(h, h->d_ckpt);
+            h->ckpt_cap = 0;
             CHK(dalloc(h, (char **)&h->d_ckpt, (size_t)need));
             h->ckpt_cap = need;
         }
         if (h->chain && h->ckst_cap < ckpt_slots) {
             dfree(h, h->d_ckst);
+            h->ckst_cap = 0;
             CHK(dalloc(h, &h->d_ckst, (size_t)(ckpt_slots * CKST_DOUBLES)));
             h->ckst_cap = ckpt_slots;
         }
@@ -906,6 +923,8 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
     {
         const int64_t kp = bmax * (bmax + 1) / 2;
         const int64_t len = std::max(setup_proposal_scratch(k, L.n, h->ncu), h->col ? 0 : k * kp);
+        if ((uint64_t)len > SIZE_MAX / sizeof(double))
+            return bail(fail(RORBK_ERR_OOM, "setup scratch of %lld doubles", (long long)len));
         Block sb;
         rc = block_get(&sb, sizeof(double) * (size_t)len);
         if (rc) return bail(rc);
@@ -999,6 +1018,7 @@ int ror_bk_sample(rorbk_handle h, uint64_t seed, int64_t j0, int64_t count, int3
     if (!h || !tau_host || count < 0 || j0 < 0)
         return fail(RORBK_ERR_INVALID_ARG, "bad sample arguments");
     if (count == 0) return RORBK_OK;
+    if (count > MAX_COUNT) return fail(RORBK_ERR_OOM, "%lld draws", (long long)count);
     int32_t *d = nullptr;
     CHK(dalloc(&d, (size_t)(3 * count)));
     hipError_t e1 = launch_sample(seed, j0, count, h->d_W, h->L.k, d, h->stream);
@@ -1078,6 +1098,9 @@ int ror_bk_fabgmres(rorbk_handle h, const double *b, double *x, uint64_t seed, d
     const Layout &L = h->L;
     if (L.dtype != RORBK_F64)
         return fail(RORBK_ERR_UNSUPPORTED, "flexible AB-GMRES runs on FP64 storage");
+    if (max_outer > INT32_MAX || inner_iters > MAX_COUNT)
+        return fail(RORBK_ERR_OOM, "%lld outer steps of %lld iterations", (long long)max_outer,
+                    (long long)inner_iters);
     hipStream_t s = h->stream;
     const int64_t m = L.m, n = L.n, M1 = max_outer + 1;
     h->rec_valid = 0;
@@ -1403,9 +1426,9 @@ int ror_bk_solve(rorbk_handle h, const void *b, void *x, uint64_t seed, double t
         HIPCHK(hipStreamSynchronize(s));
         bnorm2 = h->h_ctrl[0].bnorm2;
         const double thr = tol * std::sqrt(bnorm2);
-        if (!h->d_rhs32) {
-            char *p1 = nullptr, *p2 = nullptr;
-            CHK(dalloc(h, &p1, (size_t)(8 * L.m)));
+        if (!h->d_d32) {
+            char *p1 = (char *)h->d_rhs32, *p2 = nullptr;
+            if (!p1) CHK(dalloc(h, &p1, (size_t)(8 * L.m)));
             h->d_rhs32 = p1;
             CHK(dalloc(h, &p2, (size_t)(8 * L.n)));
             h->d_d32 = p2;

@@ -1,6 +1,7 @@
 """Device memory of closed handles: given back by ror_bk_trim and at the pool's
-bounds (the bounds themselves: test_block_pool.py), and handles made and closed
-by two threads at once, each on its own stream."""
+bounds (the bounds themselves: test_block_pool.py), handles made and closed by
+two threads at once, each on its own stream, and handles that go on after a call
+that asked for more memory than there is."""
 import threading
 
 import numpy as np
@@ -12,6 +13,7 @@ if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
 import paper_2510_02156_amd as P  # noqa: E402
+from paper_2510_02156_amd import binding  # noqa: E402
 from tests.gpu_util import DEV, dev  # noqa: E402
 
 MB = 1 << 20
@@ -79,3 +81,30 @@ def test_handles_of_two_threads():
     for t in ts:
         t.join()
     assert not errors, errors
+
+
+@pytest.mark.parametrize("iters", [1 << 36, 1537228672809129301, (1 << 63) - 1])
+@pytest.mark.parametrize("record,every", [(False, 0), (True, 0), (False, 1)])
+def test_handle_after_running_out_of_memory(iters, record, every):
+    """12 bytes of draws an iteration: 0.8 TB, 2^64 - 4 bytes (which round up to
+    2^64) and more than 64 bits hold."""
+    A = torch.randn(300, 70, dtype=torch.float64, device=DEV)
+    b = A.sum(1)
+    sol, other = P.Solver(A, 20, 1e-1), P.Solver(A, 20, 1e-1)
+    sol.solve(b, seed=1, tol=0.0, max_iters=3, record=record, checkpoint_every=every)
+    with pytest.raises(P.RorBkError) as e:
+        sol.solve(b, seed=1, tol=0.0, max_iters=iters, record=record, checkpoint_every=every)
+    assert e.value.code == P.RORBK_ERR_OOM
+    got = sol.solve(b, seed=1, tol=0.0, max_iters=9, record=record, checkpoint_every=every)[0]
+    want = other.solve(b, seed=1, tol=0.0, max_iters=9, record=record, checkpoint_every=every)[0]
+    assert torch.equal(got, want)
+    if record or every:
+        for x, y in zip(sol.backward(got), other.backward(got)):
+            assert torch.equal(x, y)
+    with pytest.raises(P.RorBkError) as e:
+        sol.fabgmres(b, max_outer=iters, inner_iters=2)
+    assert e.value.code == P.RORBK_ERR_OOM
+    out = np.zeros(3, dtype=np.int32)         # never written: the call is refused
+    with pytest.raises(P.RorBkError) as e:
+        binding._check(P.lib().ror_bk_sample(sol.h, 1, 0, iters, out.ctypes.data), "ror_bk_sample")
+    assert e.value.code == P.RORBK_ERR_OOM
