@@ -255,15 +255,19 @@ void free_solve_buffers(rorbk_handle_s *h) {
 // block (thirty separate allocations took 0.3 ms to make and to free).
 struct Arena {
     struct Req { void **p; size_t off; };
-    Req req[48];
+    static constexpr int MAX_REQ = 48;
+    Req req[MAX_REQ];
     int count = 0;
     size_t bytes = 0;
     template <typename P>
     void add(P **p, int64_t n) {
-        req[count++] = {(void **)p, bytes};
+        if (count < MAX_REQ) req[count] = {(void **)p, bytes};
+        ++count;   // (past the table: alloc refuses)
         bytes += ((size_t)(n > 0 ? n : 1) * sizeof(P) + 255) / 256 * 256;
     }
     int alloc(rorbk_handle_s *h) {
+        if (count > MAX_REQ)
+            return fail(RORBK_ERR_UNSUPPORTED, "%d buffers in a table of %d", count, MAX_REQ);
         Block b;
         CHK(block_get(&b, bytes + SPARE_BYTES));
         h->d_arena = b.p;
