@@ -296,10 +296,13 @@ void destroy_all(rorbk_handle_s *h) {
         for (int j = 0; j < 2; ++j)
             if (h->evr[i][j]) (void)hipEventDestroy(h->evr[i][j]);
     if (h->d_arena) {
-        // freeing memory waits for the device; keeping it has to as well
+        // idle once the handle's stream, which has all its work, has been waited
+        // for (a device-wide wait would also meet other streams, a capture of
+        // one of them among these); else freeing waits by itself
         int dev = -1;
         Block b = {h->d_arena, h->arena_bytes, h->arena_dev, 0};
-        if (hipGetDevice(&dev) == hipSuccess && dev == b.dev && hipDeviceSynchronize() == hipSuccess)
+        if (hipGetDevice(&dev) == hipSuccess && dev == b.dev &&
+            hipStreamSynchronize(h->stream) == hipSuccess)
             g_pool.put(&b);
         else
             (void)hipFree(b.p);
