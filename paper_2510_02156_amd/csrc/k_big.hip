@@ -153,13 +153,15 @@ __device__ bool tile_inverse32(double (*S)[TB + 1], double (*Wl)[TB + 1]) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) sE[li * 16 + 4 * q + lk] = e1[q];
         wsync();
-        dvec4 y = {0.0, 0.0, 0.0, 0.0}, v;
+        dvec4 y = {0.0, 0.0, 0.0, 0.0}, u = y, v;
 #pragma unroll
         for (int q = 0; q < 4; ++q) y = __builtin_amdgcn_mfma_f64_16x16x4f64(e1[q], t12[q], y, 0, 0, 0);
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = -y[q] * rd[4 * q + lk];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) t22 = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q], y[q], t22, 0, 0, 0);
+        for (int q = 0; q < 4; ++q) u = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q], y[q], u, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t22[q] += u[q];   // one rounding at the size of A_22
         // -(Y^T D_1^{-1}) E_1 in the shadow of the row turn of A_22
         dvec4 b = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll

@@ -9,7 +9,11 @@
 // tile in registers (lb_tile, ldl_blk.h) and leaves E_p^T in its place; the
 // waves form W_J = E_p T_pJ; then T_IJ -= W_I^T D_p^{-1} W_J on FP64 MFMA, wave
 // 0 taking the next diagonal tile and going on to eliminate it while the
-// others update the rest.  All operands are read as rows, the layout the MFMA
+// others update the rest.  The sixteen terms of a product are summed by themselves
+// and added to T_IJ once: with T_IJ as the accumulator each of the four MFMAs
+// rounds at its size, which showed where rows nearly repeat and a pivot is a
+// small difference (160 rows in pairs 1e-4 apart: x 1.5 to 1.7 times further from
+// the exact one).  All operands are read as rows, the layout the MFMA
 // results are written in, so nothing is transposed; only the backward pass
 // reads columns.  What bounds it is the chain of eliminations, 1.9 us per tile
 // row with its two barriers; the products fit beside it.
@@ -157,19 +161,19 @@ __device__ __forceinline__ bool wl_factor(double *T, double *rd, double *z) {
             if (I >= n) break;
             const double *wi = Tp + (I + 1) * WT, *wj = Tp + (J + 1) * WT;
             double *t = T + wl_tile(P, p + 1 + I, p + 1 + J);
-            double av[4], bv[4];
-            dvec4 acc;
+            double av[4], bv[4], tv[4];
+            dvec4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 av[q] = -wi[at[q]] * r[q];
                 bv[q] = wj[at[q]];
-                acc[q] = t[at[q]];
+                tv[q] = t[at[q]];
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q], bv[q], acc, 0, 0, 0);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) t[at[q]] = acc[q];
+            for (int q = 0; q < 4; ++q) t[at[q]] = tv[q] + acc[q];
             if (wv == 0) break;
             J += NR;
         }
