@@ -128,7 +128,8 @@ int ror_bk_partition(int64_t m, int64_t block_rows, int64_t *offsets_host, int64
  * with its running sums W, and the inverse (A_t A_t^T + lambda I)^{-1} of every
  * block.  lambda >= 0 (the paper uses 1e-6 * rows per block; lambda = 0 needs
  * every block to have full row rank, else RORBK_ERR_NOT_SPD).
- * stream: a hipStream_t or NULL.  On success *out owns all device workspaces. */
+ * stream: a hipStream_t or NULL.  On success *out owns all device workspaces,
+ * at least 4 MiB.  RORBK_ERR_OOM if they do not fit the device. */
 int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda,
                  void *stream, rorbk_handle *out);
 

@@ -143,7 +143,7 @@ struct rorbk_handle_s {
     double *d_XG;             // fused path: cross-Grams, two slots [2][3][bmax][bmax]
     double *d_z3;             // fused path: z = b_S - A_S x of the next three blocks
     int32_t chain;            // chain form of the fused path (K <= 64, n <= 4096)
-    double *d_C;              // chain form: A_{S'} A_I^T, [3 * FWD_B][64]
+    double *d_C;              // chain form: A_{S'} A_I^T, [nch_c][64][3 * RORBK_FWD_MAX_BLOCK]
     uint32_t *d_fwdcnt;       // fused path: greedy workgroups done, 0 between launches
     double *d_axp;            // residual partial products [nseg][m]
     void *d_r;                // residual (vector type)
