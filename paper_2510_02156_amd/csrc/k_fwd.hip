@@ -769,9 +769,9 @@ __global__ __launch_bounds__(FWD_T) void k_fwd_samp3(FwdSamp3P p) {
 // at 6 to 8 us the loads decided, so they are spread as many as the registers
 // hold (a select or a clamped address per load cost more than the memory) and
 // C comes in at most two chunks (four made the Grams 0.8 us faster and this
-// kernel 6 us slower at 2000 columns).  Per launch, stamps inside a timing
-// copy: 100000 x 2000, b = 64: 21 us (28); 20000 x 1000, b = 50: 17.5 us (26);
-// 2000 x 200, b = 20: 9.2 us (20).
+// kernel 6 us slower at 2000 columns).  Per launch, kernel trace: 100000 x 2000,
+// b = 64: 23.1 us (28.6); 20000 x 1000, b = 50: 18.3 us (26); 2000 x 200, b = 20:
+// 11.0 us (20.5).
 struct FwdChainP {
     const void *A;
     int64_t ld, n, q, rem;
