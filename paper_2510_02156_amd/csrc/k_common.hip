@@ -1029,9 +1029,12 @@ hipError_t launch_block_inverses_from_grams(const rorbk_handle_s *h, const doubl
 }
 
 // The nch chunks of `sets` packed Grams (KP entries each) summed in chunk order
-// into the first: an entry a thread, eight loads in flight, so that the factor
-// kernel's few waves have one chunk to load (64 chunks one after another there
-// would be a memory round trip each).
+// into the first: an entry a thread, eight loads in flight.  wl_load takes a
+// memory round trip per chunk and four rows of a wave, so from three chunks on
+// the chunks are summed here first (iteration with the sums there and here, us:
+// 2 chunks, 65 to 161 rows, FP64 and FP32: within 2 either way; 4 chunks, 161 rows
+// FP64 297 and 288; 32 chunks, 65 rows 181 and 133, 161 rows 478 and 363; 64 chunks,
+// 161 rows 882 and 646).
 __global__ __launch_bounds__(64) void k_sum_chunks(double *__restrict__ G, int nch, int64_t KP,
                                                    const Ctrl *__restrict__ ctrl) {
     if (ctrl->done) return;
@@ -1051,6 +1054,13 @@ __global__ __launch_bounds__(64) void k_sum_chunks(double *__restrict__ G, int n
     g[0] = v;
 }
 
+static hipError_t sum_chunks(const rorbk_handle_s *h, double *G, int nch, int64_t KP, int sets,
+                             hipStream_t s) {
+    hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((KP + 63) / 64), (unsigned)sets), dim3(64), 0,
+                       s, G, nch, KP, (const Ctrl *)h->d_ctrl);
+    return hipGetLastError();
+}
+
 // (G_t + lambda I)^{-1} of `sets` K x K Grams of nch packed chunks each, K <=
 // MAXB (the chunks are summed in place), in the factored
 // form (wl_put_factor) at M + t K (K + zc).
@@ -1059,9 +1069,7 @@ hipError_t launch_factor_sets(const rorbk_handle_s *h, double *G, int K, int nch
                               hipStream_t s) {
     const int64_t KP = (int64_t)K * (K + 1) / 2;
     if (nch > 1) {
-        hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((KP + 63) / 64), (unsigned)sets), dim3(64),
-                           0, s, G, nch, KP, (const Ctrl *)h->d_ctrl);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = sum_chunks(h, G, nch, KP, sets, s);
         if (e != hipSuccess) return e;
     }
     block_inverse_p<1, true>(G, nch * KP, sets, K, K, 0, h->L.zc, h->lambda, M, nullptr,
@@ -1070,18 +1078,18 @@ hipError_t launch_factor_sets(const rorbk_handle_s *h, double *G, int K, int nch
 }
 
 template <int P>
-static void chol_wg_p(const rorbk_handle_s *h, const double *Gpart, int K, const double *rI,
-                      const double *Pin, double *y, hipStream_t s) {
+static void chol_wg_p(const rorbk_handle_s *h, const double *Gpart, int nch, int K,
+                      const double *rI, const double *Pin, double *y, hipStream_t s) {
     const Layout &L = h->L;
     if ((K + 15) / 16 == P)
-        hipLaunchKernelGGL(k_chol_wg<P>, dim3(1), dim3(64 * CW_NW), 0, s, Gpart, (int)L.nch_g, K,
+        hipLaunchKernelGGL(k_chol_wg<P>, dim3(1), dim3(64 * CW_NW), 0, s, Gpart, nch, K,
                            h->lambda, rI, Pin, (int)L.nch_u, (int)L.bmax, y, h->d_ctrl);
     else if constexpr (P < WL_MAXP)
-        chol_wg_p<P + 1>(h, Gpart, K, rI, Pin, y, s);
+        chol_wg_p<P + 1>(h, Gpart, nch, K, rI, Pin, y, s);
 }
 
-hipError_t launch_chol_solve(const rorbk_handle_s *h, const double *Gpart, int K,
-                             const double *rI, const double *Pin, double *y, hipStream_t s) {
+hipError_t launch_chol_solve(const rorbk_handle_s *h, double *Gpart, int K, const double *rI,
+                             const double *Pin, double *y, hipStream_t s) {
     const Layout &L = h->L;
     if (K > MAXB) {
         // the handle holds the blocked factorisation's buffers for every
@@ -1090,7 +1098,13 @@ hipError_t launch_chol_solve(const rorbk_handle_s *h, const double *Gpart, int K
         return launch_big_chol_solve(h, Gpart, K, rI, Pin, y, s);
     }
     if (K > 64) {
-        chol_wg_p<5>(h, Gpart, K, rI, Pin, y, s);
+        int nch = (int)L.nch_g;
+        if (nch > 2) {   // (see k_sum_chunks)
+            const hipError_t e = sum_chunks(h, Gpart, nch, (int64_t)K * (K + 1) / 2, 1, s);
+            if (e != hipSuccess) return e;
+            nch = 1;
+        }
+        chol_wg_p<5>(h, Gpart, nch, K, rI, Pin, y, s);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_chol_wave, dim3(1), dim3(256), 0, s, Gpart, L.nch_g, K, h->lambda, rI,

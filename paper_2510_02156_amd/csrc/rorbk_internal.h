@@ -289,10 +289,10 @@ struct SelectArgs {
 };
 hipError_t launch_select(const rorbk_handle_s *h, const SelectArgs &a, hipStream_t s);
 
-// rhs: rI (forward) or -(sum of partials) (adjoint)
-hipError_t launch_chol_solve(const rorbk_handle_s *h, const double *Gpart, int K,
-                             const double *rI, const double *Pin, double *y,
-                             hipStream_t s);
+// rhs: rI (forward) or -(sum of partials) (adjoint); the Gram's chunks may be
+// summed in place
+hipError_t launch_chol_solve(const rorbk_handle_s *h, double *Gpart, int K, const double *rI,
+                             const double *Pin, double *y, hipStream_t s);
 
 hipError_t launch_cast_f64_to_f32(const double *src, float *dst, int64_t n,
                                   hipStream_t s);
