@@ -803,20 +803,60 @@ __global__ __launch_bounds__(256) void k_gram32(const T *__restrict__ A, int64_t
     const dvec4 z4 = {0.0, 0.0, 0.0, 0.0};
     dvec4 acc[2][2] = {{z4, z4}, {z4, z4}};
     const uvec4 zu = {0u, 0u, 0u, 0u};
+    const bool tiny = !AL && wb < VW;   // uniform: no whole vector in the row
     for (int64_t c = wa; c < wb; c += 4 * E * U) {
         uvec4 xa[U][2][NL], xb[U][2][NL];
+        if (tiny) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t col = c + (int64_t)u * 4 * E + (int64_t)g * E;
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int h = 0; h < NL; ++h) {
-                const int64_t cc = col + h * VW;
+                for (int h = 0; h < NL; ++h)
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; ++s2) xa[u][s2][h] = xb[u][s2][h] = zu;
+            if (g == 0) {
 #pragma unroll
                 for (int s2 = 0; s2 < 2; ++s2) {
-                    xa[u][s2][h] = load_gram_sel<T, AL>(pa[s2], cc, wb, va[s2], pa[s2], wa);
-                    xb[u][s2][h] = load_gram_sel<T, AL>(pb[s2], cc, wb, !same && vb[s2], pb[s2],
-                                                               wa);
+                    xa[0][s2][0] = load_raw<T, false>(pa[s2], 0, wb);
+                    xb[0][s2][0] = load_raw<T, false>(pb[s2], 0, wb);
                 }
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t col = c + (int64_t)u * 4 * E + (int64_t)g * E;
+#pragma unroll
+                for (int h = 0; h < NL; ++h) {
+                    const int64_t cc = col + h * VW;
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; ++s2) {
+                        xa[u][s2][h] = load_gram<T, AL>(pa[s2], cc, wb, va[s2], pa[s2], wa);
+                        xb[u][s2][h] =
+                            load_gram<T, AL>(pb[s2], cc, wb, !same && vb[s2], pb[s2], wa);
+                    }
+                }
+            }
+        }
+        if (!AL && !tiny) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t cu = c + (int64_t)u * 4 * E, col = cu + (int64_t)g * E;
+                const bool past = cu >= wb;
+                if (!past && cu + 4 * E > wb) {
+#pragma unroll
+                    for (int h = 0; h < NL; ++h)
+#pragma unroll
+                        for (int s2 = 0; s2 < 2; ++s2) {
+                            xa[u][s2][h] = tail_shift<T>(xa[u][s2][h], col + h * VW, wb);
+                            xb[u][s2][h] = tail_shift<T>(xb[u][s2][h], col + h * VW, wb);
+                        }
+                }
+#pragma unroll
+                for (int h = 0; h < NL; ++h)
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; ++s2) {
+                        xa[u][s2][h] = past ? zu : xa[u][s2][h];
+                        xb[u][s2][h] = past ? zu : xb[u][s2][h];
+                    }
             }
         }
 #pragma unroll

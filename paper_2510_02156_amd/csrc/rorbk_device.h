@@ -173,27 +173,25 @@ __device__ __forceinline__ uvec4 load_raw_sel(const T *__restrict__ row, int64_t
     return g ? w : z;
 }
 
-// load_raw_sel for the Gram kernels, whose lanes read pieces of 16 different
-// rows: FP64 rows of 8-byte alignment take two 8-byte loads there, as 16-byte
-// ones that start between two 16-byte words cost such a wave more (block Grams
-// of 300 x 2999: 610 us, 327 with the two; of 11 x 7591: 130 and 61; steps and
-// the residual, whose lanes read along a row, gain from the wide ones: 120-row
-// steps of 1501 columns 57 us with 8-byte loads, 41 with them).
+// load_raw_sel for the Gram kernels, whose steps read many rows: aligned rows
+// are masked here by selects; others are left as read, so that the loads of a
+// step go out together (behind each load of a row's end would stand a branch
+// that waits for it), and the caller clears what was not asked for and moves
+// the end of the row with tail_shift.  lim >= VW there.  Lanes that ask for
+// nothing read (srow, sc): one address for many lanes costs less than many.
+// Block Grams of 31 x 2998 FP32 46 us with a branch at each load, 31 so; 31 x
+// 2999 FP64 61 (two 8-byte loads each) and 38; the greedy Grams of one chain
+// iteration on those 14 and 11, 21 and 14.
 template <typename T, bool ALIGNED>
-__device__ __forceinline__ uvec4 load_gram_sel(const T *__restrict__ row, int64_t c, int64_t lim,
-                                               bool ok, const T *__restrict__ srow, int64_t sc) {
-    if constexpr (!ALIGNED && sizeof(T) == 8) {
-        const bool g = ok && c < lim;
-        const double *p = g ? row : srow;
-        const int64_t cc = g ? c : sc;
-        double v[2] = {p[cc], 0.0};
-        if (cc + 1 < lim) v[1] = p[cc + 1];
-        if (!g) v[0] = v[1] = 0.0;
-        uvec4 w;
-        __builtin_memcpy(&w, v, 16);
-        return w;
+__device__ __forceinline__ uvec4 load_gram(const T *__restrict__ row, int64_t c, int64_t lim,
+                                           bool ok, const T *__restrict__ srow, int64_t sc) {
+    constexpr int VW = Tr<T>::VW;
+    if constexpr (ALIGNED) {
+        return load_raw_sel<T, true>(row, c, lim, ok, srow, sc);
     } else {
-        return load_raw_sel<T, ALIGNED>(row, c, lim, ok, srow, sc);
+        const bool g = ok && c < lim;
+        const int64_t ca = c < lim - VW ? c : lim - VW, sa = sc < lim - VW ? sc : lim - VW;
+        return load_any<T, false>((g ? row : srow) + (g ? ca : sa));
     }
 }
 
@@ -242,16 +240,48 @@ __device__ __forceinline__ void mfma_gram_tile(const T *__restrict__ X, int64_t 
     const T *pa = X + (ra >= 0 ? ra : 0) * ld;
     const T *pb = X + (rb >= 0 ? rb : 0) * ld;
     const bool same = (ra == rb);
+    const bool useb = !same && rb >= 0;
+    const bool tiny = !ALIGNED && c1 < VW;   // uniform: no whole vector in the row
+    const uvec4 z = {0u, 0u, 0u, 0u};
     for (int64_t c = c0; c < c1; c += 4 * E * U) {
         uvec4 wa[U][NL], wb[U][NL];
+        if (tiny) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t col = c + (int64_t)u * 4 * E + (int64_t)g * E;
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int h = 0; h < NL; ++h) {
-                wa[u][h] = load_gram_sel<T, ALIGNED>(pa, col + h * VW, c1, ra >= 0, X, c0);
-                wb[u][h] = load_gram_sel<T, ALIGNED>(pb, col + h * VW, c1, !same && rb >= 0, X,
-                                                           c0);
+                for (int h = 0; h < NL; ++h) wa[u][h] = wb[u][h] = z;
+            if (g == 0) {
+                wa[0][0] = load_raw<T, false>(pa, 0, c1);
+                wb[0][0] = load_raw<T, false>(pb, 0, c1);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t col = c + (int64_t)u * 4 * E + (int64_t)g * E;
+#pragma unroll
+                for (int h = 0; h < NL; ++h) {
+                    wa[u][h] = load_gram<T, ALIGNED>(pa, col + h * VW, c1, ra >= 0, X, c0);
+                    wb[u][h] = load_gram<T, ALIGNED>(pb, col + h * VW, c1, useb, X, c0);
+                }
+            }
+        }
+        if (!ALIGNED) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t cu = c + (int64_t)u * 4 * E, col = cu + (int64_t)g * E;
+                const bool past = cu >= c1;
+                if (!tiny && !past && cu + 4 * E > c1) {
+#pragma unroll
+                    for (int h = 0; h < NL; ++h) {
+                        wa[u][h] = tail_shift<T>(wa[u][h], col + h * VW, c1);
+                        wb[u][h] = tail_shift<T>(wb[u][h], col + h * VW, c1);
+                    }
+                }
+#pragma unroll
+                for (int h = 0; h < NL; ++h) {
+                    wa[u][h] = !past && ra >= 0 ? wa[u][h] : z;
+                    wb[u][h] = !past && rb >= 0 ? wb[u][h] : z;
+                }
             }
         }
 #pragma unroll
