@@ -26,31 +26,13 @@ constexpr int SEG = 2048;  // columns of one residual segment (x kept in VGPRs)
 // sits in cache, done while the pass streams A (those workgroups of the other
 // segment rows leave at once).
 //
-// SH (rows whose start is 16-byte aligned or half a vector past it: a 16-byte
-// aligned matrix with a row stride of 4 mod 8 elements, BF16 rows of 1000
-// bytes for instance): a row that starts half a vector off is read with the
-// same aligned 16-byte loads moved back by half a vector, against a second
-// copy of x shifted the same way; the vector that would pass the matrix's
-// last element takes the element-wise path, and elements outside the row's
-// columns are cleared.  The other rows take the aligned form.
-//
-// Rows of any other alignment are read with 16-byte loads at the element's own
-// alignment, the last one moved back to the row's last whole vector (load_any,
-// tail_shift).  40009 x 1501 BF16: 83 us with element loads, 28 us; the shift
-// stands after all the group's loads, so that none of them waits for it.
-template <typename T>
-__device__ __forceinline__ uvec4 clear_outside(uvec4 w, int64_t c, int64_t n) {
-    constexpr int VW = Tr<T>::VW;
-    static_assert(sizeof(T) == 2, "shifted rows: 16-bit values");
-#pragma unroll
-    for (int e = 0; e < VW / 2; ++e) {
-        const int64_t c0 = c + 2 * e, c1 = c0 + 1;
-        const uint32_t lo = (c0 >= 0 && c0 < n) ? 0x0000ffffu : 0u;
-        const uint32_t hi = (c1 >= 0 && c1 < n) ? 0xffff0000u : 0u;
-        w[e] &= (lo | hi);
-    }
-    return w;
-}
+// Rows that are not 16-byte aligned are read with 16-byte loads at the element's
+// own alignment, the last one moved back to the row's last whole vector
+// (load_any, tail_shift).  40009 x 1501 BF16: 83 us with element loads, 28 us;
+// the shift stands after all the group's loads, so that none of them waits for
+// it.  (BF16 rows that start half a vector off take longer with aligned loads
+// moved back against a second copy of x: 200000 x 500 63.8 us, 51.9 so; 2400 x
+// 604 11.6 and 4.5.)
 
 // x[c .. c + VW) into registers, zero outside [0, n): 16-byte loads when
 // `vec` (x 16-byte aligned and every lane's slice inside [0, n): a
@@ -81,7 +63,7 @@ __device__ __forceinline__ void x_slice(const V *__restrict__ x, int64_t c, int6
 template <typename T, int SW>
 constexpr int resid_waves() { return (sizeof(T) == 4 && SW == SEG) ? 3 : 8; }
 
-template <typename T, typename V, bool AL, int ROWS, int SW, bool SH = false>
+template <typename T, typename V, bool AL, int ROWS, int SW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, resid_waves<T, SW>())))
 void k_resid_dense(const T *__restrict__ A, int64_t ld,
                                                      int64_t m, int64_t n,
@@ -97,6 +79,10 @@ void k_resid_dense(const T *__restrict__ A, int64_t ld,
     }
     constexpr int VW = Tr<T>::VW;
     constexpr int NVL = SW / (WAVE * VW);
+    // unaligned FP64 rows: two 8-byte loads where the chip waits rather than
+    // streams (800 x 3001 7.2 us, 7.9 with one 16-byte load; 6000 x 601 7.3 and
+    // 8.7), 16-byte ones on the others (14000 x 7999 143 us, 164 with two)
+    constexpr bool HALF = sizeof(T) == 8 && (ROWS == 1 || SW < SEG);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t seg = blockIdx.y;
     const int64_t c0 = seg * SEG;
@@ -108,71 +94,47 @@ void k_resid_dense(const T *__restrict__ A, int64_t ld,
         const int64_t cw = c0 + (int64_t)s * WAVE * VW;
         x_slice<V, VW>(x, cw + (int64_t)lane * VW, n, xal && cw + WAVE * VW <= n, xr[s]);
     }
-    V xs[SH ? NVL : 1][VW];   // x moved back by half a vector (SH)
-    if constexpr (SH) {
-#pragma unroll
-        for (int s = 0; s < NVL; ++s) {
-            const int64_t cw = c0 + (int64_t)s * WAVE * VW - VW / 2;
-            x_slice<V, VW>(x, cw + (int64_t)lane * VW, n, xal && cw >= 0 && cw + WAVE * VW <= n,
-                           xs[s]);
-        }
-    }
-    const int64_t last = (m - 1) * ld + n;   // one past the matrix's last element
     const int64_t bx = (int64_t)blockIdx.x - side.jobs;
     const int64_t nwaves = (int64_t)(gridDim.x - side.jobs) * 4;
     const int64_t stride = nwaves * ROWS;
-    const uvec4 zero = {0u, 0u, 0u, 0u};
     for (int64_t i = (bx * 4 + w) * ROWS; i < m; i += stride) {
         uvec4 raw[ROWS][NVL];
 #pragma unroll
         for (int rr = 0; rr < ROWS; ++rr) {
             const int64_t row = (i + rr < m) ? i + rr : m - 1;
-            if constexpr (SH) {
-                // wave-uniform: does this row start half a vector off?
-                const int64_t sh = ((row * ld) & (VW - 1)) ? VW / 2 : 0;
 #pragma unroll
-                for (int s = 0; s < NVL; ++s) {
-                    const int64_t col = c0 + (int64_t)(s * WAVE + lane) * VW - sh;
-                    uvec4 w;
-                    if (row * ld + col + VW <= last)
-                        w = __builtin_nontemporal_load(
-                            reinterpret_cast<const uvec4 *>(A + row * ld + col));
-                    else
-                        w = load_raw<T, false>(A + row * ld, col, n);
-                    raw[rr][s] = clear_outside<T>(w, col, n);
-                }
-            } else {
-#pragma unroll
-                for (int s = 0; s < NVL; ++s) {
-                    const int64_t col = c0 + (int64_t)(s * WAVE + lane) * VW;
-                    if constexpr (AL)
-                        raw[rr][s] = load_raw_nt_sel<T, AL>(A + row * ld, col, n, true, A + row * ld, c0);
-                    else if (n >= VW)   // uniform; the row's last vector moves down below
-                        raw[rr][s] = load_any<T, true>(A + row * ld + (col + VW <= n ? col : n - VW));
-                    else
-                        raw[rr][s] = load_raw<T, AL>(A + row * ld, col, n);
+            for (int s = 0; s < NVL; ++s) {
+                const int64_t col = c0 + (int64_t)(s * WAVE + lane) * VW;
+                const T *row_p = A + row * ld;
+                if constexpr (AL) {
+                    raw[rr][s] = load_raw_nt_sel<T, AL>(row_p, col, n, true, row_p, c0);
+                } else if constexpr (HALF) {
+                    const double v[2] = {(double)row_p[col < n ? col : n - 1],
+                                         (double)row_p[col + 1 < n ? col + 1 : n - 1]};
+                    __builtin_memcpy(&raw[rr][s], v, 16);
+                } else if (n >= VW) {   // uniform; the row's last vector moves down below
+                    raw[rr][s] = load_any<T, true>(row_p + (col + VW <= n ? col : n - VW));
+                } else {
+                    raw[rr][s] = load_raw<T, AL>(row_p, col, n);
                 }
             }
         }
 #pragma unroll
         for (int rr = 0; rr < ROWS; ++rr) {
             V acc = (V)0;
-            bool shifted = false;
-            if constexpr (SH) {
-                const int64_t row = (i + rr < m) ? i + rr : m - 1;
-                shifted = ((row * ld) & (VW - 1)) != 0;
-            }
 #pragma unroll
             for (int s = 0; s < NVL; ++s) {
-                if constexpr (!AL && !SH) {
+                if constexpr (!AL) {
                     // uniform: the slice that holds the row's end, and those past it
-                    if (n >= VW && c0 + (int64_t)(s + 1) * WAVE * VW > n)
-                        raw[rr][s] = tail_shift<T>(raw[rr][s], c0 + (int64_t)(s * WAVE + lane) * VW, n);
+                    const int64_t col = c0 + (int64_t)(s * WAVE + lane) * VW;
+                    if ((HALF || n >= VW) && c0 + (int64_t)(s + 1) * WAVE * VW > n)
+                        raw[rr][s] = HALF ? mask_raw<T>(raw[rr][s], col, n)
+                                          : tail_shift<T>(raw[rr][s], col, n);
                 }
                 V a[VW];
                 cvt_raw<T, V>(raw[rr][s], a);
 #pragma unroll
-                for (int e = 0; e < VW; ++e) acc = fmaT(a[e], shifted ? xs[s][e] : xr[s][e], acc);
+                for (int e = 0; e < VW; ++e) acc = fmaT(a[e], xr[s][e], acc);
             }
             const V sres = group_sum(acc, WAVE);
             if (lane == 0 && i + rr < m) axp[seg * m + i + rr] = (double)sres;
@@ -180,7 +142,7 @@ void k_resid_dense(const T *__restrict__ A, int64_t ld,
     }
 }
 
-template <typename T, typename V, int ROWS, int SW, bool SH = false>
+template <typename T, typename V, int ROWS, int SW>
 static hipError_t resid_typed(const rorbk_handle_s *h, const void *A, int aligned,
                               const void *x, double *axp, const XgSide &side, hipStream_t s) {
     static_assert(SW == SEG || SW == 512 || SW == 1024, "segment width");
@@ -199,7 +161,7 @@ static hipError_t resid_typed(const rorbk_handle_s *h, const void *A, int aligne
     // 400 x 40001 FP64 50 / 53, 20000 x 450 FP32 36.3 / 37.0, 9000 x 1500 BF16 39 / 53)
     if constexpr (ROWS > 1) {
         if (groups * L.nseg <= (PER_CU > 2 ? 3 : 1) * (int64_t)h->ncu)
-            return resid_typed<T, V, 1, SW, SH>(h, A, aligned, x, axp, side, s);
+            return resid_typed<T, V, 1, SW>(h, A, aligned, x, axp, side, s);
     }
     int64_t cap = PER_CU * (int64_t)h->ncu / L.nseg;
     if (PER_CU > 2) {
@@ -211,12 +173,6 @@ static hipError_t resid_typed(const rorbk_handle_s *h, const void *A, int aligne
     if (cap < 1) cap = 1;
     if (groups > cap) groups = cap;
     dim3 grid((unsigned)(groups + side.jobs), (unsigned)L.nseg);
-    if constexpr (SH) {
-        hipLaunchKernelGGL((k_resid_dense<T, V, false, ROWS, SW, true>), grid, dim3(256), 0, s,
-                           (const T *)A, L.ld, L.m, L.n, (const V *)x, axp,
-                           (const Ctrl *)h->d_ctrl, side);
-        return hipGetLastError();
-    }
     if (aligned)
         hipLaunchKernelGGL((k_resid_dense<T, V, true, ROWS, SW>), grid, dim3(256), 0, s, (const T *)A,
                            L.ld, L.m, L.n, (const V *)x, axp, (const Ctrl *)h->d_ctrl, side);
@@ -250,17 +206,9 @@ hipError_t launch_residual_dense_side(const rorbk_handle_s *h, const void *A, in
         if (n <= 1024) return resid_typed<float, float, 4, 1024>(h, A, aligned, x, axp, side, s);
         return resid_typed<float, float, 2, SEG>(h, A, aligned, x, axp, side, s);
     }
-    // BF16 rows that start 16-byte aligned or half a vector past it (a
-    // 16-byte aligned matrix, row stride 4 mod 8 elements): the shifted form
-    const bool sh = !aligned && (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (h->L.ld & 7) == 4;
-    if (n <= 512)
-        return sh ? resid_typed<bf16_t, float, 16, 512, true>(h, A, aligned, x, axp, side, s)
-                  : resid_typed<bf16_t, float, 16, 512>(h, A, aligned, x, axp, side, s);
-    if (n <= 1024)
-        return sh ? resid_typed<bf16_t, float, 8, 1024, true>(h, A, aligned, x, axp, side, s)
-                  : resid_typed<bf16_t, float, 8, 1024>(h, A, aligned, x, axp, side, s);
-    return sh ? resid_typed<bf16_t, float, 4, SEG, true>(h, A, aligned, x, axp, side, s)
-              : resid_typed<bf16_t, float, 4, SEG>(h, A, aligned, x, axp, side, s);
+    if (n <= 512) return resid_typed<bf16_t, float, 16, 512>(h, A, aligned, x, axp, side, s);
+    if (n <= 1024) return resid_typed<bf16_t, float, 8, 1024>(h, A, aligned, x, axp, side, s);
+    return resid_typed<bf16_t, float, 4, SEG>(h, A, aligned, x, axp, side, s);
 }
 
 }  // namespace rorbk
