@@ -832,8 +832,7 @@ int ror_bk_setup(const rorbk_matrix *A, int64_t block_rows, double lambda, void 
         // spill its registers.  An iteration with two chunks, and with the
         // chain step that took four (us): 4096 columns, blocks of 8 rows 77.1
         // and 82.4, of 16 (FP32) 62.9 and 68.3, of 32 99.0 and 98.2, of 64
-        // 105.0 and 112.4; 3000 columns, 64 rows 87.1 and 95.6; 2049 columns,
-        // 16 rows 85.5 and 85.9, 32 rows 88.5 and 88.9
+        // 105.0 and 112.4; 3000 columns, 64 rows 87.1 and 95.6
         h->chain = (L.K <= 64 && L.n <= 4096 && L.nch_s * L.K <= 8192) ? 1 : 0;
         if (h->chain) {
             int64_t nc = (L.n + 511) / 512;
